@@ -1,10 +1,10 @@
 // dsu_api.hip -- the host-driven single walker of the C ABI (include/dsu.h):
 // a host state machine around three kernels (look-ahead ratio, accept with
-// bordering, flush) plus the FP64 Gauss-Jordan recompute.
+// bordering, flush) plus the FP64 Gauss-Jordan recompute.  A move is one
+// look-ahead launch the host waits for and one accept launch it does not.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -33,24 +33,24 @@ struct dsu_walker {
     int n = 0, np = 0, K = 0, kp = 0, prec = 0, policy = 0, flush_mode = DSU_FLUSH_AUTO;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    WalkerDev wd{};
+    LaDev wd{};
     void *flush_desc = nullptr;     // FlushDesc<T>[1] on the device
     double **a_ptr = nullptr;       // device array {a}
     void **bt_ptr = nullptr;        // device array {bt}
     double *inv_tmp = nullptr;      // n x n FP64 for dsu_get_inverse
     double *row_stage = nullptr;    // mapped pinned host staging: proposal row, then its 3 gradient rows
     const double *row_stage_dev = nullptr;  // its device address
-    double *ratio_h = nullptr;      // pinned host words the propose kernel writes R and grad R into
+    double *words_h = nullptr;      // pinned host words the look-ahead kernel writes R and grad R into
     GjWork gj;
     // host mirror of the state machine
     int k = 0, slots = 0;
-    unsigned tag = 0;               // completion tag of the last look-ahead call
     // multideterminant expansion (FP64 walkers): table, excitations, Q
     MdDev md{};
     bool md_on = false, prop_md = false;
     double md_q = 1.0, md_q_pending = 1.0;
     double *vphi_stage = nullptr;           // mapped pinned staging of the virtual row
-    const double *vphi_stage_dev = nullptr;
+    void *md_part = nullptr;                // partial sums with the expansion's m columns
+    int md_ldp = 0;
     std::vector<int> idx;
     bool has_prop = false;
     int prop_e = -1;
@@ -62,24 +62,23 @@ struct dsu_walker {
 static size_t elem(int prec) { return dsu::elem_size(prec); }
 
 static void walker_md_free(dsu_walker *w) {
-    for (void *p : {(void *)w->md.v, (void *)w->md.t, (void *)w->md.c, (void *)w->md.vphi, (void *)w->md.x,
-                    (void *)w->md.order, (void *)w->md.occ, (void *)w->md.virt, (void *)w->md.coef, (void *)w->md.q})
+    for (void *p : {(void *)w->md.v, (void *)w->md.t, (void *)w->md.vphi, (void *)w->md.x,
+                    (void *)w->md.order, (void *)w->md.occ, (void *)w->md.occ_u, (void *)w->md.virt,
+                    (void *)w->md.uocc, (void *)w->md.cu, (void *)w->md.coef, (void *)w->md.q, w->md_part})
         dfree(p);
     if (w->vphi_stage) (void)hipHostFree(w->vphi_stage);
     w->vphi_stage = nullptr;
-    w->vphi_stage_dev = nullptr;
+    w->md_part = nullptr;
     w->md = MdDev{};
     w->md_on = w->prop_md = false;
 }
 
 static void walker_free(dsu_walker *w) {
-    if (w->wd.phi != (void *)w->wd.phi64) dfree(w->wd.phi);  // FP64 walkers share one row buffer
-    for (void *p : {w->wd.bt, w->wd.u, w->wd.vg, (void *)w->wd.a, (void *)w->wd.phi64, (void *)w->wd.cinv,
-                    (void *)w->wd.gdots,
-                    (void *)w->wd.dots, (void *)w->wd.t, (void *)w->wd.ratio, (void *)w->wd.idx, (void *)w->wd.counter,
-                    w->flush_desc, (void *)w->a_ptr, (void *)w->bt_ptr, (void *)w->inv_tmp})
+    if (w->wd.phi != w->wd.phi64) dfree(w->wd.phi);  // FP64 walkers share one row buffer
+    for (void *p : {w->wd.bt, w->wd.u, w->wd.vg, w->wd.a, w->wd.phi64, w->wd.cinv, w->wd.cinvt, w->wd.part, w->wd.t, w->wd.b,
+                    w->wd.ratio, (void *)w->wd.idx, (void *)w->wd.counter, w->flush_desc, (void *)w->a_ptr, (void *)w->bt_ptr, (void *)w->inv_tmp})
         dfree(p);
-    if (w->ratio_h) (void)hipHostFree(w->ratio_h);
+    if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
     walker_md_free(w);
     w->gj.release();
@@ -139,25 +138,25 @@ extern "C" int dsu_walker_create(int32_t n, int32_t k_delay, int32_t precision, 
     TRY(dev_alloc(&w->wd.bt, np * np * s));
     TRY(dev_alloc(&w->wd.u, kp * np * s));
     TRY(dev_alloc(&w->wd.vg, kp * np * s));
-    TRY(dalloc(&w->wd.a, np * np));
-    // proposal row and its three gradient rows, contiguous (np each)
-    TRY(dalloc(&w->wd.phi64, 4 * np));
+    TRY(dev_alloc(&w->wd.a, np * np * sizeof(double)));
+    TRY(dev_alloc(&w->wd.phi64, np * sizeof(double)));
     if (precision == DSU_FP64) w->wd.phi = w->wd.phi64;
-    else TRY(dev_alloc(&w->wd.phi, 4 * np * s));
-    w->wd.dphi = static_cast<char *>(w->wd.phi) + np * s;
-    TRY(dalloc(&w->wd.gdots, 3 * (kp + 1) + kp));
-    TRY(dalloc(&w->wd.cinv, kp * (kp + 1)));
-    TRY(dalloc(&w->wd.dots, 1 + 2 * kp));
-    TRY(dalloc(&w->wd.t, kp));
-    TRY(dalloc(&w->wd.ratio, 1));
+    else TRY(dev_alloc(&w->wd.phi, np * s));
+    w->wd.ldp = la_ldp((int)kp);
+    TRY(dev_alloc(&w->wd.part, (size_t)kLaBlocks * w->wd.ldp * sizeof(double)));
+    TRY(dev_alloc(&w->wd.cinv, kp * (kp + 1) * sizeof(double)));
+    TRY(dev_alloc(&w->wd.cinvt, kp * (kp + 1) * sizeof(double)));
+    TRY(dev_alloc(&w->wd.t, kp * sizeof(double)));
+    TRY(dev_alloc(&w->wd.b, kp * sizeof(double)));
+    TRY(dev_alloc(&w->wd.ratio, sizeof(double)));
     TRY(dalloc(&w->wd.idx, kp));
     TRY(dalloc(&w->wd.counter, 1));
     w->wd.ldc = (int)kp + 1;
-    // coherent: the host watches the completion tag while the kernel runs
-    if (hipHostMalloc((void **)&w->ratio_h, 5 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
+    // coherent: the host watches the result words while the kernel runs
+    if (hipHostMalloc((void **)&w->words_h, kLaWords * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess)
         TRY(fail(DSU_ENOMEM, "hipHostMalloc failed"));
-    std::memset(w->ratio_h, 0, 5 * sizeof(double));
+    std::memset(w->words_h, 0, kLaWords * sizeof(double));
     if (hipHostMalloc((void **)&w->row_stage, 4 * np * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess)
         TRY(fail(DSU_ENOMEM, "hipHostMalloc failed"));
@@ -169,9 +168,9 @@ extern "C" int dsu_walker_create(int32_t n, int32_t k_delay, int32_t precision, 
     }
     {
         void *dptr = nullptr;
-        if (hipHostGetDevicePointer(&dptr, w->ratio_h, 0) != hipSuccess)
+        if (hipHostGetDevicePointer(&dptr, w->words_h, 0) != hipSuccess)
             TRY(fail(DSU_EDEVICE, "hipHostGetDevicePointer failed"));
-        w->wd.ratio_host = static_cast<double *>(dptr);
+        w->wd.words = static_cast<double *>(dptr);
     }
     // pointer tables for the batched-style launchers
     TRY(dalloc(&w->a_ptr, 1));
@@ -180,13 +179,15 @@ extern "C" int dsu_walker_create(int32_t n, int32_t k_delay, int32_t precision, 
         hipMemcpy(w->bt_ptr, &w->wd.bt, sizeof(void *), hipMemcpyHostToDevice) != hipSuccess)
         TRY(fail(DSU_EDEVICE, "pointer table upload failed"));
     if (precision == DSU_FP64) {
-        FlushDesc<double> fd{(double *)w->wd.bt, (const double *)w->wd.u, (const double *)w->wd.vg, w->wd.cinv,
+        FlushDesc<double> fd{(double *)w->wd.bt, (const double *)w->wd.u, (const double *)w->wd.vg,
+                             (const double *)w->wd.cinv,
                              w->wd.idx, w->wd.ldc};
         TRY(dev_alloc(&w->flush_desc, sizeof(fd)));
         if (hipMemcpy(w->flush_desc, &fd, sizeof(fd), hipMemcpyHostToDevice) != hipSuccess)
             TRY(fail(DSU_EDEVICE, "descriptor upload failed"));
     } else {
-        FlushDesc<float> fd{(float *)w->wd.bt, (const float *)w->wd.u, (const float *)w->wd.vg, w->wd.cinv,
+        FlushDesc<float> fd{(float *)w->wd.bt, (const float *)w->wd.u, (const float *)w->wd.vg,
+                            (const double *)w->wd.cinv,
                             w->wd.idx, w->wd.ldc};
         TRY(dev_alloc(&w->flush_desc, sizeof(fd)));
         if (hipMemcpy(w->flush_desc, &fd, sizeof(fd), hipMemcpyHostToDevice) != hipSuccess)
@@ -230,35 +231,22 @@ extern "C" int dsu_flush(dsu_walker *w) {
     return walker_do_flush(w);
 }
 
-// Wait for the look-ahead kernel of call `tag`: it writes the tag to mapped
-// host memory after its results, so watching that word returns as soon as the
-// results are there.  After 2 s of no tag the stream is synchronised instead,
-// which reports a failed kernel.
-static int walker_wait(dsu_walker *w, unsigned tag) {
-    const volatile double *h = w->ratio_h;
-    const auto t0 = std::chrono::steady_clock::now();
-    for (unsigned spin = 0;; ++spin) {
-        if (h[4] == (double)tag) return DSU_OK;
-        if ((spin & 4095u) == 4095u && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) break;
-    }
-    HIPCHK(hipStreamSynchronize(w->stream));
-    if (h[4] != (double)tag) return fail(DSU_EDEVICE, "look-ahead kernel did not report");
-    return DSU_OK;
-}
-
-static int walker_propose_common(dsu_walker *w, int e, double *ratio_out, double *grad_out = nullptr) {
+// Look-ahead of the row(s) in `src` against electron e; the proposal becomes pending.
+static int walker_propose_common(dsu_walker *w, const LaSource &src, int e, double *ratio_out,
+                                 double *grad_out = nullptr) {
     // an electron may hold at most one pending move: apply the window first
     for (int j = 0; j < w->k; ++j)
         if (w->idx[j] == e) {
             CHK(walker_do_flush(w));
             break;
         }
-    const int gm = grad_out ? 1 : 0;
-    const unsigned tag = ++w->tag;
-    if (w->prec == DSU_FP64) HIPCHK(launch_walker_propose<double>(&w->wd, w->n, w->np, w->k, e, gm, -1, tag, w->stream));
-    else HIPCHK(launch_walker_propose<float>(&w->wd, w->n, w->np, w->k, e, gm, -1, tag, w->stream));
-    CHK(walker_wait(w, tag));
-    const volatile double *h = w->ratio_h;
+    const int gm = grad_out ? 1 : 0, words = grad_out ? 4 : 1;
+    la_arm(w->words_h, 0, words);
+    if (w->prec == DSU_FP64)
+        HIPCHK(launch_walker_propose<double>(w->wd, src, w->n, w->np, w->k, e, gm, -1, w->stream));
+    else HIPCHK(launch_walker_propose<float>(w->wd, src, w->n, w->np, w->k, e, gm, -1, w->stream));
+    CHK(la_wait(w->words_h, 0, words, w->stream));
+    const volatile double *h = w->words_h;
     const double r = h[0];
     w->has_prop = true;
     w->prop_e = e;
@@ -269,23 +257,17 @@ static int walker_propose_common(dsu_walker *w, int e, double *ratio_out, double
     return DSU_OK;
 }
 
-// Stage `nrows` host rows (n FP64 each) at row `first` of the walker's
-// 4-row block (0 = proposal, 1..3 = gradient rows), zero padded to np, and
-// convert them to the walker's precision.
-static int walker_stage_rows(dsu_walker *w, int first, int nrows, const double *const *rows) {
-    // every earlier copy out of the staging buffer was followed on the stream
-    // by a look-ahead kernel the host waited for, so the buffer is free
+// Copy `nrows` host rows (n FP64 each) into the pinned staging rows the
+// look-ahead kernel reads, zero padded to np.  Every earlier look-ahead was
+// waited for, so the rows are free.
+static LaSource walker_stage_rows(dsu_walker *w, int nrows, const double *const *rows) {
     const size_t np = w->np;
-    double *st = w->row_stage + first * np;
     for (int r = 0; r < nrows; ++r) {
-        std::memcpy(st + r * np, rows[r], sizeof(double) * w->n);
-        std::memset(st + r * np + w->n, 0, sizeof(double) * (np - w->n));
+        double *st = w->row_stage + r * np;
+        std::memcpy(st, rows[r], sizeof(double) * w->n);
+        std::memset(st + w->n, 0, sizeof(double) * (np - w->n));
     }
-    // read over the host link by one small kernel (no runtime copy)
-    HIPCHK(launch_rows_from_host(w->row_stage_dev + first * np, w->wd.phi64 + first * np,
-                                 w->prec == DSU_FP64 ? nullptr : static_cast<float *>(w->wd.phi) + first * np,
-                                 (int)(nrows * np), w->stream));
-    return DSU_OK;
+    return LaSource{w->row_stage_dev, nullptr};
 }
 
 extern "C" int dsu_propose_ratio(dsu_walker *w, int32_t electron, const double *phi_host, double *ratio_out) {
@@ -293,8 +275,7 @@ extern "C" int dsu_propose_ratio(dsu_walker *w, int32_t electron, const double *
     if (w->md_on) return fail(DSU_ESTATE, "multideterminant walker: propose with dsu_propose_ratio_md");
     if (electron < 0 || electron >= w->n) return fail(DSU_EINVAL, "electron %d out of range", electron);
     if (!phi_host) return fail(DSU_EINVAL, "row is NULL");
-    CHK(walker_stage_rows(w, 0, 1, &phi_host));
-    return walker_propose_common(w, electron, ratio_out);
+    return walker_propose_common(w, walker_stage_rows(w, 1, &phi_host), electron, ratio_out);
 }
 
 extern "C" int dsu_propose_ratio_grad(dsu_walker *w, int32_t electron, const double *phi_host, const double *dphi_host,
@@ -304,8 +285,7 @@ extern "C" int dsu_propose_ratio_grad(dsu_walker *w, int32_t electron, const dou
     if (electron < 0 || electron >= w->n) return fail(DSU_EINVAL, "electron %d out of range", electron);
     if (!phi_host || !dphi_host || !grad_out) return fail(DSU_EINVAL, "NULL argument");
     const double *rows[4] = {phi_host, dphi_host, dphi_host + w->n, dphi_host + 2 * (size_t)w->n};
-    CHK(walker_stage_rows(w, 0, 4, rows));
-    return walker_propose_common(w, electron, ratio_out, grad_out);
+    return walker_propose_common(w, walker_stage_rows(w, 4, rows), electron, ratio_out, grad_out);
 }
 
 extern "C" int dsu_eval_grad(dsu_walker *w, int32_t electron, const double *dphi_host, double *grad_out) {
@@ -313,16 +293,16 @@ extern "C" int dsu_eval_grad(dsu_walker *w, int32_t electron, const double *dphi
     if (electron < 0 || electron >= w->n) return fail(DSU_EINVAL, "electron %d out of range", electron);
     if (!dphi_host || !grad_out) return fail(DSU_EINVAL, "NULL argument");
     const double *rows[3] = {dphi_host, dphi_host + w->n, dphi_host + 2 * (size_t)w->n};
-    CHK(walker_stage_rows(w, 1, 3, rows));
+    const LaSource src = walker_stage_rows(w, 3, rows);
     int m = -1;  // pending slot holding this electron's accepted move, if any
     for (int j = 0; j < w->k; ++j)
         if (w->idx[j] == electron) m = j;
-    const unsigned tag = ++w->tag;
+    la_arm(w->words_h, 1, 3);
     if (w->prec == DSU_FP64)
-        HIPCHK(launch_walker_propose<double>(&w->wd, w->n, w->np, w->k, electron, 2, m, tag, w->stream));
-    else HIPCHK(launch_walker_propose<float>(&w->wd, w->n, w->np, w->k, electron, 2, m, tag, w->stream));
-    CHK(walker_wait(w, tag));
-    const volatile double *h = w->ratio_h;
+        HIPCHK(launch_walker_propose<double>(w->wd, src, w->n, w->np, w->k, electron, 2, m, w->stream));
+    else HIPCHK(launch_walker_propose<float>(w->wd, src, w->n, w->np, w->k, electron, 2, m, w->stream));
+    CHK(la_wait(w->words_h, 1, 3, w->stream));
+    const volatile double *h = w->words_h;
     for (int a = 0; a < 3; ++a) grad_out[a] = h[1 + a];
     return DSU_OK;
 }
@@ -332,14 +312,7 @@ extern "C" int dsu_propose_ratio_dev(dsu_walker *w, int32_t electron, const void
     if (w->md_on) return fail(DSU_ESTATE, "multideterminant walker: propose with dsu_propose_ratio_md");
     if (electron < 0 || electron >= w->n) return fail(DSU_EINVAL, "electron %d out of range", electron);
     if (!phi_dev) return fail(DSU_EINVAL, "row is NULL");
-    if (w->prec == DSU_FP64) {
-        HIPCHK(launch_row_to((const double *)phi_dev, w->wd.phi64, 0, w->n, w->np, w->stream));
-    } else {
-        HIPCHK(hipMemsetAsync(w->wd.phi, 0, sizeof(float) * w->np, w->stream));
-        HIPCHK(hipMemcpyAsync(w->wd.phi, phi_dev, sizeof(float) * w->n, hipMemcpyDeviceToDevice, w->stream));
-        HIPCHK(launch_row_to((const double *)w->wd.phi, w->wd.phi64, 2, w->n, w->np, w->stream));
-    }
-    return walker_propose_common(w, electron, ratio_out);
+    return walker_propose_common(w, LaSource{nullptr, phi_dev}, electron, ratio_out);
 }
 
 static int walker_slot_used(dsu_walker *w) {
@@ -357,12 +330,14 @@ extern "C" int dsu_accept(dsu_walker *w) {
     if (!(std::fabs(r) > floor) || !std::isfinite(r)) return fail(DSU_ESINGULAR, "ratio %g cannot be accepted", r);
     if (w->prop_md && !(std::fabs(w->md_q_pending) > 0.0 && std::isfinite(w->md_q_pending)))
         return fail(DSU_ESINGULAR, "the expansion vanishes at the proposed configuration");
-    if (w->prec == DSU_FP64) HIPCHK(launch_walker_accept<double>(&w->wd, w->n, w->np, w->k, w->kp, w->prop_e, w->stream));
-    else HIPCHK(launch_walker_accept<float>(&w->wd, w->n, w->np, w->k, w->kp, w->prop_e, w->stream));
     if (w->prop_md) {
-        HIPCHK(launch_md_accept(&w->md, w->n, w->np, w->prop_e, w->stream));
+        HIPCHK(launch_md_accept(w->wd, w->md, w->n, w->np, w->k, w->prop_e, w->stream));
         w->md_q = w->md_q_pending;
         w->prop_md = false;
+    } else if (w->prec == DSU_FP64) {
+        HIPCHK(launch_walker_accept<double>(w->wd, w->n, w->np, w->k, w->prop_e, w->stream));
+    } else {
+        HIPCHK(launch_walker_accept<float>(w->wd, w->n, w->np, w->k, w->prop_e, w->stream));
     }
     w->idx[w->k] = w->prop_e;
     ++w->k;
@@ -449,11 +424,11 @@ extern "C" int dsu_walker_set_flush_kernel(dsu_walker *w, int32_t mode) {
 // ==========================================================================
 // Table T = A^{-1} V from the present (flushed) inverse, and Q of the present table.
 static int walker_md_refresh(dsu_walker *w) {
-    HIPCHK(launch_md_table(&w->wd, &w->md, w->n, w->np, w->stream));
-    const unsigned tag = ++w->tag;
-    HIPCHK(launch_md_init(&w->wd, &w->md, tag, w->stream));
-    CHK(walker_wait(w, tag));
-    const double q = ((const volatile double *)w->ratio_h)[2];
+    HIPCHK(launch_md_table(w->wd, w->md, w->n, w->np, w->stream));
+    la_arm(w->words_h, 2, 1);
+    HIPCHK(launch_md_init(w->wd, w->md, w->stream));
+    CHK(la_wait(w->words_h, 2, 1, w->stream));
+    const double q = ((const volatile double *)w->words_h)[2];
     if (!(std::fabs(q) > 0.0) || !std::isfinite(q)) return fail(DSU_ESINGULAR, "the expansion vanishes (Q = %g)", q);
     w->md_q = q;
     return DSU_OK;
@@ -493,7 +468,24 @@ extern "C" int dsu_walker_set_multidet(dsu_walker *w, int32_t m, const double *v
     } while (0)
     MDTRY(dalloc(&w->md.v, np * m));
     MDTRY(dalloc(&w->md.t, np * m));
-    MDTRY(dalloc(&w->md.c, np));
+    // the occupied orbitals the expansion replaces, each once
+    std::vector<int> place(w->n, -1), uocc, occ_u(4 * (size_t)ndet, 0);
+    for (int d = 0; d < ndet; ++d)
+        for (int a = 0; a < order[d]; ++a) {
+            const int j = occ[4 * d + a];
+            if (place[j] < 0) {
+                place[j] = (int)uocc.size();
+                uocc.push_back(j);
+            }
+            occ_u[4 * (size_t)d + a] = place[j];
+        }
+    w->md.nu = (int)uocc.size();
+    uocc.push_back(0);  // never empty
+    MDTRY(dalloc(&w->md.uocc, uocc.size()));
+    MDTRY(dalloc(&w->md.cu, uocc.size()));
+    MDTRY(dalloc(&w->md.occ_u, 4 * (size_t)ndet));
+    w->md_ldp = la_ldp(w->kp) + m;
+    MDTRY(dev_alloc(&w->md_part, (size_t)kLaBlocks * w->md_ldp * sizeof(double)));
     MDTRY(dalloc(&w->md.vphi, (size_t)m));
     MDTRY(dalloc(&w->md.x, (size_t)m));
     MDTRY(dalloc(&w->md.order, (size_t)ndet));
@@ -508,13 +500,15 @@ extern "C" int dsu_walker_set_multidet(dsu_walker *w, int32_t m, const double *v
         void *dptr = nullptr;
         if (hipHostGetDevicePointer(&dptr, w->vphi_stage, 0) != hipSuccess)
             MDTRY(fail(DSU_EDEVICE, "hipHostGetDevicePointer failed"));
-        w->vphi_stage_dev = static_cast<const double *>(dptr);
+        w->md.vphi_host = static_cast<const double *>(dptr);
     }
     w->md.m = m;
     w->md.ndet = ndet;
     if (hipMemcpy(w->md.v, virt_host, sizeof(double) * w->n * m, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w->md.order, order, sizeof(int) * ndet, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w->md.occ, occ, sizeof(int) * 4 * ndet, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(w->md.occ_u, occ_u.data(), sizeof(int) * 4 * ndet, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(w->md.uocc, uocc.data(), sizeof(int) * uocc.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w->md.virt, virt, sizeof(int) * 4 * ndet, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w->md.coef, coef, sizeof(double) * ndet, hipMemcpyHostToDevice) != hipSuccess)
         MDTRY(fail(DSU_EDEVICE, "expansion upload failed"));
@@ -530,21 +524,21 @@ extern "C" int dsu_propose_ratio_md(dsu_walker *w, int32_t electron, const doubl
     if (!w->md_on) return fail(DSU_ESTATE, "no multideterminant expansion set");
     if (electron < 0 || electron >= w->n) return fail(DSU_EINVAL, "electron %d out of range", electron);
     if (!phi_host || !vphi_host) return fail(DSU_EINVAL, "row is NULL");
-    CHK(walker_stage_rows(w, 0, 1, &phi_host));
+    const LaSource src = walker_stage_rows(w, 1, &phi_host);
     std::memcpy(w->vphi_stage, vphi_host, sizeof(double) * w->md.m);
-    HIPCHK(launch_rows_from_host(w->vphi_stage_dev, w->md.vphi, nullptr, w->md.m, w->stream));
     // an electron may hold at most one pending move: apply the window first
     for (int j = 0; j < w->k; ++j)
         if (w->idx[j] == electron) {
             CHK(walker_do_flush(w));
             break;
         }
-    const unsigned t1 = ++w->tag;
-    HIPCHK(launch_walker_propose<double>(&w->wd, w->n, w->np, w->k, electron, 0, -1, t1, w->stream));
-    const unsigned t2 = ++w->tag;
-    HIPCHK(launch_md_propose(&w->wd, &w->md, w->n, w->np, w->k, electron, t2, w->stream));
-    CHK(walker_wait(w, t2));
-    const volatile double *h = w->ratio_h;
+    LaDev wd = w->wd;  // with room for the expansion's columns in the partial sums
+    wd.part = w->md_part;
+    wd.ldp = w->md_ldp;
+    la_arm(w->words_h, 0, 3);
+    HIPCHK(launch_md_propose(wd, src, w->md, w->n, w->np, w->k, electron, w->stream));
+    CHK(la_wait(w->words_h, 0, 3, w->stream));
+    const volatile double *h = w->words_h;
     const double total = h[0], r = h[1], q = h[2];
     w->has_prop = true;
     w->prop_e = electron;

@@ -1,70 +1,88 @@
-// walker.hpp -- device state and kernel launchers of the host-driven single
-// walker (look-ahead ratio, its gradient, accept with bordering).
+// walker.hpp -- device state and kernel launchers of the host-driven walkers
+// (look-ahead ratio, its gradient, accept with bordering).
 #pragma once
 #include "dsu_internal.hpp"
 
 namespace dsu {
 
-// Single-walker device state (one walker, precision T behind the void*).
-struct WalkerDev {
-    void *bt;          // np x np, T
-    void *u;           // kp x np, T
-    void *vg;          // kp x np, T
-    double *a;         // np x np, FP64 Slater matrix
-    void *phi;         // np, T: pending proposal row
-    double *phi64;     // np, FP64 copy of the proposal row
-    double *cinv;      // kp x (kp+1): C_k^{-1} in pending order
-    double *dots;      // 1 + 2 kp: r0, p[0..k), q[0..k)
-    double *t;         // kp: C_k^{-1} q
-    double *ratio;     // device copy of R
-    double *ratio_host;// pinned host memory (mapped): R, grad R (or the drift), then the call's completion tag
-    void *dphi;        // 3 x np, T: gradient rows (x, y, z) of the proposal or of the present row
-    double *gdots;     // 3 (kp + 1) + kp: gradient rows against BT[e] and Vg, then q of the drift call
-    int *idx;          // kp pending electrons
-    unsigned *counter; // blocks finished (last-block reduction)
-    int ldc;           // kp + 1
+// Blocks of a look-ahead launch at most.
+constexpr int kLaBlocks = 32;
+// Host result words before a launch: a signalling NaN no arithmetic produces.
+constexpr unsigned long long kLaPending = 0x7FF4A5C35A3C1E0Full;
+constexpr int kLaWords = 4;
+
+// Device state of a host-driven walker.  Element type T (float, double, or
+// interleaved complex double2) and K x K type S (double or double2).
+struct LaDev {
+    void *bt;       // np x np, T
+    void *u;        // kp x np, T
+    void *vg;       // kp x np, T
+    void *a;        // np x np, S: Slater matrix
+    void *phi;      // np, T: pending proposal row
+    void *phi64;    // np, S: the same before rounding to T (phi itself if T = S)
+    void *cinv;     // kp x ldc, S: C_k^{-1} in pending order
+    void *cinvt;    // kp x ldc, S: its transpose
+    void *t;        // kp, S: C_k^{-1} q of the pending proposal
+    void *b;        // kp, S: p^T C_k^{-1}
+    void *ratio;    // S: device copy of R
+    void *part;     // kLaBlocks x ldp, S: the blocks' partial sums
+    double *words;  // kLaWords mapped pinned host words: results (R; grad R or the drift in 1..3)
+    int *idx;       // kp pending electrons
+    unsigned *counter;  // blocks finished (last-block reduction)
+    int ldc;        // kp + 1
+    int ldp;        // partial sums a block leaves
+};
+
+// Where a launch reads the proposed rows: FP64 host rows in mapped pinned
+// memory (stride np, zero padded), or one device row of n elements of T.
+struct LaSource {
+    const void *host;
+    const void *dev;
 };
 
 // Multideterminant state of an FP64 walker (single-reference expansion).
 struct MdDev {
     double *v;      // np x m: virtual orbitals, row i = electron i (zero rows past n)
     double *t;      // np x m: table T = A^{-1} V (row j = occupied orbital j)
-    double *c;      // np: column e of the current inverse (look-ahead corrected)
     double *vphi;   // m: virtual row of the proposal
+    const double *vphi_host;  // the same in mapped pinned host memory
     double *x;      // m: (vphi - phi T) / R
     int *order;     // ndet: substitutions per determinant (0..4)
     int *occ;       // ndet x 4: occupied orbitals replaced
+    int *occ_u;     // ndet x 4: their places in uocc
     int *virt;      // ndet x 4: virtual orbitals put in their place
+    int *uocc;      // nu: the occupied orbitals the expansion replaces, each once
+    double *cu;     // nu: column e of the current inverse (look-ahead corrected) at uocc
     double *coef;   // ndet
     double *q;      // [0]: sum_I c_I det S_I of the pending proposal; [1]: of the present state
-    int m, ndet;
+    int m, ndet, nu;
 };
 
-// Single-walker look-ahead ratio and accept (bordering).
+// Partial sums per block at delay kp: four x rows against BT[e] and Vg, then q
+// (and m columns of phi T).
+inline int la_ldp(int kp) { return 4 * (kp + 1) + kp; }
+
+// Single-walker look-ahead ratio and accept (bordering); lookahead.hpp.
 // grad_mode 0: ratio; 1: ratio and its gradient; 2: gradient of the present
-// row only (m = pending slot held by e, or -1).  The results are written to
-// ratio_host, then `tag` to ratio_host[4] (after a system-scope fence), so the
-// host can wait for the call by watching that word.
+// row only (m = pending slot held by e, or -1).
 template <typename T>
-hipError_t launch_walker_propose(WalkerDev *wd, int n, int np, int k, int e, int grad_mode, int m, unsigned tag,
+hipError_t launch_walker_propose(const LaDev &w, const LaSource &src, int n, int np, int k, int e, int grad_mode, int m,
                                  hipStream_t s);
-template <typename T>
-hipError_t launch_walker_accept(WalkerDev *wd, int n, int np, int k, int kp, int e, hipStream_t s);
-// Row copy into a padded device row: mode 0 FP64->FP64, 1 FP64->float, 2 float->FP64.
-hipError_t launch_row_to(const double *src, void *dst, int mode, int n, int np, hipStream_t s);
-// count FP64 values from mapped pinned host memory (device address) into
-// dst64 and, if dst32 is not NULL, their float casts into dst32.
-hipError_t launch_rows_from_host(const double *src_mapped, double *dst64, float *dst32, int count, hipStream_t s);
-// Multideterminant steps (FP64).  table: T = BT^T V.  propose: after the
-// look-ahead kernel (ratio R and t in *wd), c = BT[e] - sum_j t_j Vg[j], x =
-// (vphi - phi T) / R, Q' = sum_I c_I det(S_I + c_J x_V) -> ratio_host[0..2] =
-// (R Q' / Q, R, Q'), then `tag` to ratio_host[4].  init: Q = sum_I c_I det S_I
-// of the present table -> q[1] and ratio_host[2], then the tag.  accept:
-// T += c x, V[e] = vphi, Q = Q'.
-hipError_t launch_md_table(const WalkerDev *wd, const MdDev *md, int n, int np, hipStream_t s);
-hipError_t launch_md_propose(const WalkerDev *wd, const MdDev *md, int n, int np, int k, int e, unsigned tag,
+template <typename T> hipError_t launch_walker_accept(const LaDev &w, int n, int np, int k, int e, hipStream_t s);
+// Multideterminant steps (FP64).  table: T = BT^T V.  propose: the look-ahead
+// and Q' = sum_I c_I det(S_I + c_J x_V); words 0..2 = (R Q' / Q, R, Q').
+// init: Q = sum_I c_I det S_I of the present table -> q[1] and word 2.
+// accept: the acceptance, T += c x, V[e] = vphi, Q = Q'.
+hipError_t launch_md_table(const LaDev &w, const MdDev &md, int n, int np, hipStream_t s);
+hipError_t launch_md_propose(const LaDev &w, const LaSource &src, const MdDev &md, int n, int np, int k, int e,
                              hipStream_t s);
-hipError_t launch_md_init(const WalkerDev *wd, const MdDev *md, unsigned tag, hipStream_t s);
-hipError_t launch_md_accept(const MdDev *md, int n, int np, int e, hipStream_t s);
+hipError_t launch_md_init(const LaDev &w, const MdDev &md, hipStream_t s);
+hipError_t launch_md_accept(const LaDev &w, const MdDev &md, int n, int np, int k, int e, hipStream_t s);
+
+// Host side of the result words: la_arm marks `count` of them pending before
+// the launch, la_wait returns once each holds a result (after 2 s without one
+// the stream is synchronised instead, which reports a failed kernel).
+void la_arm(double *words, int first, int count);
+int la_wait(const double *words, int first, int count, hipStream_t s);
 
 }  // namespace dsu

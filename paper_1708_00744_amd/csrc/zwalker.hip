@@ -10,12 +10,12 @@
 // Complex values are stored interleaved (re, im) as double2.
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
 #include "host_common.hpp"
+#include "lookahead.hpp"
 
 namespace dsu {
 
@@ -31,19 +31,14 @@ __device__ __forceinline__ zc zinv(zc a) {
     return make_double2(a.x / d, -a.y / d);
 }
 
+// Beside the look-ahead state: the flush's and the inversion's work arrays.
 struct ZWalkerDev {
     zc *bt;            // np x np
     zc *u;             // kp x np: new rows of the pending moves
     zc *vg;            // kp x np: stale BT rows of the pending electrons
     zc *a;             // np x np: Slater matrix
-    zc *phi;           // np: pending proposal row
     zc *cinv;          // kp x (kp + 1): C_k^{-1} in pending order
-    zc *dots;          // 1 + 2 kp: r0, p[0..k), q[0..k)
-    zc *t;             // kp: C_k^{-1} q
-    zc *ratio;         // device copy of R
-    double *ratio_host;// mapped pinned: R (re, im), then the call's completion tag
     int *idx;          // kp pending electrons
-    unsigned *counter; // blocks finished (last-block reduction)
     zc *w;             // np x (kp + 1): flush scratch W
     zc *fcol;          // np: Gauss-Jordan multipliers
     int *piv;          // np: Gauss-Jordan row interchanges
@@ -51,99 +46,6 @@ struct ZWalkerDev {
     int *status;       // 1 if a pivot is singular to working precision
     int ldc;           // kp + 1
 };
-
-__device__ __forceinline__ zc block_zsum(zc v, zc *sbuf) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        v.x += __shfl_xor(v.x, o, 64);
-        v.y += __shfl_xor(v.y, o, 64);
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) sbuf[wave] = v;
-    __syncthreads();
-    zc s = make_double2(0.0, 0.0);
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) s = make_double2(s.x + sbuf[q].x, s.y + sbuf[q].y);
-    return s;
-}
-
-// Look-ahead ratio: 2k+1 blocks (r0, p, q dot products); the last block to
-// finish forms t = C_k^{-1} q and R = r0 - p.t.
-__global__ __launch_bounds__(kThreads) void k_zpropose(ZWalkerDev w, int np, int k, int e, unsigned tag) {
-    __shared__ zc sbuf[kThreads / 64];
-    __shared__ int is_last;
-    __shared__ zc s_t[DSU_KMAX_LDS];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    const zc *x, *yv;
-    if (b == 0) { x = w.phi; yv = w.bt + (size_t)e * np; }
-    else if (b <= k) { x = w.phi; yv = w.vg + (size_t)(b - 1) * np; }
-    else { x = w.u + (size_t)(b - 1 - k) * np; yv = w.bt + (size_t)e * np; }
-    zc acc = make_double2(0.0, 0.0);
-    for (int c = tid; c < np; c += kThreads) acc = zfma(x[c], yv[c], acc);
-    acc = block_zsum(acc, sbuf);
-    if (tid == 0) {
-        w.dots[b] = acc;
-        __threadfence();
-        is_last = atomicAdd(w.counter, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!is_last) return;
-    __threadfence();
-    for (int i = tid; i < k; i += kThreads) {
-        zc s = make_double2(0.0, 0.0);
-        for (int j = 0; j < k; ++j) s = zfma(w.cinv[(size_t)i * w.ldc + j], w.dots[1 + k + j], s);
-        s_t[i] = s;
-        w.t[i] = s;
-    }
-    __syncthreads();
-    zc part = make_double2(0.0, 0.0);
-    for (int i = tid; i < k; i += kThreads) part = zfma(w.dots[1 + i], s_t[i], part);
-    part = block_zsum(part, sbuf);
-    if (tid == 0) {
-        const zc r = zsub(w.dots[0], part);
-        w.ratio[0] = r;
-        w.ratio_host[0] = r.x;
-        w.ratio_host[1] = r.y;
-        *w.counter = 0u;
-        __threadfence_system();  // the ratio reaches host memory before the tag
-        w.ratio_host[2] = (double)tag;
-    }
-}
-
-// Bordering on acceptance (one block):
-//   C_{k+1}^{-1} = [[C^{-1} + t b^T / R, -t / R], [-b^T / R, 1 / R]],
-//   t = C^{-1} q, b^T = p^T C^{-1}; then append U, Vg, A rows and the electron.
-__global__ __launch_bounds__(kThreads) void k_zaccept(ZWalkerDev w, int np, int k, int e) {
-    __shared__ zc s_b[DSU_KMAX_LDS];
-    __shared__ zc s_t[DSU_KMAX_LDS];
-    const int tid = threadIdx.x;
-    const zc rinv = zinv(w.ratio[0]);
-    for (int j = tid; j < k; j += kThreads) {
-        zc s = make_double2(0.0, 0.0);
-        for (int i = 0; i < k; ++i) s = zfma(w.dots[1 + i], w.cinv[(size_t)i * w.ldc + j], s);
-        s_b[j] = zmul(s, rinv);
-        s_t[j] = w.t[j];
-    }
-    __syncthreads();
-    const int k1 = k + 1;
-    for (int v = tid; v < k1 * k1; v += kThreads) {
-        const int i = v / k1, j = v % k1;
-        zc *c = w.cinv + (size_t)i * w.ldc + j;
-        if (i < k && j < k) *c = zfma(s_t[i], s_b[j], *c);
-        else if (i < k) {
-            const zc v = zmul(s_t[i], rinv);
-            *c = make_double2(-v.x, -v.y);
-        }
-        else if (j < k) *c = make_double2(-s_b[j].x, -s_b[j].y);
-        else *c = rinv;
-    }
-    for (int c = tid; c < np; c += kThreads) {
-        w.u[(size_t)k * np + c] = w.phi[c];
-        w.vg[(size_t)k * np + c] = w.bt[(size_t)e * np + c];
-        w.a[(size_t)e * np + c] = w.phi[c];
-    }
-    if (tid == 0) w.idx[k] = e;
-}
 
 // C[M x N] = (or -=) A[M x Kd] op(B); op(B) = B^T with B stored N x Kd when
 // TRANSB, else B stored Kd x N.  64 x 64 tile per workgroup, 4 x 4 per thread.
@@ -363,12 +265,6 @@ __global__ void k_zgj_unperm(ZWalkerDev w, int ld, int n) {
     }
 }
 
-// The proposal row from mapped pinned host memory (read once over the host link).
-__global__ void k_zrow_from_host(const double *src, zc *phi, int np) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < np) phi[c] = make_double2(src[2 * c], src[2 * c + 1]);
-}
-
 // out[i][j] = BT[j][i] (A^{-1}, n x n).
 __global__ void k_zuntranspose(const zc *bt, zc *out, int n, int np) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
@@ -389,12 +285,12 @@ struct dsu_zwalker {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     ZWalkerDev wd{};
-    double *ratio_h = nullptr;
+    LaDev la{};                             // look-ahead state (shares bt, u, vg, a, cinv, idx)
+    double *words_h = nullptr;              // pinned host words the look-ahead kernel writes R into
     double *row_stage = nullptr;            // mapped pinned host staging of a proposal row
     const double *row_stage_dev = nullptr;  // its device address
     zc *inv_tmp = nullptr;
     int k = 0, slots = 0;
-    unsigned tag = 0;  // completion tag of the last look-ahead call
     std::vector<int> idx;
     bool has_prop = false;
     int prop_e = -1;
@@ -410,12 +306,12 @@ static double wrap_phase(double p) {
 }
 
 static void zwalker_free(dsu_zwalker *w) {
-    for (void *p : {(void *)w->wd.bt, (void *)w->wd.u, (void *)w->wd.vg, (void *)w->wd.a, (void *)w->wd.phi,
-                    (void *)w->wd.cinv, (void *)w->wd.dots, (void *)w->wd.t, (void *)w->wd.ratio, (void *)w->wd.idx,
-                    (void *)w->wd.counter, (void *)w->wd.w, (void *)w->wd.fcol, (void *)w->wd.piv,
+    for (void *p : {(void *)w->wd.bt, (void *)w->wd.u, (void *)w->wd.vg, (void *)w->wd.a, w->la.phi,
+                    (void *)w->wd.cinv, w->la.cinvt, w->la.part, w->la.t, w->la.b, w->la.ratio, (void *)w->wd.idx,
+                    (void *)w->la.counter, (void *)w->wd.w, (void *)w->wd.fcol, (void *)w->wd.piv,
                     (void *)w->wd.stat, (void *)w->wd.status, (void *)w->inv_tmp, (void *)w->vh})
         dfree(p);
-    if (w->ratio_h) (void)hipHostFree(w->ratio_h);
+    if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
     if (w->own_stream && w->stream) (void)hipStreamDestroy(w->stream);
 }
@@ -509,13 +405,23 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     TRY(dalloc(&w->wd.u, kp * np));
     TRY(dalloc(&w->wd.vg, kp * np));
     TRY(dalloc(&w->wd.a, np * np));
-    TRY(dalloc(&w->wd.phi, np));
     TRY(dalloc(&w->wd.cinv, kp * (kp + 1)));
-    TRY(dalloc(&w->wd.dots, 1 + 2 * kp));
-    TRY(dalloc(&w->wd.t, kp));
-    TRY(dalloc(&w->wd.ratio, 1));
     TRY(dalloc(&w->wd.idx, kp));
-    TRY(dalloc(&w->wd.counter, 1));
+    TRY(dev_alloc(&w->la.cinvt, kp * (kp + 1) * sizeof(zc)));
+    TRY(dev_alloc(&w->la.phi, np * sizeof(zc)));
+    TRY(dev_alloc(&w->la.t, kp * sizeof(zc)));
+    TRY(dev_alloc(&w->la.b, kp * sizeof(zc)));
+    TRY(dev_alloc(&w->la.ratio, sizeof(zc)));
+    w->la.ldp = la_ldp((int)kp);
+    TRY(dev_alloc(&w->la.part, (size_t)kLaBlocks * w->la.ldp * sizeof(zc)));
+    TRY(dalloc(&w->la.counter, 1));
+    w->la.bt = w->wd.bt;
+    w->la.u = w->wd.u;
+    w->la.vg = w->wd.vg;
+    w->la.a = w->wd.a;
+    w->la.phi64 = w->la.phi;
+    w->la.cinv = w->wd.cinv;
+    w->la.idx = w->wd.idx;
     TRY(dalloc(&w->wd.w, np * (kp + 1)));
     TRY(dalloc(&w->wd.fcol, np));
     TRY(dalloc(&w->wd.piv, np));
@@ -524,12 +430,12 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     // embedded stale rows: 2 kp slots (capped at 256, the widest matrix-core update)
     w->kp2 = std::min<int>(256, kpad(std::min<int>(2 * (int)kp, 256)));
     TRY(dalloc(&w->vh, (size_t)w->kp2 * 2 * np));
-    w->wd.ldc = (int)kp + 1;
-    // coherent: the host watches the completion tag while the kernel runs
-    if (hipHostMalloc((void **)&w->ratio_h, 3 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
+    w->wd.ldc = w->la.ldc = (int)kp + 1;
+    // coherent: the host watches the result words while the kernel runs
+    if (hipHostMalloc((void **)&w->words_h, kLaWords * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess)
         TRY(fail(DSU_ENOMEM, "hipHostMalloc failed"));
-    std::memset(w->ratio_h, 0, 3 * sizeof(double));
+    std::memset(w->words_h, 0, kLaWords * sizeof(double));
     if (hipHostMalloc((void **)&w->row_stage, 2 * np * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess)
         TRY(fail(DSU_ENOMEM, "hipHostMalloc failed"));
@@ -541,9 +447,9 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     }
     {
         void *dptr = nullptr;
-        if (hipHostGetDevicePointer(&dptr, w->ratio_h, 0) != hipSuccess)
+        if (hipHostGetDevicePointer(&dptr, w->words_h, 0) != hipSuccess)
             TRY(fail(DSU_EDEVICE, "hipHostGetDevicePointer failed"));
-        w->wd.ratio_host = static_cast<double *>(dptr);
+        w->la.words = static_cast<double *>(dptr);
     }
     if (hipMemcpy2D(w->wd.a, np * sizeof(zc), slater_host, n * sizeof(zc), n * sizeof(zc), n, hipMemcpyHostToDevice) !=
         hipSuccess)
@@ -573,32 +479,14 @@ extern "C" int dsu_zpropose_ratio(dsu_zwalker *w, int32_t electron, const double
             CHK(zwalker_flush(w));
             break;
         }
-    // every earlier copy out of the staging buffer was followed on the stream by
-    // a look-ahead kernel the host waited for, so the buffer is free
+    // every earlier look-ahead was waited for, so the staging row is free
     std::memcpy(w->row_stage, phi_host, sizeof(double) * 2 * w->n);
     std::memset(w->row_stage + 2 * w->n, 0, sizeof(double) * 2 * (w->np - w->n));
-    hipLaunchKernelGGL(k_zrow_from_host, dim3((w->np + 255) / 256), dim3(256), 0, w->stream, w->row_stage_dev, w->wd.phi,
-                       w->np);
-    HIPCHK(hipGetLastError());
-    const unsigned tag = ++w->tag;
-    hipLaunchKernelGGL(k_zpropose, dim3(2 * w->k + 1), dim3(kThreads), 0, w->stream, w->wd, w->np, w->k, electron,
-                       tag);
-    HIPCHK(hipGetLastError());
-    // the kernel writes the tag to mapped memory after the ratio; after 2 s
-    // without it the stream is synchronised instead (reports a failed kernel)
-    const volatile double *h = w->ratio_h;
-    {
-        const auto t0 = std::chrono::steady_clock::now();
-        bool seen = false;
-        for (unsigned spin = 0; !seen; ++spin) {
-            if (h[2] == (double)tag) seen = true;
-            else if ((spin & 4095u) == 4095u && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) break;
-        }
-        if (!seen) {
-            HIPCHK(hipStreamSynchronize(w->stream));
-            if (h[2] != (double)tag) return fail(DSU_EDEVICE, "look-ahead kernel did not report");
-        }
-    }
+    la_arm(w->words_h, 0, 2);
+    HIPCHK((la_propose<zc, 0>(w->la, LaSource{w->row_stage_dev, nullptr}, w->n, w->np, w->k, electron, -1, MdDev{},
+                              w->stream)));
+    CHK(la_wait(w->words_h, 0, 2, w->stream));
+    const volatile double *h = w->words_h;
     w->prop_re = h[0];
     w->prop_im = h[1];
     w->has_prop = true;
@@ -623,8 +511,7 @@ extern "C" int dsu_zaccept(dsu_zwalker *w) {
     const double mod = std::hypot(w->prop_re, w->prop_im);
     if (!(mod > RatioFloor<double>::value) || !std::isfinite(mod))
         return fail(DSU_ESINGULAR, "ratio (%g, %g) cannot be accepted", w->prop_re, w->prop_im);
-    hipLaunchKernelGGL(k_zaccept, dim3(1), dim3(kThreads), 0, w->stream, w->wd, w->np, w->k, w->prop_e);
-    HIPCHK(hipGetLastError());
+    HIPCHK((la_accept<zc>(w->la, w->n, w->np, w->k, w->prop_e, MdDev{}, w->stream)));
     w->idx[w->k] = w->prop_e;
     ++w->k;
     w->logabs += std::log(mod);

@@ -1,0 +1,58 @@
+"""Kernels at the sizes where their tilings change: edges of tiles, remainders,
+the smallest and largest of a range.  References are LAPACK and the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import require_gpu
+from paper_1708_00744_amd import dsu, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def well_conditioned(seed, n, complex_=False):
+    """2 I + (entries uniform in [-1, 1]) / (2 sqrt(n)): singular values within
+    about [1, 3], so FP64 ratios are good to ~n 2^-53 and FP32 ones to ~n 2^-24
+    of the terms' size (bounded by 4)."""
+    a = inputs.dense_matrix(seed, n) / (2.0 * np.sqrt(n))
+    if complex_:
+        a = a + 1j * inputs.dense_matrix(seed + 1, n) / (2.0 * np.sqrt(n))
+    return a + 2.0 * np.eye(n)
+
+
+# Look-ahead launches: 64 real columns a block up to 2048, more from there
+# (2049 real: 128 with a half last block; complex from 1025); 2 k + 1 rows in
+# tiles of 16 over 8 waves (k = 7, 8: one and two tiles; k = 63, 64: one and
+# two rounds of the waves); k = 65 and 130: second and third 64 entries of t.
+@pytest.mark.parametrize("n,K,moves,kind", [
+    (1, 1, 1, "fp64"), (64, 9, 10, "fp64"), (65, 66, 65, "fp64"), (200, 131, 131, "fp64"),
+    (2049, 10, 12, "fp64"), (130, 66, 70, "fp32"), (2113, 9, 12, "fp32"), (2113, 9, 12, "fp32_dev"),
+    (67, 66, 67, "complex"), (1030, 9, 12, "complex")])
+def test_lookahead_edges(n, K, moves, kind):
+    require_gpu()
+    import torch
+    cplx = kind == "complex"
+    a = well_conditioned(11 + n, n, cplx)
+    inv = np.linalg.inv(a)
+    noise = inputs.rows(5, moves, n) + (1j * inputs.rows(6, moves, n) if cplx else 0.0)
+    f32 = kind.startswith("fp32")
+    # FP32: N-term dot products of terms bounded by 4, unit roundoff 2^-24, x 4 for the pending moves' solve
+    tol = 16.0 * np.sqrt(n) * 2.0**-24 if f32 else 1e-10
+    w = dsu.ZWalker(a, K) if cplx else dsu.Walker(a, K, precision=dsu.FP32_MIXED if f32 else dsu.FP64)
+    with w:
+        for m in range(moves):
+            e = (7 * m) % n if n > moves else m
+            row = 0.9 * a[e] + 0.1 * noise[m] / np.sqrt(n)
+            if kind == "fp32_dev":
+                dev = torch.tensor(row, dtype=torch.float32, device="cuda")
+                torch.cuda.synchronize()
+                row = dev.cpu().numpy().astype(np.float64)
+                r = w.propose_dev(e, dev.data_ptr())
+            else:
+                r = w.propose(e, row)
+            exact = row @ inv[:, e]
+            assert abs(r - exact) <= tol * max(1.0, abs(exact)), (m, e, r, exact)
+            w.accept()
+            inv = inv - np.outer(inv[:, e], row @ inv - np.eye(n)[e]) / exact
+        got = w.inverse()
+    assert np.abs(got - inv).max() <= (1e-9 if not f32 else 16.0 * np.sqrt(n) * 2.0**-24)
