@@ -128,9 +128,9 @@ struct GjDesc {
     double *m;        // np x np work (in: A^T padded with identity; out: inverse scrambled)
     double *m2;       // np x np: the other buffer of the ping-pong trailing update
     double *panel;    // np x nb: the panel's columns, column-major (factored in place)
-    double *w;        // np x nb: a column group's update (E - S), column-major
+    double *w;        // 32 x 64 (of np x nb): a column group's pivot rows in the panel's other columns
     int *piv;         // n pivots
-    int *perm;        // np final column permutation
+    int *perm;        // np: map of all row interchanges so far; at the end the final column permutation
     int *rowsrc;      // np: the panel's row interchanges, composed (row i <- row rowsrc[i])
     double *logdet;   // out
     int *sign;        // out
@@ -152,7 +152,7 @@ template <> struct RatioFloor<float> { static constexpr double value = 1e-6; };
 // Blocking of the Gauss-Jordan inversion: panel width nb (16, 32, 64, or 128
 // = 64-column panels factored in pairs that share one rank-128 trailing
 // update), the single-panel update's column chunk cw (32, or 64 when np is a
-// multiple of 128) and the panel columns one apply workgroup takes, cpb (1 or 4).
+// multiple of 128); cpb (1 or 4) is kept for the callers, without effect.
 struct GjTiles {
     int nb = 64, cw = 32, cpb = 1;
 };

@@ -281,34 +281,40 @@ __global__ __launch_bounds__(kThreads) void k_gj_panel(const GjDesc *__restrict_
     }
 }
 
+// The row whose old contents end up at row x after the interchanges k0 + q <->
+// piv[q], q = 0 .. w - 1, in that order.
+__device__ __forceinline__ int gj_trace(int x, const int *piv, int k0, int w) {
+    for (int q = w - 1; q >= 0; --q) x = x == k0 + q ? piv[q] : (x == piv[q] ? k0 + q : x);
+    return x;
+}
+
+// Compose the interchanges `piv` (of rows k0 .. k0 + w - 1, in LDS) into the
+// running map of all interchanges so far: perm[r] = the row of the first matrix
+// whose contents row r holds now.  src = gj_trace of row r, thread tid < 2 w.
+__device__ __forceinline__ void gj_total_map(int *perm, int r, int src, bool on) {
+    const int from = on ? perm[src] : 0;
+    __syncthreads();  // every source read before any row changes
+    if (on) perm[r] = from;  // rows named twice get the same value
+}
+
 // The panel's row interchanges, composed: rowsrc[i] = the row of M whose
 // contents row i holds after the swaps k <-> piv[k], k = k0 .. k1-1, in order
-// (one workgroup per determinant; rows outside the panel's reach stay i).
-// The map is built in LDS (np ints, dynamic shared memory) when it fits,
-// else in place in global memory.
-__global__ __launch_bounds__(kThreads) void k_gj_rowsrc(const GjDesc *__restrict__ descs, int np, int k0, int k1,
-                                                        int in_lds) {
-    extern __shared__ int s_rs[];
+// (one workgroup per determinant).  At most 2 (k1 - k0) rows move, each traced
+// by its own thread; the rest stay i.
+__global__ __launch_bounds__(kThreads) void k_gj_rowsrc(const GjDesc *__restrict__ descs, int np, int k0, int k1) {
     __shared__ int s_piv[64];
     const GjDesc g = descs[blockIdx.x];
-    const int w = k1 - k0;
-    int *rs = in_lds ? s_rs : g.rowsrc;
-    if (threadIdx.x < w) s_piv[threadIdx.x] = g.piv[k0 + threadIdx.x];
-    for (int i = threadIdx.x; i < np; i += kThreads) rs[i] = i;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int kk = 0; kk < w; ++kk) {
-            const int k = k0 + kk, p = s_piv[kk];
-            if (p != k) {
-                const int t = rs[k];
-                rs[k] = rs[p];
-                rs[p] = t;
-            }
-        }
+    const int w = k1 - k0, tid = threadIdx.x;
+    if (tid < w) s_piv[tid] = g.piv[k0 + tid];
+    for (int i = tid; i < np; i += kThreads) {
+        g.rowsrc[i] = i;
+        if (k0 == 0) g.perm[i] = i;
     }
     __syncthreads();
-    if (in_lds)
-        for (int i = threadIdx.x; i < np; i += kThreads) g.rowsrc[i] = s_rs[i];
+    const bool on = tid < 2 * w;
+    const int r = on ? (tid < w ? k0 + tid : s_piv[tid - w]) : 0, x = on ? gj_trace(r, s_piv, k0, w) : 0;
+    if (on) g.rowsrc[r] = x;
+    gj_total_map(g.perm, r, x, on);
 }
 
 // Trailing update with the row interchanges folded in, into the other buffer:
@@ -488,363 +494,339 @@ __global__ __launch_bounds__(kThreads, 2) void k_gj_update(const GjDesc *__restr
 }
 
 // ---------------------------------------------------------------------------
-// Two-level panel factorisation (same algebra one level down).  One panel
-// pass of the single-workgroup step above moves the whole N x nb panel for
-// every column; here the panel's columns are factored WS at a time inside LDS
-// by one workgroup per determinant (k_gj_sub), and each group's row swaps and
-// rank-WS update  P_c <- P_c - (E - S) P_c[pivot rows]  reach the panel's
-// other columns through k_gj_sub_apply, spread over many workgroups.
+// Two-level panel factorisation (same algebra one level down): the panel's
+// columns are factored WS at a time by one workgroup per determinant
+// (k_gj_group), and each group's rank-WS update reaches the panel's other
+// columns through k_gj_apply, spread over many workgroups.
 // ---------------------------------------------------------------------------
-constexpr int kGjThreads = 1024;
 
-// P[j][i] = M[i][k0 + j] for the panel's w columns (64-row tiles through LDS).
+// P[j][i] = M[i][k0 + j] for the panel's w columns (64-row tiles through LDS,
+// every load of a thread in flight at once).
 __global__ __launch_bounds__(kThreads) void k_gj_gather(const GjDesc *__restrict__ descs, int np, int k0, int w) {
     __shared__ double t[64][65];
     const GjDesc g = descs[blockIdx.y];
-    const int r0 = blockIdx.x * 64, tid = threadIdx.x;
-    for (int v = tid; v < 64 * w; v += kThreads) {
-        const int i = v / w, j = v % w;
-        t[i][j] = g.m[(size_t)(r0 + i) * np + k0 + j];
-    }
+    const int r0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    DSU_GLOBAL const double *m = gmem<const double>(g.m) + (size_t)r0 * np + k0 + lane;
+    DSU_GLOBAL double *P = gmem(g.panel) + r0 + lane;
+    double v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = lane < w ? m[(size_t)(wave + 4 * q) * np] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) t[wave + 4 * q][lane] = v[q];
     __syncthreads();
-    for (int v = tid; v < 64 * w; v += kThreads) {
-        const int j = v / 64, i = v % 64;
-        g.panel[(size_t)j * np + r0 + i] = t[i][j];
-    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        if (wave + 4 * q < w) P[(size_t)(wave + 4 * q) * np] = t[lane][wave + 4 * q];
 }
 
-template <int WS, int NPMAX>
-__global__ __launch_bounds__(kGjThreads) void k_gj_sub(const GjDesc *__restrict__ descs, int n, int np, int k0, int j0,
-                                                       int ws) {
-    __shared__ double S[WS * NPMAX];  // the group's columns, S[j * np + i]
-    __shared__ double s_v[kGjThreads / 64];
-    __shared__ int s_i[kGjThreads / 64];
-    const GjDesc g = descs[blockIdx.x];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double *P = g.panel + (size_t)j0 * np;
-    for (int v = tid; v < ws * np; v += kGjThreads) S[v] = P[v];
-    // running log|det|, sign and status: thread 0's registers for the whole
-    // group, read once and written once; the largest pivot so far (the
-    // singularity threshold): every thread's register
-    double logdet = 0.0, pmax = 0.0;
-    int sign = 1, status = 0;
-    if (!(k0 == 0 && j0 == 0)) {
-        pmax = *g.pmax;
-        if (tid == 0) {
-            logdet = *g.logdet;
-            sign = *g.sign;
-            status = *g.status;
-        }
+// Lane exchanges of a double within the vector unit (DPP).  dpp_f64: every
+// lane of the pattern has a source; dpp_old_f64: lanes outside the rows in
+// ROWS keep their own value.
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_old_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// Lane L of each row of 16 lanes to the whole row.
+template <int L> __device__ __forceinline__ double row_bcast_f64(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + L, 0xf, 0xf, true);
+}
+// Maximum over groups of 4 or 8 lanes (every lane gets it).
+template <int N> __device__ __forceinline__ double group_max(double v) {
+    v = fmax(v, dpp_f64<0xB1>(v));                           // lane ^ 1
+    v = fmax(v, dpp_f64<0x4E>(v));                           // lane ^ 2
+    if constexpr (N == 8) v = fmax(v, dpp_f64<0x141>(v));    // mirrored in eight lanes
+    return v;
+}
+// Maximum over the wave, the same for every lane.
+__device__ __forceinline__ double wave_max(double v) {
+    v = group_max<8>(v);
+    v = fmax(v, dpp_f64<0x140>(v));           // mirrored in sixteen lanes
+    v = fmax(v, dpp_old_f64<0x142, 0xa>(v));  // lane 15 of a row of 16 to the next row
+    v = fmax(v, dpp_old_f64<0x143, 0xc>(v));  // lane 31 to lanes 32 .. 63
+    return lane_f64(v, 63);
+}
+// Of the lanes in `mask` (not empty) the one that holds the smallest idx.
+__device__ __forceinline__ int lowest_lane(unsigned long long mask, int idx) {
+    int l = __builtin_ctzll(mask);
+    for (unsigned long long m = mask & (mask - 1); m; m &= m - 1) {  // (ties only)
+        const int o = __builtin_ctzll(m);
+        if (__builtin_amdgcn_readlane(idx, o) < __builtin_amdgcn_readlane(idx, l)) l = o;
     }
-    __syncthreads();
-    for (int kk = 0; kk < ws; ++kk) {
-        const int k = k0 + j0 + kk;
-        const double *sc = S + kk * np;
-        double best = -1.0;
-        int bi = n;
-        for (int i = k + tid; i < n; i += kGjThreads) argmax_combine(best, bi, fabs(sc[i]), i);
-        for (int o = 32; o > 0; o >>= 1) {
-            const double v2 = __shfl_xor(best, o, 64);
-            const int i2 = __shfl_xor(bi, o, 64);
-            argmax_combine(best, bi, v2, i2);
-        }
-        if (lane == 0) { s_v[wave] = best; s_i[wave] = bi; }
-        __syncthreads();
-        // every thread combines the waves' candidates (same order, same result)
-        double bv = s_v[0];
-        int p = s_i[0];
-#pragma unroll
-        for (int q = 1; q < kGjThreads / 64; ++q) argmax_combine(bv, p, s_v[q], s_i[q]);
-        pmax = fmax(pmax, bv);
-        // singular when the best pivot is at rounding level of the largest one:
-        // flagged, and no interchange
-        if (!(bv > (double)n * 2.220446049250313e-16 * pmax)) {
-            status = -3;
-            p = k;
-        }
-        // the pivot row (old row p) in registers before anything is written
-        const double d = S[kk * np + p];
-        const double dinv = d != 0.0 ? 1.0 / d : 0.0;
-        double rp[WS];
-#pragma unroll
-        for (int j = 0; j < WS; ++j) rp[j] = j < ws ? (j == kk ? dinv : S[j * np + p] * dinv) : 0.0;
-        if (tid == 0) {
-            g.piv[k] = p;
-            if (d != 0.0) logdet += log(fabs(d));
-            if (p != k) sign = -sign;
-            if (d < 0.0) sign = -sign;
-        }
-        __syncthreads();
-        // rows after the interchange: row k = the scaled pivot row, row p =
-        // old row k eliminated, every other row eliminated in place; the owner
-        // of row k writes rows k and p
-        for (int i = tid; i < np; i += kGjThreads) {
-            if (i == p && p != k) continue;
-            if (i == k) {
-                const double f = S[kk * np + k];
-#pragma unroll
-                for (int j = 0; j < WS; ++j) {
-                    if (j >= ws) continue;
-                    const double ok = S[j * np + k];
-                    S[j * np + k] = rp[j];
-                    if (p != k) S[j * np + p] = j == kk ? -f * dinv : ok - f * rp[j];
-                }
-                continue;
-            }
-            const double f = S[kk * np + i];
-#pragma unroll
-            for (int j = 0; j < WS; ++j) {
-                if (j >= ws) continue;
-                S[j * np + i] = j == kk ? -f * dinv : S[j * np + i] - f * rp[j];
-            }
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        *g.logdet = logdet;
-        *g.pmax = pmax;
-        *g.sign = sign;
-        *g.status = status;
-    }
-    // the factored columns, and the group's update (E - S) column-major in w
-    for (int v = tid; v < ws * np; v += kGjThreads) {
-        const int j = v / np, i = v % np;
-        P[v] = S[v];
-        g.w[v] = (i == k0 + j0 + j ? 1.0 : 0.0) - S[v];
-    }
+    return l;
 }
 
-// Register-resident form of the group step above: thread t owns rows
-// t + 1024 r (r < RPT) of the group's WS columns in registers, so a group can
-// be WS = 32 / RPT columns wide where the LDS form holds 4 (np = 4096).  Per
-// column two barriers: one for the waves' pivot candidates, one for the
-// pivot row and the old row k, which their owners publish in LDS.  Every
-// element gets the same operations as in k_gj_sub.
-template <int WS, int RPT>
-__global__ __launch_bounds__(kGjThreads) void k_gj_subr(const GjDesc *__restrict__ descs, int n, int np, int k0,
-                                                        int j0, int ws) {
-    __shared__ double s_v[kGjThreads / 64];
-    __shared__ int s_i[kGjThreads / 64];
-    __shared__ double s_prow[WS], s_krow[WS];
+// One group of WS panel columns, factored in registers: thread t owns rows
+// t + NT r (r < RPT).  What bounds it: the pivots are a serial chain on one
+// compute unit, N x WS multiply-adds each.  So:
+//  * WS RPT = 64 values a thread on as few waves as hold the rows (NT = 256
+//    or 512): barriers span 4 or 8 waves, and what a wave does once a pivot
+//    serves RPT rows of each lane;
+//  * rows are interchanged in name only: a thread keeps its rows and the
+//    position each one has, which the interchanges and the ties of the pivot
+//    search go by; the positions are used when the columns are stored.  Only
+//    the pivot row's owner does anything of its own in a step (it scales its
+//    row in place);
+//  * the scaled pivot row sits one column a lane (one LDS read and one
+//    multiply) and enters the multiply-adds from scalar registers (readlane);
+//    every wave reading it from LDS as broadcasts cost 16 reads of 16 bytes a
+//    wave and bound the step;
+//  * four pivots per loop body, then the columns rotate by four through the
+//    registers: every register index is fixed, and the body of a few KB stays
+//    in the instruction cache (a step unrolled per column fetches each line
+//    once, from memory);
+//  * logarithms of the pivots after the loop, one per lane.
+// Every element gets the operations of one plain elimination step in the same
+// order, whatever NT and RPT.  Per launch (N = 1024, 32 columns, 64
+// determinants): 152 -> 61 us; N = 2048, 16 columns: 81 -> 36; N = 4096, 8
+// columns: 48 -> 30 us (32 determinants); N = 512: 267 -> 79 us (512).
+// Afterwards the workgroup moves the group's row interchanges through the
+// panel's other columns (a permutation of at most 2 ws rows, one round of
+// loads and stores) and leaves the pivot rows of those columns in g.w for
+// k_gj_apply: Q[j][c] at w[64 j + c].
+template <int NT, int WS, int RPT>
+__global__ __launch_bounds__(NT) void k_gj_group(const GjDesc *__restrict__ descs, int n, int np, int k0, int j0,
+                                                 int ws, int w) {
+    constexpr int NW = NT / 64;
+    __shared__ double s_prow[WS + 1];
+    __shared__ double s_cv[NW], s_d[WS];
+    __shared__ int s_ci[NW], s_p[WS], s_src[2 * WS];
     const GjDesc g = descs[blockIdx.x];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kb = k0 + j0;
     DSU_GLOBAL double *P = gmem(g.panel) + (size_t)j0 * np;
-    DSU_GLOBAL double *Wg = gmem(g.w);
     double sv[RPT][WS];
+    int pos[RPT];  // the position of each row after the interchanges so far
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        const int i = tid + kGjThreads * r;
+        const int i = tid + NT * r;
+        pos[r] = i;
+        DSU_GLOBAL const double *pi = P + (i < np ? i : 0);
+        if (ws == WS) {
 #pragma unroll
-        for (int j = 0; j < WS; ++j) sv[r][j] = 0.0;
-        if (i < np) {
-            if (ws == WS) {
+            for (int j = 0; j < WS; ++j) sv[r][j] = pi[(size_t)j * np];
+        } else {
 #pragma unroll
-                for (int j = 0; j < WS; ++j) sv[r][j] = P[(size_t)j * np + i];
-            } else {
-#pragma unroll
-                for (int j = 0; j < WS; ++j)
-                    if (j < ws) sv[r][j] = P[(size_t)j * np + i];
-            }
+            for (int j = 0; j < WS; ++j) sv[r][j] = j < ws ? pi[(size_t)j * np] : 0.0;
         }
     }
-    double logdet = 0.0, pmax = 0.0;
-    int sign = 1, status = 0;
-    if (!(k0 == 0 && j0 == 0)) {
+    double pmax = 0.0;
+    int status = 0;
+    if (kb != 0) {
         pmax = *g.pmax;
-        if (tid == 0) {
-            logdet = *g.logdet;
-            sign = *g.sign;
-            status = *g.status;
-        }
+        status = *g.status;
     }
-    // fully unrolled (every register index fixed); columns past ws skipped
-    auto step = [&](auto kk_c) __attribute__((always_inline)) {
-        constexpr int kk = decltype(kk_c)::value;
+    const double tiny = (double)n * 2.220446049250313e-16;
+    auto step = [&](auto q_c, int kk) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_c)::value;
         if (kk >= ws) return;  // uniform
-        const int k = k0 + j0 + kk;
+        const int k = kb + kk;
+        // the wave's candidate: largest |entry| of column kk at positions k .. n - 1, lowest position on ties
         double best = -1.0;
-        int bi = n;
+        int bp = n;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
-            const int i = tid + kGjThreads * r;
-            if (i >= k && i < n) argmax_combine(best, bi, fabs(sv[r][kk]), i);
+            const double a = fabs(sv[r][q]);
+            if (pos[r] >= k && pos[r] < n && (a > best || (a == best && pos[r] < bp))) {
+                best = a;
+                bp = pos[r];
+            }
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double v2 = __shfl_xor(best, o, 64);
-            const int i2 = __shfl_xor(bi, o, 64);
-            argmax_combine(best, bi, v2, i2);
+        const double wm = wave_max(best);
+        // (a wave without a candidate: any lane, position n)
+        const int wl = wm >= 0.0 ? lowest_lane(__ballot(best == wm), bp) : 0;
+        if (lane == wl) {
+            s_cv[wave] = wm;
+            s_ci[wave] = bp;
         }
-        if (lane == 0) { s_v[wave] = best; s_i[wave] = bi; }
         __syncthreads();
-        double bv = s_v[0];
-        int p = s_i[0];
-#pragma unroll
-        for (int q = 1; q < kGjThreads / 64; ++q) argmax_combine(bv, p, s_v[q], s_i[q]);
+        // every wave combines the candidates (same values, same result)
+        const double cv = s_cv[lane & (NW - 1)];
+        const int ci = s_ci[lane & (NW - 1)];
+        const double bv = lane_f64(group_max<NW>(cv), 0);
+        int p = __builtin_amdgcn_readlane(ci, lowest_lane(__ballot(cv == bv) & ((1ull << NW) - 1), ci));
         pmax = fmax(pmax, bv);
-        if (!(bv > (double)n * 2.220446049250313e-16 * pmax)) {
+        // singular when the best pivot is at rounding level of the largest
+        // one: flagged, and no interchange
+        if (!(bv > tiny * pmax)) {
             status = -3;
             p = k;
         }
-        // the owners publish the pivot row (old row p) and the old row k
-        // (rows p and k have one owner each: rare, divergent branches)
+        // the owner publishes the pivot row
+        bool own[RPT];
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
-            const int i = tid + kGjThreads * r;
-            if (i == p)
+            own[r] = pos[r] == p;
+            if (own[r])
 #pragma unroll
                 for (int j = 0; j < WS; ++j) s_prow[j] = sv[r][j];
-            if (i == k)
-#pragma unroll
-                for (int j = 0; j < WS; ++j) s_krow[j] = sv[r][j];
+            pos[r] = pos[r] == p ? k : (pos[r] == k ? p : pos[r]);
         }
         __syncthreads();
-        const double d = s_prow[kk];
+        // column j of the row in lane j of each row of 16 lanes
+        constexpr int NR = (WS + 15) / 16;
+        double rp[NR];
+#pragma unroll
+        for (int h = 0; h < NR; ++h) rp[h] = s_prow[(16 * h + (lane & 15)) & (WS - 1)];
+        const double d = row_bcast_f64<q>(rp[0]);
         const double dinv = d != 0.0 ? 1.0 / d : 0.0;
+#pragma unroll
+        for (int h = 0; h < NR; ++h) rp[h] *= dinv;
         if (tid == 0) {
-            g.piv[k] = p;
-            if (d != 0.0) logdet += log(fabs(d));
-            if (p != k) sign = -sign;
-            if (d < 0.0) sign = -sign;
+            s_p[kk] = p;
+            s_d[kk] = d;
         }
-        if constexpr (RPT >= 4) {
-            // narrow groups: the scaled pivot row (its own column becomes 1/d)
-            // in registers; every row eliminated in place, then the owners of
-            // rows k and p overwrite theirs: row k = the scaled pivot row, row
-            // p = old row k eliminated
-            double rp[WS];
+        double f[RPT];
 #pragma unroll
-            for (int j = 0; j < WS; ++j) rp[j] = j == kk ? dinv : s_prow[j] * dinv;
+        for (int r = 0; r < RPT; ++r) {
+            f[r] = own[r] ? 0.0 : -sv[r][q];
+            if (own[r])
 #pragma unroll
-            for (int r = 0; r < RPT; ++r) {
-                const int i = tid + kGjThreads * r;
-                const double f = sv[r][kk];
-#pragma unroll
-                for (int j = 0; j < WS; ++j) sv[r][j] = j == kk ? -f * dinv : sv[r][j] - f * rp[j];
-                if (i == k) {
-#pragma unroll
-                    for (int j = 0; j < WS; ++j) sv[r][j] = rp[j];
-                } else if (i == p) {
-                    const double fk = s_krow[kk];
-#pragma unroll
-                    for (int j = 0; j < WS; ++j) sv[r][j] = j == kk ? -fk * dinv : s_krow[j] - fk * rp[j];
-                }
-            }
-        } else {
-            // wide groups (registers are short): the same values by selects,
-            // the pivot row read from LDS where it is used
-#pragma unroll
-            for (int r = 0; r < RPT; ++r) {
-                const int i = tid + kGjThreads * r;
-                if (i >= np) continue;
-                const bool is_k = i == k, is_p = i == p && p != k;
-                const double f = is_p ? s_krow[kk] : sv[r][kk];
-#pragma unroll
-                for (int j = 0; j < WS; ++j) {
-                    const double rpj = j == kk ? dinv : s_prow[j] * dinv;
-                    const double cur = is_p ? s_krow[j] : sv[r][j];
-                    sv[r][j] = is_k ? rpj : (j == kk ? -f * dinv : cur - f * rpj);
-                }
-            }
+                for (int j = 0; j < WS; ++j) sv[r][j] *= dinv;
         }
+        static_for(std::make_integer_sequence<int, WS>{}, [&](auto j_c) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_c)::value;
+            if constexpr (j != q) {
+                const double pj = row_bcast_f64<j % 16>(rp[j / 16]);
+#pragma unroll
+                for (int r = 0; r < RPT; ++r) sv[r][j] = __builtin_fma(f[r], pj, sv[r][j]);
+            }
+        });
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) sv[r][q] = own[r] ? dinv : f[r] * dinv;
     };
-    static_for(std::make_integer_sequence<int, WS>{}, step);
-    if (tid == 0) {
-        *g.logdet = logdet;
-        *g.pmax = pmax;
-        *g.sign = sign;
-        *g.status = status;
+    int turned = 0;  // columns rotated so far
+#pragma unroll 1
+    for (; turned < ws; turned += 4) {
+        step(std::integral_constant<int, 0>{}, turned);
+        step(std::integral_constant<int, 1>{}, turned + 1);
+        step(std::integral_constant<int, 2>{}, turned + 2);
+        step(std::integral_constant<int, 3>{}, turned + 3);
+        if constexpr (WS > 4)
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                const double t0 = sv[r][0], t1 = sv[r][1], t2 = sv[r][2], t3 = sv[r][3];
+#pragma unroll
+                for (int j = 0; j < WS - 4; ++j) sv[r][j] = sv[r][j + 4];
+                sv[r][WS - 4] = t0;
+                sv[r][WS - 3] = t1;
+                sv[r][WS - 2] = t2;
+                sv[r][WS - 1] = t3;
+            }
     }
-    // the factored columns, and the group's update (E - S) column-major in w
+    // column j now sits at place j + WS - turned; rows go to their positions
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        const int i = tid + kGjThreads * r;
-        if (i >= np) continue;
+        if (tid + NT * r >= np) continue;
+        DSU_GLOBAL double *po = P + pos[r];
+        if (ws == WS) {
 #pragma unroll
-        for (int j = 0; j < WS; ++j) {
-            if (j >= ws) continue;
-            P[(size_t)j * np + i] = sv[r][j];
-            Wg[(size_t)j * np + i] = (i == k0 + j0 + j ? 1.0 : 0.0) - sv[r][j];
+            for (int j = 0; j < WS; ++j) po[(size_t)j * np] = sv[r][j];
+        } else {
+#pragma unroll
+            for (int q = 0; q < WS; ++q) {
+                const int j = q - (WS - turned);
+                if (j >= 0 && j < ws) po[(size_t)j * np] = sv[r][q];
+            }
         }
     }
-}
-
-// The group's swaps, then P_c -= (E - S) Q_c, for every other panel column c.
-// The swaps k <-> piv[k] (k = k0 + j0 .. + ws - 1, in order) compose into a
-// permutation of at most 2 ws rows: row r ends up holding the old row
-// s_0(s_1(...s_{ws-1}(r))), traced by one thread per involved row, so the
-// values move in one parallel round of loads and stores.  A workgroup takes
-// CPB columns, so each element of (E - S) it reads serves CPB of them.
-template <int CPB, int RB>
-__global__ __launch_bounds__(kThreads) void k_gj_sub_apply(const GjDesc *__restrict__ descs, int np, int k0, int j0,
-                                                           int ws, int w) {
-    __shared__ int s_k[64], s_p[64], s_src[128];
-    __shared__ double s_val[CPB][128];
-    const int c0 = blockIdx.x * CPB, tid = threadIdx.x;
-    bool on[CPB], any = false;  // columns of this block that take the update: in the panel, outside the group
-#pragma unroll
-    for (int q = 0; q < CPB; ++q) {
-        on[q] = c0 + q < w && !(c0 + q >= j0 && c0 + q < j0 + ws);
-        any = any || on[q];
-    }
-    if (!any) return;  // uniform
-    const GjDesc g = descs[blockIdx.y];
-    DSU_GLOBAL double *P = gmem(g.panel);
-    DSU_GLOBAL const double *Wg = gmem(g.w);
+    __syncthreads();  // s_p, s_d
     if (tid < ws) {
-        s_k[tid] = k0 + j0 + tid;
-        s_p[tid] = g.piv[k0 + j0 + tid];
+        const double d = s_d[tid];
+        s_d[tid] = d != 0.0 ? log(fabs(d)) : 0.0;
+        int flips = (s_p[tid] != kb + tid ? 1 : 0) ^ (d < 0.0 ? 1 : 0);
+        const int odd = __popcll(__ballot(flips != 0)) & 1;
+        g.piv[kb + tid] = s_p[tid];
+        if (tid == 0) {
+            double ld = kb != 0 ? *g.logdet : 0.0;
+            for (int q = 0; q < ws; ++q) ld += s_d[q];
+            const int sign = kb != 0 ? *g.sign : 1;
+            *g.logdet = ld;
+            *g.sign = odd ? -sign : sign;
+            *g.status = status;
+            *g.pmax = pmax;
+        }
     }
-    __syncthreads();
+    if (w <= ws) return;
+    // the interchanges k <-> p, in order, put old row s_0(s_1(...(r))) at row r
     if (tid < 2 * ws) {
-        int x = tid < ws ? s_k[tid] : s_p[tid - ws];
-        for (int kk = ws - 1; kk >= 0; --kk) x = x == s_k[kk] ? s_p[kk] : (x == s_p[kk] ? s_k[kk] : x);
+        int x = tid < ws ? kb + tid : s_p[tid - ws];
+        for (int q = ws - 1; q >= 0; --q) x = x == kb + q ? s_p[q] : (x == s_p[q] ? kb + q : x);
         s_src[tid] = x;
     }
     __syncthreads();
-    for (int v = tid; v < CPB * 2 * ws; v += kThreads) {
-        const int q = v / (2 * ws), t = v % (2 * ws);
-        if (on[q]) s_val[q][t] = P[(size_t)(c0 + q) * np + s_src[t]];
+    constexpr int NM = (2 * WS * (64 - WS) + NT - 1) / NT;  // moved values a thread, at most
+    const int oc = w - ws, cnt = 2 * ws * oc;
+    DSU_GLOBAL double *A = gmem(g.panel), *Q = gmem(g.w);
+    double mv[NM];
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+        const int v = tid + NT * q, c = v / (2 * ws), t = v % (2 * ws);
+        if (v < cnt) mv[q] = A[(size_t)(c < j0 ? c : c + ws) * np + s_src[t]];
     }
-    __syncthreads();
-    for (int v = tid; v < CPB * 2 * ws; v += kThreads) {
-        const int q = v / (2 * ws), t = v % (2 * ws);
-        const int r = t < ws ? s_k[t] : s_p[t - ws];
-        if (on[q]) P[(size_t)(c0 + q) * np + r] = s_val[q][t];  // rows named twice receive the same value
+    __syncthreads();  // every value read before any row changes
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+        const int v = tid + NT * q, c = v / (2 * ws), t = v % (2 * ws);
+        if (v < cnt) {
+            const int cc = c < j0 ? c : c + ws;
+            A[(size_t)cc * np + (t < ws ? kb + t : s_p[t - ws])] = mv[q];  // rows named twice receive the same value
+            if (t < ws) Q[64 * t + cc] = mv[q];
+        }
     }
-    __syncthreads();
-    // q[kk] = the value at row k0 + j0 + kk after the swaps = s_val[.][kk].
-    // RB rows a thread per pass, their loads all issued before the pass's
-    // stores (which may alias them for all the compiler knows): one memory
-    // latency per RB rows.  RB = 4 where the blocks are few (np >= 2048: 2 ms
-    // less per recompute of 32 x 4096); where they are many, the registers it
-    // takes cost more occupancy than it saves (RB = 1).
-    for (int i0 = tid; i0 < np; i0 += RB * kThreads) {
-        double a[RB][CPB];
+}
+
+// The group's update of the panel's other columns, P_c += (S - E) Q_c, as
+// matrix-core tiles: a wave takes 16 rows and, transposed (D' = Q^T (S - E)^T,
+// so that a lane's result lies along the column-major panel), the columns in
+// tiles of 16.  One workgroup per 64 rows: the few MB it moves and 2 N ws w
+// flops are a few microseconds on any number of determinants, so it is bound by
+// its launch or by the panel's bytes (N = 1024, 32 columns, 64 determinants: 44
+// -> 13 us; N = 512, 512 determinants: 143 -> 39; N = 4096, 8 columns, 32: 37
+// -> 22; one determinant of N = 1024: 9 -> 6; the first figures with one or four
+// columns per workgroup on the vector units).  A matrix-core step adds its four
+// products in ascending order, so each element gets the chain of multiply-adds
+// of the vector form.
+__global__ __launch_bounds__(kThreads) void k_gj_apply(const GjDesc *__restrict__ descs, int np, int k0, int j0, int ws,
+                                                       int w) {
+    const GjDesc g = descs[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
+    const int row = blockIdx.x * 64 + 16 * wave + lr;
+    DSU_GLOBAL double *P = gmem(g.panel);
+    DSU_GLOBAL const double *S = P + (size_t)j0 * np, *Q = gmem<const double>(g.w);
+    double b[8];  // (S - E)[row][lk + 4 s]
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int i = i0 + r * kThreads;
+    for (int s = 0; s < 8; ++s) {
+        const int j = lk + 4 * s;
+        b[s] = j < ws ? S[(size_t)j * np + row] - (row == k0 + j0 + j ? 1.0 : 0.0) : 0.0;
+    }
+    for (int c0 = 0; c0 < w; c0 += 16) {
+        if (c0 >= j0 && c0 + 16 <= j0 + ws) continue;
+        f64x4 acc;
+        double a[8];
 #pragma unroll
-            for (int q = 0; q < CPB; ++q) a[r][q] = on[q] && i < np ? P[(size_t)(c0 + q) * np + i] : 0.0;
+        for (int i = 0; i < 4; ++i) {
+            const int c = c0 + lk + 4 * i;
+            acc[i] = c < w ? P[(size_t)c * np + row] : 0.0;
         }
-#pragma unroll 8
-        for (int kk = 0; kk < ws; ++kk) {
-            double e[RB];
 #pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const int i = i0 + r * kThreads;
-                e[r] = i < np ? Wg[(size_t)kk * np + i] : 0.0;
-            }
+        for (int s = 0; s < 8; ++s) a[s] = lk + 4 * s < ws && c0 + lr < w ? Q[64 * (lk + 4 * s) + c0 + lr] : 0.0;
 #pragma unroll
-            for (int r = 0; r < RB; ++r)
+        for (int s = 0; s < 8; ++s)
+            if (4 * s < ws) acc = Mma<double>::mma(a[s], b[s], acc);
 #pragma unroll
-                for (int q = 0; q < CPB; ++q) a[r][q] -= e[r] * s_val[q][kk];
-        }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int i = i0 + r * kThreads;
-#pragma unroll
-            for (int q = 0; q < CPB; ++q)
-                if (on[q] && i < np) P[(size_t)(c0 + q) * np + i] = a[r][q];
+        for (int i = 0; i < 4; ++i) {
+            const int c = c0 + lk + 4 * i;
+            if (c < w && !(c >= j0 && c < j0 + ws)) P[(size_t)c * np + row] = acc[i];
         }
     }
 }
@@ -910,33 +892,27 @@ __global__ __launch_bounds__(kThreads) void k_gj_pair_slab(const GjDesc *__restr
 
 // After the second panel: rowsrc_b = P2 (its own swaps), rowsrc = P2 P1 (row
 // i of the result <- row rowsrc[i] of M), qrow[l] = P1's source of row k0 + l.
-// One workgroup per determinant; both maps in dynamic LDS (8 np bytes).
+// One workgroup per determinant; P1's map in dynamic LDS (4 np bytes) while
+// rowsrc is overwritten.
 __global__ __launch_bounds__(kThreads) void k_gj_pair_rowsrc(const GjDesc *__restrict__ descs, int np, int k0) {
-    extern __shared__ int s_rr[];
+    extern __shared__ int s_r1[];
     __shared__ int s_piv[64];
     const GjDesc g = descs[blockIdx.x];
-    int *r1 = s_rr, *r2 = s_rr + np;
-    if (threadIdx.x < 64) s_piv[threadIdx.x] = g.piv[k0 + 64 + threadIdx.x];
-    for (int i = threadIdx.x; i < np; i += kThreads) {
-        r1[i] = g.rowsrc[i];
-        r2[i] = i;
+    const int tid = threadIdx.x, kb = k0 + 64;
+    if (tid < 64) s_piv[tid] = g.piv[kb + tid];
+    for (int i = tid; i < np; i += kThreads) {
+        s_r1[i] = g.rowsrc[i];
+        g.rowsrc_b[i] = i;
     }
     __syncthreads();
-    if (threadIdx.x == 0)
-        for (int kk = 0; kk < 64; ++kk) {
-            const int k = k0 + 64 + kk, p = s_piv[kk];
-            if (p != k) {
-                const int t = r2[k];
-                r2[k] = r2[p];
-                r2[p] = t;
-            }
-        }
-    __syncthreads();
-    for (int i = threadIdx.x; i < np; i += kThreads) {
-        g.rowsrc_b[i] = r2[i];
-        g.rowsrc[i] = r1[r2[i]];
+    const bool on = tid < 128;
+    const int r = on ? (tid < 64 ? kb + tid : s_piv[tid - 64]) : 0, x = on ? gj_trace(r, s_piv, kb, 64) : 0;
+    if (on) {
+        g.rowsrc_b[r] = x;
+        g.rowsrc[r] = s_r1[x];
     }
-    if (threadIdx.x < 64) g.qrow[threadIdx.x] = r1[k0 + threadIdx.x];
+    if (tid < 64) g.qrow[tid] = s_r1[k0 + tid];
+    gj_total_map(g.perm, r, x, on);
 }
 
 // Q2[j] = M1[P2 row k0 + 64 + j] = M[rowsrc[k0 + 64 + j]] + (T1 - E1)[r_j] Q1,
@@ -1059,64 +1035,38 @@ static void launch_gj_update(const GjDesc *descs_dev, int ndesc, int np, int nb,
     else hipLaunchKernelGGL((k_gj_update<64, RT, CW>), grid, dim3(kThreads), 0, s, descs_dev, np, nblk, k0, w);
 }
 
-// gather = 0: the panel buffer already holds the panel's columns (a pair's second panel)
-template <int WS, int NPMAX, bool REG = false>
-static void launch_gj_panel2(const GjDesc *descs_dev, int ndesc, int n, int np, int nb, int k0, int w, int cpb,
-                             hipStream_t s, bool gather = true) {
+// Factor the panel [k0, k0 + w); gather = false: the panel buffer already
+// holds the panel's columns (a pair's second panel).
+template <int NT, int WS, int RPT>
+static void launch_gj_panel(const GjDesc *descs_dev, int ndesc, int n, int np, int k0, int w, hipStream_t s,
+                            bool gather) {
     if (gather) hipLaunchKernelGGL(k_gj_gather, dim3(np / 64, ndesc), dim3(kThreads), 0, s, descs_dev, np, k0, w);
     for (int j0 = 0; j0 < w; j0 += WS) {
         const int ws = j0 + WS <= w ? WS : w - j0;
-        if constexpr (REG)
-            hipLaunchKernelGGL((k_gj_subr<WS, NPMAX / kGjThreads>), dim3(ndesc), dim3(kGjThreads), 0, s, descs_dev, n,
-                               np, k0, j0, ws);
-        else
-            hipLaunchKernelGGL((k_gj_sub<WS, NPMAX>), dim3(ndesc), dim3(kGjThreads), 0, s, descs_dev, n, np, k0, j0,
-                               ws);
-        if (w > ws && cpb == 4 && np >= 2048)
-            hipLaunchKernelGGL((k_gj_sub_apply<4, 4>), dim3((w + 3) / 4, ndesc), dim3(kThreads), 0, s, descs_dev, np,
-                               k0, j0, ws, w);
-        else if (w > ws && cpb == 4)
-            hipLaunchKernelGGL((k_gj_sub_apply<4, 1>), dim3((w + 3) / 4, ndesc), dim3(kThreads), 0, s, descs_dev, np,
-                               k0, j0, ws, w);
-        else if (w > ws)
-            hipLaunchKernelGGL((k_gj_sub_apply<1, 1>), dim3(w, ndesc), dim3(kThreads), 0, s, descs_dev, np, k0, j0, ws,
-                               w);
+        hipLaunchKernelGGL((k_gj_group<NT, WS, RPT>), dim3(ndesc), dim3(NT), 0, s, descs_dev, n, np, k0, j0, ws, w);
+        if (w > ws)
+            hipLaunchKernelGGL(k_gj_apply, dim3(np / 64, ndesc), dim3(kThreads), 0, s, descs_dev, np, k0, j0, ws, w);
     }
 }
 
-// Final column permutation: idx = identity, then for k = n-1..0 swap idx[k],
-// idx[piv[k]].  The swaps are a serial chain on one thread; it runs over LDS
-// copies of the pivots and the permutation (dynamic LDS: 8 np bytes) when
-// they fit, which the workgroup loads and stores in parallel, else in place.
-__global__ __launch_bounds__(kThreads) void k_gj_perm(const GjDesc *__restrict__ descs, int n, int np, int in_lds) {
-    extern __shared__ int s_pp[];
+// Final column permutation: the swaps k <-> piv[k] undone on the columns, last
+// one first, put column perm[j] at place j, perm = the inverse of the map of
+// all row interchanges that the panels composed in g.perm.  (Following the n
+// swaps on one thread took 78 us at n = 1024.)  g.rowsrc is scratch here.
+__global__ __launch_bounds__(1024) void k_gj_perm(const GjDesc *__restrict__ descs, int np) {
     const GjDesc g = descs[blockIdx.x];
-    int *perm = in_lds ? s_pp : g.perm;
-    const int *piv = in_lds ? s_pp + np : g.piv;
-    for (int j = threadIdx.x; j < np; j += kThreads) {
-        perm[j] = j;
-        if (in_lds) s_pp[np + j] = j < n ? g.piv[j] : j;
-    }
+    for (int r = threadIdx.x; r < np; r += 1024) g.rowsrc[r] = g.perm[r];
     __syncthreads();
-    if (threadIdx.x == 0)
-        for (int k = n - 1; k >= 0; --k) {
-            const int p = piv[k];
-            const int t = perm[k];
-            perm[k] = perm[p];
-            perm[p] = t;
-        }
-    __syncthreads();
-    if (in_lds)
-        for (int j = threadIdx.x; j < np; j += kThreads) g.perm[j] = s_pp[j];
+    for (int r = threadIdx.x; r < np; r += 1024) g.perm[g.rowsrc[r]] = r;
 }
 
 GjTiles gj_tiles_default(int n, int np) {
-    // measured on MI355X: 64-column panels from N = 512, in pairs from 1024
-    // (4096: 146 ms against 162 for 32 inverses, 2048: 45 against 47 ms for
-    // 64, 1024: 26.2 against 26.8 ms for 256; at 512 single panels are
-    // faster); 64-column update chunks where np pairs them up (3 % faster
-    // than 32 at N = 4096); four apply columns a workgroup from N = 2048 (one
-    // below: enough workgroups)
+    // measured on MI355X (before k_gj_group; the ranking of the panels is kept
+    // because the blocking decides the rounding): 64-column panels from N =
+    // 512, in pairs from 1024 (4096: 146 ms against 162 for 32 inverses, 2048:
+    // 45 against 47 ms for 64, 1024: 26.2 against 26.8 ms for 256; at 512
+    // single panels are faster); 64-column update chunks where np pairs them
+    // up (3 % faster than 32 at N = 4096)
     GjTiles t;
     t.nb = n >= 1024 && np <= 4096 ? 128 : (n >= 512 ? 64 : (n >= 64 ? 32 : 16));
     t.cw = np % 128 == 0 ? 64 : 32;
@@ -1126,19 +1076,20 @@ GjTiles gj_tiles_default(int n, int np) {
 
 hipError_t launch_gj_invert(const GjDesc *set_a, const GjDesc *set_b, int ndesc, int n, int np, const GjTiles &tiles,
                             hipStream_t s, const GjDesc **final_set) {
-    const int nb = tiles.nb, cw = tiles.cw, cpb = tiles.cpb;
+    const int nb = tiles.nb, cw = tiles.cw;  // (tiles.cpb has no effect)
     if (nb != 16 && nb != 32 && nb != 64 && nb != 128) return hipErrorInvalidValue;
     if (np % 64) return hipErrorInvalidValue;  // the trailing update takes column chunks in pairs
-    if (!(cw == 32 || (cw == 64 && np % 128 == 0)) || (cpb != 1 && cpb != 4)) return hipErrorInvalidValue;
+    if (!(cw == 32 || (cw == 64 && np % 128 == 0))) return hipErrorInvalidValue;
     const int pw = nb == 128 ? 64 : nb;  // columns factored at a time
-    const int in_lds = np <= 8192;       // row map in dynamic LDS (32 KB at most)
-    // factor the panel [k0, k0 + w): groups of 32 / 16 / 8 columns in registers up to np = 4096 (32 doubles a
-    // thread), then 2 columns in LDS up to 8192, else one column at a time
+    // factor the panel [k0, k0 + w): groups of 32 .. 4 columns in registers up to np = 8192 (64 values a thread),
+    // beyond that one column at a time
     auto factor = [&](const GjDesc *d, int k0, int w, bool gather) {
-        if (np <= 1024) launch_gj_panel2<32, 1024, true>(d, ndesc, n, np, pw, k0, w, cpb, s, gather);
-        else if (np <= 2048) launch_gj_panel2<16, 2048, true>(d, ndesc, n, np, pw, k0, w, cpb, s, gather);
-        else if (np <= 4096) launch_gj_panel2<8, 4096, true>(d, ndesc, n, np, pw, k0, w, cpb, s, gather);
-        else if (np <= 8192) launch_gj_panel2<2, 8192>(d, ndesc, n, np, pw, k0, w, cpb, s, gather);
+        if (np <= 256) launch_gj_panel<256, 32, 1>(d, ndesc, n, np, k0, w, s, gather);
+        else if (np <= 512) launch_gj_panel<256, 32, 2>(d, ndesc, n, np, k0, w, s, gather);
+        else if (np <= 1024) launch_gj_panel<512, 32, 2>(d, ndesc, n, np, k0, w, s, gather);
+        else if (np <= 2048) launch_gj_panel<512, 16, 4>(d, ndesc, n, np, k0, w, s, gather);
+        else if (np <= 4096) launch_gj_panel<512, 8, 8>(d, ndesc, n, np, k0, w, s, gather);
+        else if (np <= 8192) launch_gj_panel<512, 4, 16>(d, ndesc, n, np, k0, w, s, gather);
         else hipLaunchKernelGGL(k_gj_panel, dim3(ndesc), dim3(kThreads), 0, s, d, n, np, pw, k0, k0 + w);
     };
     const GjDesc *cur = set_a, *nxt = set_b;
@@ -1149,13 +1100,11 @@ hipError_t launch_gj_invert(const GjDesc *set_a, const GjDesc *set_b, int ndesc,
         const bool pair = nb == 128 && k0 + 128 <= n && np <= 4096;
         factor(cur, k0, k1 - k0, true);
         // row interchanges, then the trailing update into the other buffer
-        hipLaunchKernelGGL(k_gj_rowsrc, dim3(ndesc), dim3(kThreads), in_lds ? np * sizeof(int) : 0, s, cur, np, k0,
-                           k1, in_lds);
+        hipLaunchKernelGGL(k_gj_rowsrc, dim3(ndesc), dim3(kThreads), 0, s, cur, np, k0, k1);
         if (pair) {
             hipLaunchKernelGGL(k_gj_pair_slab, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
             factor(cur, k0 + 64, 64, false);
-            hipLaunchKernelGGL(k_gj_pair_rowsrc, dim3(ndesc), dim3(kThreads), (size_t)np * 2 * sizeof(int), s, cur, np,
-                               k0);
+            hipLaunchKernelGGL(k_gj_pair_rowsrc, dim3(ndesc), dim3(kThreads), (size_t)np * sizeof(int), s, cur, np, k0);
             hipLaunchKernelGGL(k_gj_pair_q2, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
             hipLaunchKernelGGL((k_gj_update<128, 1, 32, true>), dim3(ndesc * (np / 64)), dim3(kThreads), 0, s, cur, np,
                                np / 64, k0, 64);
@@ -1173,9 +1122,7 @@ hipError_t launch_gj_invert(const GjDesc *set_a, const GjDesc *set_b, int ndesc,
         cur = nxt;
         nxt = t;
     }
-    const int perm_lds = np <= 8192;  // 64 KB of dynamic LDS at most
-    hipLaunchKernelGGL(k_gj_perm, dim3(ndesc), dim3(kThreads), perm_lds ? (size_t)np * 2 * sizeof(int) : 0, s, cur, n,
-                       np, perm_lds);
+    hipLaunchKernelGGL(k_gj_perm, dim3(ndesc), dim3(1024), 0, s, cur, np);
     if (final_set) *final_set = cur;
     return hipGetLastError();
 }

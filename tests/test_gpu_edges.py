@@ -56,3 +56,32 @@ def test_lookahead_edges(n, K, moves, kind):
             inv = inv - np.outer(inv[:, e], row @ inv - np.eye(n)[e]) / exact
         got = w.inverse()
     assert np.abs(got - inv).max() <= (1e-9 if not f32 else 16.0 * np.sqrt(n) * 2.0**-24)
+
+
+# Gauss-Jordan groups: 256 threads up to a padded 256 and 512 rows, 512 threads
+# up to 1024, 2048, 4096 and 8192; the last panel and its last group narrower
+# than their tiles (4 pivots a loop body, 32 .. 4 columns a group).
+@pytest.mark.parametrize("n", [3, 67, 255, 257, 511, 513, 1027, 2051, 4101])
+def test_inverse_edges(n):
+    require_gpu()
+    a = well_conditioned(31 + n, n)
+    with dsu.Walker(a, 4) as w:
+        got, (sg, ld) = w.inverse(), w.logdet()
+    s_np, l_np = np.linalg.slogdet(a)
+    # well conditioned: backward-stable elimination, growth far below sqrt(n)
+    assert np.abs(got @ a - np.eye(n)).max() <= 64 * n * 2.0**-53 * 4
+    assert sg == s_np and abs(ld - l_np) <= 64 * n * 2.0**-53 * max(1.0, abs(l_np))
+
+
+# Every pivot column full of ties and every pivot off the diagonal: a signed
+# permutation matrix, whose inverse (its transpose) has no rounding at all.
+@pytest.mark.parametrize("n", [2, 70, 300, 1100])
+def test_inverse_of_signed_permutation_is_exact(n):
+    require_gpu()
+    rng = np.random.default_rng(n)
+    a = np.zeros((n, n))
+    a[np.arange(n), rng.permutation(n)] = rng.choice([-1.0, 1.0], n)
+    with dsu.Walker(a, 4) as w:
+        assert np.array_equal(w.inverse(), a.T)
+        sg, ld = w.logdet()
+    assert ld == 0.0 and sg == round(np.linalg.slogdet(a)[0])
