@@ -63,9 +63,9 @@ enum {
 
 /* Flush kernel selection for the single-walker form. */
 enum {
-    DSU_FLUSH_AUTO = 0,  /* VALU for k <= 4, matrix cores above                  */
+    DSU_FLUSH_AUTO = 0,  /* VALU for k = 1 and small k n, matrix cores above     */
     DSU_FLUSH_VALU = 1,  /* vector-ALU rank-k kernel                             */
-    DSU_FLUSH_MFMA = 2   /* fused matrix-core (MFMA) rank-k kernel               */
+    DSU_FLUSH_MFMA = 2   /* matrix-core (MFMA) rank-k kernels                    */
 };
 
 #define DSU_MAX_K 256    /* largest supported delay */
@@ -242,13 +242,13 @@ int dsu_zget_inverse(dsu_zwalker *w, double *out_host);
  * since the last fresh inverse). */
 int dsu_zget_logdet(dsu_zwalker *w, double *logabs, double *phase);
 int dsu_zwalker_pending(dsu_zwalker *w, int32_t *k_out);
-/* Flush kernel of the complex walker.  W = (BT U^T - E) C^{-T} is formed row
- * by row on the vector ALUs; the rank-k update BT -= W Vg then runs, with
- * DSU_FLUSH_MFMA, on the FP64 matrix cores through the real embedding of the
+/* Flush kernel of the complex walker.  Where 2k <= 256 the three products of
+ * eq. (4) run on the FP64 matrix cores through the real embedding of the
  * complex operands (the inverse and W read as real rows of interleaved
- * doubles, Vg expanded to 2k real rows: each complex product as its four real
- * products), tiled over rows and columns, when 2k <= 256; otherwise, and
- * with DSU_FLUSH_VALU, as a complex product on the vector ALUs.  DSU_FLUSH_AUTO (default): the matrix cores for k > 2. */
+ * doubles, U, C^{-1} and Vg expanded to 2k real rows: each complex product as
+ * its four real products); otherwise, and with DSU_FLUSH_VALU, W is formed row
+ * by row and BT -= W Vg as a complex product on the vector ALUs.
+ * DSU_FLUSH_AUTO (default): the matrix cores. */
 int dsu_zwalker_set_flush_kernel(dsu_zwalker *w, int32_t mode);
 
 /* ======================================================================

@@ -113,7 +113,7 @@ void Bucket::release() {
     if (stream) (void)hipStreamSynchronize(stream);
     if (side) (void)hipStreamSynchronize(side);
     drop_graph();
-    for (void *p : {(void *)kvec, ddesc_, fdesc_, sub_ddesc_, (void *)sub_pos_, (void *)sub_bt_, (void *)drift_,
+    for (void *p : {(void *)kvec, ddesc_, sub_ddesc_, (void *)sub_pos_, (void *)sub_bt_, (void *)drift_,
                     (void *)res_rows_, (void *)res_eidx_, (void *)res_bits_})
         dfree(p);
     if (res_host_) (void)hipHostFree(res_host_);
@@ -128,7 +128,7 @@ void Bucket::release() {
     stage_h_ = nullptr;
     pending_.clear();
     kvec = nullptr;
-    ddesc_ = fdesc_ = sub_ddesc_ = nullptr;
+    ddesc_ = sub_ddesc_ = nullptr;
     sub_pos_ = nullptr;
     sub_bt_ = nullptr;
     drift_ = nullptr;
@@ -162,15 +162,13 @@ int Bucket::ensure_capacity(int n) {
     // callers grow the arrays only between sweeps, after a synchronisation)
     HIPCHK(hipStreamSynchronize(stream));
     std::vector<int> keep(status_h_ ? status_h_ : nullptr, status_h_ ? status_h_ + pending_.size() : nullptr);
-    for (void *p : {ddesc_, fdesc_, sub_ddesc_, (void *)sub_pos_, (void *)sub_bt_, (void *)drift_}) dfree(p);
+    for (void *p : {ddesc_, sub_ddesc_, (void *)sub_pos_, (void *)sub_bt_, (void *)drift_}) dfree(p);
     if (status_h_) (void)hipHostFree(status_h_);
     if (stage_h_) (void)hipHostFree(stage_h_);
     status_h_ = nullptr;
     stage_h_ = nullptr;
     const size_t dsz = std::max(sizeof(DetDesc<double>), sizeof(DetDesc<float>));
-    const size_t fsz = std::max(sizeof(FlushDesc<double>), sizeof(FlushDesc<float>));
     CHK(dev_alloc(&ddesc_, dsz * c));
-    CHK(dev_alloc(&fdesc_, fsz * c));
     CHK(dev_alloc(&sub_ddesc_, dsz * c));
     CHK(dalloc(&sub_pos_, c));
     CHK(dalloc(&sub_bt_, c));
@@ -211,14 +209,9 @@ template <typename T> static DetDesc<T> to_desc(const DetSlot &s) {
 
 template <typename T> int Bucket::upload_t() {
     std::vector<DetDesc<T>> dd(dets.size());
-    std::vector<FlushDesc<T>> fd(dets.size());
-    for (size_t i = 0; i < dets.size(); ++i) {
-        dd[i] = to_desc<T>(dets[i]);
-        fd[i] = FlushDesc<T>{dd[i].bt, dd[i].u, dd[i].vg, dd[i].cfl, dd[i].idx, sh.kp};
-    }
+    for (size_t i = 0; i < dets.size(); ++i) dd[i] = to_desc<T>(dets[i]);
     if (!dets.empty()) {
         HIPCHK(hipMemcpyAsync(ddesc_, dd.data(), sizeof(dd[0]) * dd.size(), hipMemcpyHostToDevice, stream));
-        HIPCHK(hipMemcpyAsync(fdesc_, fd.data(), sizeof(fd[0]) * fd.size(), hipMemcpyHostToDevice, stream));
         HIPCHK(hipStreamSynchronize(stream));
     }
     return DSU_OK;

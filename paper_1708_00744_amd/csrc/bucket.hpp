@@ -93,7 +93,7 @@ class Bucket {
 
   private:
     int cap_ = 0;
-    void *ddesc_ = nullptr, *fdesc_ = nullptr;
+    void *ddesc_ = nullptr;
     void *sub_ddesc_ = nullptr;
     double **sub_pos_ = nullptr;
     void **sub_bt_ = nullptr;

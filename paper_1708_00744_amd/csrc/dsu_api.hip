@@ -34,7 +34,7 @@ struct dsu_walker {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     LaDev wd{};
-    void *flush_desc = nullptr;     // FlushDesc<T>[1] on the device
+    void *flush_y = nullptr, *flush_w = nullptr;  // scratch of the matrix-core flush
     double **a_ptr = nullptr;       // device array {a}
     void **bt_ptr = nullptr;        // device array {bt}
     double *inv_tmp = nullptr;      // n x n FP64 for dsu_get_inverse
@@ -76,7 +76,7 @@ static void walker_md_free(dsu_walker *w) {
 static void walker_free(dsu_walker *w) {
     if (w->wd.phi != w->wd.phi64) dfree(w->wd.phi);  // FP64 walkers share one row buffer
     for (void *p : {w->wd.bt, w->wd.u, w->wd.vg, w->wd.a, w->wd.phi64, w->wd.cinv, w->wd.cinvt, w->wd.part, w->wd.t, w->wd.b,
-                    w->wd.ratio, (void *)w->wd.idx, (void *)w->wd.counter, w->flush_desc, (void *)w->a_ptr, (void *)w->bt_ptr, (void *)w->inv_tmp})
+                    w->wd.ratio, (void *)w->wd.idx, (void *)w->wd.counter, w->flush_y, w->flush_w, (void *)w->a_ptr, (void *)w->bt_ptr, (void *)w->inv_tmp})
         dfree(p);
     if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
@@ -178,21 +178,9 @@ extern "C" int dsu_walker_create(int32_t n, int32_t k_delay, int32_t precision, 
     if (hipMemcpy(w->a_ptr, &w->wd.a, sizeof(double *), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(w->bt_ptr, &w->wd.bt, sizeof(void *), hipMemcpyHostToDevice) != hipSuccess)
         TRY(fail(DSU_EDEVICE, "pointer table upload failed"));
-    if (precision == DSU_FP64) {
-        FlushDesc<double> fd{(double *)w->wd.bt, (const double *)w->wd.u, (const double *)w->wd.vg,
-                             (const double *)w->wd.cinv,
-                             w->wd.idx, w->wd.ldc};
-        TRY(dev_alloc(&w->flush_desc, sizeof(fd)));
-        if (hipMemcpy(w->flush_desc, &fd, sizeof(fd), hipMemcpyHostToDevice) != hipSuccess)
-            TRY(fail(DSU_EDEVICE, "descriptor upload failed"));
-    } else {
-        FlushDesc<float> fd{(float *)w->wd.bt, (const float *)w->wd.u, (const float *)w->wd.vg,
-                            (const double *)w->wd.cinv,
-                            w->wd.idx, w->wd.ldc};
-        TRY(dev_alloc(&w->flush_desc, sizeof(fd)));
-        if (hipMemcpy(w->flush_desc, &fd, sizeof(fd), hipMemcpyHostToDevice) != hipSuccess)
-            TRY(fail(DSU_EDEVICE, "descriptor upload failed"));
-    }
+    TRY(dev_alloc(&w->flush_y, s * (precision == DSU_FP64 ? flush_scratch_elems<double>(w->np, w->np, w->kp)
+                                                          : flush_scratch_elems<float>(w->np, w->np, w->kp))));
+    TRY(dev_alloc(&w->flush_w, np * kp * s));
     TRY(w->gj.alloc(1, w->np, n));
     if (hipMemcpy2D(w->wd.a, np * sizeof(double), slater_host, n * sizeof(double), n * sizeof(double), n,
                     hipMemcpyHostToDevice) != hipSuccess)
@@ -212,13 +200,23 @@ extern "C" int dsu_walker_destroy(dsu_walker *w) {
     return DSU_OK;
 }
 
+template <typename T> static hipError_t walker_flush_t(dsu_walker *w, bool valu) {
+    const FlushArgs<T> fa{(T *)w->wd.bt, (const T *)w->wd.u, (const T *)w->wd.vg, (const double *)w->wd.cinv,
+                          (const double *)w->wd.cinvt, w->wd.idx, w->wd.ldc, (T *)w->flush_y, (T *)w->flush_w};
+    return valu ? launch_flush_valu<T>(fa, w->np, w->k, w->stream)
+                : launch_flush_mfma<T, 1>(fa, w->np, w->k, w->stream);
+}
+
 static int walker_do_flush(dsu_walker *w) {
     if (w->k > 0) {
-        const int mode = w->flush_mode == DSU_FLUSH_VALU ? 1 : (w->flush_mode == DSU_FLUSH_MFMA ? 0 : (w->k <= 4 ? 1 : 0));
-        if (w->prec == DSU_FP64)
-            HIPCHK(launch_flush<double>((const FlushDesc<double> *)w->flush_desc, 1, w->n, w->np, w->k, mode, w->stream));
-        else
-            HIPCHK(launch_flush<float>((const FlushDesc<float> *)w->flush_desc, 1, w->n, w->np, w->k, mode, w->stream));
+        // the vector ALUs read BT, U and Vg once per slot group and cost about
+        // k np; the matrix cores three launches.  FP64 us, vector / matrix:
+        // k = 1 16 / 22 at n = 1024, 64 / 80 at 4096; k = 2 15 / 17 at 512, 23 /
+        // 22 at 1024; k = 4 16 / 17 at 256, 23 / 17 at 512
+        const bool valu = w->flush_mode == DSU_FLUSH_VALU ||
+                          (w->flush_mode == DSU_FLUSH_AUTO && (w->k == 1 || (w->k <= 4 && w->k * w->np <= 1024)));
+        if (w->prec == DSU_FP64) HIPCHK(walker_flush_t<double>(w, valu));
+        else HIPCHK(walker_flush_t<float>(w, valu));
     }
     w->k = 0;
     w->slots = 0;

@@ -57,18 +57,22 @@ template <int KP> __host__ __device__ __forceinline__ int cfl32_index(int l, int
     return ((t * (KP / 16) + (s >> 2)) * 64 + lane) * 4 + (s & 3);
 }
 
-// --------------------------------------------------- descriptors (device)
-// One rank-k update target: BT <- BT - ((BT U^T - E) C^T) Vg   (eq. (4),
-// transposed and row-local).  idx[j] = electron of slot j (-1 = unused).
-template <typename T> struct FlushDesc {
+// One rank-k update of the host-driven walker: BT <- BT - ((BT U^T - E) C^T) Vg
+// (eq. (4), transposed and row-local).  idx[j] = electron of slot j.  A complex
+// walker passes its interleaved arrays as doubles.
+template <typename T> struct FlushArgs {
     T *bt;
     const T *u;
     const T *vg;
-    const double *cinv;
+    const double *cinv;   // C^{-1}, row length ldc
+    const double *cinvt;  // its transpose
     const int *idx;
     int ldc;
+    T *y;                 // scratch: flush_scratch_elems
+    T *w;                 // scratch: np x padded (real) slots
 };
 
+// --------------------------------------------------- descriptors (device)
 // Per-determinant running state of the batched form (device memory).
 struct DetState {
     double logdet;
@@ -111,17 +115,14 @@ template <typename T> struct DetDesc {
 // ------------------------------------------------------- launchers (host)
 // All launchers return hipSuccess or the launch error.
 
-// Flush (eq. (4)) of `ndesc` determinants with `kslots` delayed slots
-// (<= kp of the descriptors' buffers); mode 0 = MFMA fused, 1 = VALU.
-// ld: row length of BT, U and Vg (0 = np; MFMA mode only otherwise).
-template <typename T>
-hipError_t launch_flush(const FlushDesc<T> *descs_dev, int ndesc, int n, int np, int kslots, int mode,
-                        hipStream_t s, int ld = 0);
-
-// C[0:nrows, 0:ncols] -= W[:, 0:kslots] V[0:kslots, :] (FP64, matrix cores;
-// V rows kslots .. padded width zero; nrows and ncols multiples of 64).
-hipError_t launch_gemm_sub(const double *W, int ldw, int kslots, const double *V, int ldv, double *C, int ldc,
-                           int nrows, int ncols, hipStream_t s);
+// Flush (eq. (4)) of one determinant with `kslots` delayed slots on matrix
+// cores (Z = 2: complex, T = double, 2 kslots <= 256) or vector ALUs (<= 64).
+template <typename T, int Z>
+hipError_t launch_flush_mfma(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s);
+template <typename T> hipError_t launch_flush_valu(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s);
+// Elements of the y scratch for up to kp_max padded (real) slots, rows of ldr
+// real elements.
+template <typename T> size_t flush_scratch_elems(int np, int ldr, int kp_max);
 
 // FP64 inversion by blocked Gauss-Jordan with partial pivoting.
 struct GjDesc {

@@ -1,14 +1,13 @@
 // k_linalg.hip -- matrix kernels of libdsu for gfx950.
 //
-//  * k_flush_mfma: the en-bloc update of the inverse, Sherman-Morrison-Woodbury,
-//    eq. (4) of arXiv:1708.00744, written for the transposed inverse BT:
+//  * k_flush_y / k_flush_w / k_flush_bt: the host-driven walker's en-bloc update
+//    of the inverse, Sherman-Morrison-Woodbury, eq. (4) of arXiv:1708.00744,
+//    written for the transposed inverse BT:
 //        Y  = BT U^T            (np x k)   U   = accepted new orbital rows
 //        Y' = Y - E             E[idx_j][j] = 1
 //        W  = Y' C^{-T}         C^{-1}     = inverse of I_k + V'A^{-1}U (eq. (3))
 //        BT = BT - W Vg         Vg         = stale BT rows of the moved electrons
-//    Row i of the new BT needs only row i of the old one, so each workgroup
-//    owns 64 rows and does the three products back to back on matrix cores
-//    (v_mfma_*_16x16x4), reading its rows of BT twice and writing them once.
+//    on matrix cores (v_mfma_*_16x16x4), one launch per product.
 //  * k_flush_valu: the same update with vector ALUs, one wave per row (small k).
 //  * k_gj_update: the trailing update of the Gauss-Jordan inversion,
 //    M' = (row-interchanged M) - W Q, on matrix cores.
@@ -18,6 +17,215 @@
 #include "tiles.hpp"
 
 namespace dsu {
+
+// ---------------------------------------------------------------------------
+// The flush of one determinant, real (Z = 1) or complex (Z = 2, interleaved:
+// the real embedding, each complex product as its four real ones).  One
+// workgroup per 64 rows doing the three products back to back left all but
+// N / 64 compute units idle (161 us at N = 1024, K = 64 in FP64, 644 us at N =
+// 4096, K = 128 in FP32), so each product has the launch its shape asks for:
+//  * Y: 64 rows x 32 slots a workgroup and, in FP64, the columns in up to 8
+//    parts where the rows leave the GPU idle (partial sums, added by W's
+//    launch; FP32 keeps one chain of additions per element).  Operands go from
+//    global memory straight into fragments, four 128-byte steps ahead;
+//  * W: a wave per 16 rows x 32 slots, C^{-T} coalesced;
+//  * BT: 64 x 64 tiles, V through LDS.
+// Measured, the three launches: N = 1024, K = 64 FP64 161 -> 32 us, N = 1000, K =
+// 32 105 -> 25, N = 4096, K = 128 FP32 644 -> 199, complex N = 500, K = 16 51 ->
+// 25 (there against W row by row on the vector units, an embedding and an update).
+// ---------------------------------------------------------------------------
+// Y[part][row][slot], slots kb .. kb + NT 16: real columns c of BT's row and U's
+// rows.  For Z = 2 slot 2 j is (re, -im) and 2 j + 1 (im, re) of U[j].
+template <typename T, int NT, int Z>
+__global__ __launch_bounds__(kThreads) void k_flush_y(FlushArgs<T> fa, int np, int ldr, int kp, int nkb, int cols) {
+    typedef typename Vec16<T>::type vec_t;
+    constexpr int VEC = 16 / (int)sizeof(T), E = 2 * VEC, CW = 4 * E, D = 4;  // E columns a lane and step, D steps ahead
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int kb = (b % nkb) * 16 * NT, rb = (b / nkb) % (np / 64), part = b / nkb / (np / 64);
+    const int c0 = part * cols, c1 = c0 + cols < ldr ? c0 + cols : ldr;
+    DSU_GLOBAL const T *ap = gmem<const T>(fa.bt) + (size_t)(64 * rb + 16 * wave + lr) * ldr + E * lk;
+    DSU_GLOBAL const T *bp[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) bp[t] = gmem(fa.u) + (size_t)((kb + 16 * t + lr) / Z) * ldr + E * lk;
+    typename Mma<T>::acc_t acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = typename Mma<T>::acc_t{0, 0, 0, 0};
+    vec_t a[D][2], bv[D][NT][2];
+    auto load = [&](int d, int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            a[d][h] = *(DSU_GLOBAL const vec_t *)(ap + c + h * VEC);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) bv[d][t][h] = *(DSU_GLOBAL const vec_t *)(bp[t] + c + h * VEC);
+        }
+    };
+    auto mul = [&](int d) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                vec_t x = bv[d][t][h];
+                if constexpr (Z == 2) {  // (kb and 16 t are even: lr's parity is the slot's)
+                    const T re = x[0], im = x[1];
+                    x[0] = lr & 1 ? im : re;
+                    x[1] = lr & 1 ? re : -im;
+                }
+#pragma unroll
+                for (int q = 0; q < VEC; ++q) acc[t] = Mma<T>::mma(a[d][h][q], x[q], acc[t]);
+            }
+    };
+    // c1 - c0 is a multiple of CW; D steps loaded ahead, in a ring
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, c0 + d * CW < c1 ? c0 + d * CW : c0);
+    for (int c = c0; c < c1; c += D * CW)
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (c + d * CW < c1) {
+                mul(d);
+                const int cn = c + (D + d) * CW;
+                load(d, cn < c1 ? cn : c0);
+            }
+    T *y = fa.y + ((size_t)part * np + 64 * rb + 16 * wave + Mma<T>::row0(lane)) * kp + kb + lr;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[(size_t)i * Mma<T>::row_step * kp + 16 * t] = acc[t][i];
+}
+
+// W[row][l] = sum_j (Y - E)[row][j] C^{-1}[l][j] for 16 NT of the (real) slots
+// l, one wave per 16 rows; C^{-1} taken as zero beyond kslots (complex) slots.
+// The row's Y values (sums of the parts) are in registers before the products.
+template <typename T, int KP, int NT, int Z>
+__global__ __launch_bounds__(64) void k_flush_w(FlushArgs<T> fa, int np, int parts, int kslots) {
+    constexpr int S = KP / 4, nkb = KP / (16 * NT);
+    const int lane = threadIdx.x, lr = lane & 15, lk = lane >> 4;
+    const int kb = (blockIdx.x % nkb) * 16 * NT, row = blockIdx.x / nkb * 16 + lr;
+    DSU_GLOBAL const T *y = gmem<const T>(fa.y) + (size_t)row * KP + lk;
+    DSU_GLOBAL const double *ct = gmem(fa.cinvt);
+    DSU_GLOBAL const int *idx = gmem(fa.idx);
+    T a[S];
+    int e[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        a[s] = y[4 * s];
+        e[s] = idx[(4 * s + lk) / Z < kslots ? (4 * s + lk) / Z : 0];
+    }
+#pragma unroll 2
+    for (int q = 1; q < parts; ++q)
+#pragma unroll
+        for (int s = 0; s < S; ++s) a[s] += y[(size_t)q * np * KP + 4 * s];
+    typename Mma<T>::acc_t acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = typename Mma<T>::acc_t{0, 0, 0, 0};
+    constexpr int B = S < 16 ? S : 16;  // steps whose C^{-T} loads are in flight together
+#pragma unroll
+    for (int s0 = 0; s0 < S; s0 += B) {
+        if (4 * s0 >= Z * kslots) break;
+        double c[B][NT];
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int j = 4 * (s0 + b) + lk, l = kb + 16 * t + lr, jz = j / Z, lz = l / Z;
+                const bool in = jz < kslots && lz < kslots;
+                DSU_GLOBAL const double *p = ct + (size_t)Z * (in ? (size_t)jz * fa.ldc + lz : 0);
+                if constexpr (Z == 2) {
+                    // (y_re, y_im) times (c_re, c_im): re takes c_re, -c_im; im takes c_im, c_re
+                    const double v = p[(l ^ j) & 1];
+                    c[b][t] = !in ? 0.0 : ((l & 1) < (j & 1) ? -v : v);
+                } else {
+                    c[b][t] = in ? p[0] : 0.0;
+                }
+            }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int j = 4 * (s0 + b) + lk;
+            T v = a[s0 + b];
+            if (j / Z >= kslots) v = T(0);
+            else if (j % Z == 0 && e[s0 + b] == row) v -= T(1);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = Mma<T>::mma(v, T(c[b][t]), acc[t]);
+        }
+    }
+    T *w = fa.w + (size_t)(blockIdx.x / nkb * 16 + Mma<T>::row0(lane)) * KP + kb + lr;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[(size_t)i * Mma<T>::row_step * KP + 16 * t] = acc[t][i];
+}
+
+// One 64 x 64 tile of BT -= W Vg (real columns; Z = 2: row 2 j of the embedded
+// Vg is (re, im) of Vg[j], row 2 j + 1 (-im, re)).
+template <typename T, int KP, int Z>
+__global__ __launch_bounds__(kThreads) void k_flush_bt(FlushArgs<T> fa, int ldr, int ncb) {
+    typedef Phase3Cfg<T, KP> C;
+    typedef typename Vec16<T>::type vec_t;
+    constexpr int CW = C::CW, LDV = C::LDV, VEC = 16 / (int)sizeof(T), RS = Mma<T>::row_step;
+    constexpr int NV = KP * (CW / VEC) / kThreads;
+    __shared__ __attribute__((aligned(16))) T lds[KP * LDV];
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int r0 = (b / ncb) * 64, cb = (b % ncb) * 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    DSU_GLOBAL const T *wr = gmem<const T>(fa.w) + (size_t)(r0 + 16 * wave + (lane & 15)) * KP + (lane >> 4);
+    DSU_GLOBAL T *rp = gmem(fa.bt) + (size_t)(r0 + 16 * wave + Mma<T>::row0(lane)) * ldr + cb + (lane & 15);
+    DSU_GLOBAL const T *vg = gmem(fa.vg) + cb;
+    T wa[KP / 4];
+#pragma unroll
+    for (int s = 0; s < KP / 4; ++s) wa[s] = -wr[4 * s];
+    for (int c0 = 0; c0 < 64; c0 += CW) {
+        vec_t sv[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const int v = tid + q * kThreads, r = v / (CW / VEC), cc = (v % (CW / VEC)) * VEC;
+            sv[q] = *(DSU_GLOBAL const vec_t *)(vg + (size_t)(r / Z) * ldr + c0 + cc);
+            if constexpr (Z == 2)
+                if (r & 1) sv[q] = vec_t{-sv[q][1], sv[q][0]};
+        }
+        typename Mma<T>::acc_t acc[CW / 16];
+#pragma unroll
+        for (int t = 0; t < CW / 16; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[t][i] = rp[(size_t)(i * RS) * ldr + c0 + 16 * t];
+        if (c0 > 0) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const int v = tid + q * kThreads, r = v / (CW / VEC), cc = (v % (CW / VEC)) * VEC;
+            *reinterpret_cast<vec_t *>(lds + r * LDV + cc) = sv[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < KP / 4; ++s) {
+            const T *bp = lds + (4 * s + (lane >> 4)) * LDV + (lane & 15);
+#pragma unroll
+            for (int t = 0; t < CW / 16; ++t) acc[t] = Mma<T>::mma(wa[s], bp[16 * t], acc[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < CW / 16; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rp[(size_t)(i * RS) * ldr + c0 + 16 * t] = acc[t][i];
+    }
+}
+
+// Column parts of Y's launch: FP64 only, up to 8, while the launch has fewer
+// than 256 workgroups and a part at least 128 columns.
+template <typename T> static int flush_parts(int np, int ldr, int kp) {
+    int p = 1;
+    if (sizeof(T) == 8)
+        while (p < 8 && (np / 64) * (kp / (kp > 16 ? 32 : 16)) * p < 256 && ldr / (2 * p) >= 128) p *= 2;
+    return p;
+}
+
+template <typename T> size_t flush_scratch_elems(int np, int ldr, int kp_max) {
+    size_t most = 0;
+    for (int kp = 16; kp <= kp_max; kp *= 2) {
+        const size_t e = (size_t)flush_parts<T>(np, ldr, kp) * np * kp;
+        most = e > most ? e : most;
+    }
+    return most;
+}
+template size_t flush_scratch_elems<float>(int, int, int);
+template size_t flush_scratch_elems<double>(int, int, int);
 
 template <typename T, int KP> struct FlushLds {
     static constexpr int LDY = KP + 16 / (int)sizeof(T);
@@ -29,19 +237,18 @@ template <typename T, int KP> struct FlushLds {
 };
 
 // ---------------------------------------------------------------------------
-// Fused Woodbury flush, one 64-row block of one determinant per workgroup.
+// The three products of eq. (4) in one launch, 64 rows per workgroup: for
+// matrices of at most kFusedRows padded rows, where two launches fewer count
+// more than idle compute units (np = 64: 9 us against 13 in three launches; np = 128: 14
+// and 15; np = 192: 18 and 17).
 // ---------------------------------------------------------------------------
-// Rows of BT, U and Vg are `ld` elements long (ld = np for a real inverse;
-// the complex walker passes its interleaved complex inverse as real rows of
-// 2 np, with U, Vg and C^{-1} in their real embedding).
+constexpr int kFusedRows = 128;
+
 template <typename T, int KP>
-__global__ __launch_bounds__(kThreads) void k_flush_mfma(const FlushDesc<T> *__restrict__ descs, int ld,
-                                                         int nblk, int kslots) {
+__global__ __launch_bounds__(kThreads) void k_flush_fused(FlushArgs<T> fd, int ld, int kslots) {
     __shared__ __attribute__((aligned(16))) T lds[FlushLds<T, KP>::elems];
     constexpr int LDY = FlushLds<T, KP>::LDY;
-    const int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int d = b / nblk, r0 = (b % nblk) * kRowBlock;
-    const FlushDesc<T> fd = descs[d];
+    const int r0 = blockIdx.x * kRowBlock;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     typename Mma<T>::acc_t acc[KP / 16];
@@ -72,41 +279,37 @@ __global__ __launch_bounds__(kThreads) void k_flush_mfma(const FlushDesc<T> *__r
     rowblock_plus_wv<T, KP>(fd.bt + (size_t)r0 * ld, ld, ld, fd.vg, ld, wa, lds);
 }
 
-// ---------------------------------------------------------------------------
-// C[0:nrows, 0:ncols] -= W[:, 0:kslots] V[0:kslots, :] in FP64 on matrix cores,
-// tiled over rows and columns (64 x 64 per workgroup) so that one matrix
-// fills the GPU.  W fragments beyond kslots are taken as zero; V rows beyond
-// kslots (up to KP) must be zero.  nrows and ncols multiples of 64.
-// ---------------------------------------------------------------------------
-template <int KP>
-__global__ __launch_bounds__(kThreads) void k_gemm_sub(const double *__restrict__ W, int ldw, int kslots,
-                                                       const double *__restrict__ V, int ldv, double *C, int ldc,
-                                                       int ncb) {
-    __shared__ __attribute__((aligned(16))) double lds[KP * Phase3Cfg<double, KP>::LDV];
-    const int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int r0 = (b / ncb) * kRowBlock, c0 = (b % ncb) * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double wa[KP / 4];
-    const double *wr = W + (size_t)(r0 + 16 * wave + (lane & 15)) * ldw + (lane >> 4);
-#pragma unroll
-    for (int s = 0; s < KP / 4; ++s) wa[s] = 4 * s + (lane >> 4) < kslots ? -wr[4 * s] : 0.0;
-    rowblock_plus_wv<double, KP>(C + (size_t)r0 * ldc + c0, ldc, 64, V + c0, ldv, wa, lds);
+template <typename T, int KP, int Z>
+static hipError_t flush_mfma(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s) {
+    if constexpr (Z == 1)
+        if (np <= kFusedRows) {
+            hipLaunchKernelGGL((k_flush_fused<T, KP>), dim3(np / kRowBlock), dim3(kThreads), 0, s, fa, np, kslots);
+            return hipGetLastError();
+        }
+    constexpr int NT = KP > 16 ? 2 : 1;
+    const int ldr = Z * np, nkb = KP / (16 * NT), parts = flush_parts<T>(np, ldr, KP);
+    // whole steps of 128 bytes a part
+    const int step = 128 / (int)sizeof(T), cols = ((ldr + parts - 1) / parts + step - 1) / step * step;
+    hipLaunchKernelGGL((k_flush_y<T, NT, Z>), dim3((np / 64) * nkb * parts), dim3(kThreads), 0, s, fa, np, ldr, KP, nkb,
+                       cols);
+    hipLaunchKernelGGL((k_flush_w<T, KP, NT, Z>), dim3((np / 16) * nkb), dim3(64), 0, s, fa, np, parts, kslots);
+    hipLaunchKernelGGL((k_flush_bt<T, KP, Z>), dim3((np / 64) * (ldr / 64)), dim3(kThreads), 0, s, fa, ldr, ldr / 64);
+    return hipGetLastError();
 }
 
-hipError_t launch_gemm_sub(const double *W, int ldw, int kslots, const double *V, int ldv, double *C, int ldc,
-                           int nrows, int ncols, hipStream_t s) {
-    if (nrows % kRowBlock || ncols % 64 || kslots < 1) return hipErrorInvalidValue;
-    const int ncb = ncols / 64;
-    const dim3 grid((nrows / kRowBlock) * ncb);
-#define DSU_GS(KPV)                                                                                              \
-    if (kslots <= KPV) {                                                                                         \
-        hipLaunchKernelGGL((k_gemm_sub<KPV>), grid, dim3(kThreads), 0, s, W, ldw, kslots, V, ldv, C, ldc, ncb);  \
-        return hipGetLastError();                                                                                \
-    }
-    DSU_GS(16) DSU_GS(32) DSU_GS(64) DSU_GS(128) DSU_GS(256)
-#undef DSU_GS
+template <typename T, int Z> hipError_t launch_flush_mfma(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s) {
+    if (kslots <= 0) return hipSuccess;
+    const int kr = Z * kslots;
+    if (kr <= 16) return flush_mfma<T, 16, Z>(fa, np, kslots, s);
+    if (kr <= 32) return flush_mfma<T, 32, Z>(fa, np, kslots, s);
+    if (kr <= 64) return flush_mfma<T, 64, Z>(fa, np, kslots, s);
+    if (kr <= 128) return flush_mfma<T, 128, Z>(fa, np, kslots, s);
+    if (kr <= 256) return flush_mfma<T, 256, Z>(fa, np, kslots, s);
     return hipErrorInvalidValue;
 }
+template hipError_t launch_flush_mfma<float, 1>(const FlushArgs<float> &, int, int, hipStream_t);
+template hipError_t launch_flush_mfma<double, 1>(const FlushArgs<double> &, int, int, hipStream_t);
+template hipError_t launch_flush_mfma<double, 2>(const FlushArgs<double> &, int, int, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // VALU flush: one wave per row of BT, k <= KMAX slots in registers.
@@ -119,12 +322,9 @@ __device__ __forceinline__ T wave_sum(T v) {
 }
 
 template <typename T, int KMAX>
-__global__ __launch_bounds__(kThreads) void k_flush_valu(const FlushDesc<T> *__restrict__ descs, int np, int kslots) {
+__global__ __launch_bounds__(kThreads) void k_flush_valu(FlushArgs<T> fd, int np, int kslots) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int rows_per_det = np;
-    const int g = blockIdx.x * 4 + wave;
-    const int d = g / rows_per_det, row = g % rows_per_det;
-    const FlushDesc<T> fd = descs[d];
+    const int row = blockIdx.x * 4 + wave;
     T *bt = fd.bt + (size_t)row * np;
     T y[KMAX];
 #pragma unroll
@@ -158,37 +358,19 @@ __global__ __launch_bounds__(kThreads) void k_flush_valu(const FlushDesc<T> *__r
     }
 }
 
-template <typename T>
-hipError_t launch_flush(const FlushDesc<T> *descs_dev, int ndesc, int n, int np, int kslots, int mode,
-                        hipStream_t s, int ld) {
-    (void)n;
-    if (ld == 0) ld = np;
-    if (mode == 1 && ld != np) return hipErrorInvalidValue;
-    if (ndesc <= 0 || kslots <= 0) return hipSuccess;
-    if (mode == 1) {
-        const int blocks = ndesc * np / 4;
-#define DSU_VALU(KM)                                                                             \
-    if (kslots <= KM) {                                                                          \
-        hipLaunchKernelGGL((k_flush_valu<T, KM>), dim3(blocks), dim3(kThreads), 0, s, descs_dev, np, kslots); \
-        return hipGetLastError();                                                                \
+template <typename T> hipError_t launch_flush_valu(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s) {
+    if (kslots <= 0) return hipSuccess;
+#define DSU_VALU(KM)                                                                                   \
+    if (kslots <= KM) {                                                                                \
+        hipLaunchKernelGGL((k_flush_valu<T, KM>), dim3(np / 4), dim3(kThreads), 0, s, fa, np, kslots); \
+        return hipGetLastError();                                                                      \
     }
-        DSU_VALU(1) DSU_VALU(2) DSU_VALU(4) DSU_VALU(8) DSU_VALU(16) DSU_VALU(32) DSU_VALU(64)
+    DSU_VALU(1) DSU_VALU(2) DSU_VALU(4) DSU_VALU(8) DSU_VALU(16) DSU_VALU(32) DSU_VALU(64)
 #undef DSU_VALU
-        return hipErrorInvalidValue;
-    }
-    const int nblk = np / kRowBlock;
-    const dim3 grid(ndesc * nblk);
-#define DSU_MFMA(KPV)                                                                            \
-    if (kslots <= KPV) {                                                                         \
-        hipLaunchKernelGGL((k_flush_mfma<T, KPV>), grid, dim3(kThreads), 0, s, descs_dev, ld, nblk, kslots); \
-        return hipGetLastError();                                                                \
-    }
-    DSU_MFMA(16) DSU_MFMA(32) DSU_MFMA(64) DSU_MFMA(128) DSU_MFMA(256)
-#undef DSU_MFMA
     return hipErrorInvalidValue;
 }
-template hipError_t launch_flush<float>(const FlushDesc<float> *, int, int, int, int, int, hipStream_t, int);
-template hipError_t launch_flush<double>(const FlushDesc<double> *, int, int, int, int, int, hipStream_t, int);
+template hipError_t launch_flush_valu<float>(const FlushArgs<float> &, int, int, hipStream_t);
+template hipError_t launch_flush_valu<double>(const FlushArgs<double> &, int, int, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Blocked Gauss-Jordan inversion (FP64, in place, partial pivoting).

@@ -148,24 +148,6 @@ __global__ __launch_bounds__(kThreads) void k_zflush_w(ZWalkerDev w, int np, int
     }
 }
 
-// Real embedding of the rank-k update BT -= W Vg for the FP64 matrix cores.
-// Read as real matrices (each complex entry two adjacent doubles), BT is
-// np x 2np and W np x 2k; with Vg[j][c] = x + i y,
-//   Vh[2j][2c] = x,  Vh[2j][2c+1] = y,  Vh[2j+1][2c] = -y,  Vh[2j+1][2c+1] = x
-// the real product W Vh is W Vg: each complex product as its four real
-// products.  Rows 2k .. kp2-1 of Vh are zero.
-__global__ void k_zembed_v(ZWalkerDev w, double *vh, int np, int k) {
-    const int r = blockIdx.y;  // embedded slot row
-    const int j = r >> 1, odd = r & 1;
-    const bool live = j < k;
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < np; c += gridDim.x * blockDim.x) {
-        const zc v = live ? w.vg[(size_t)j * np + c] : make_double2(0.0, 0.0);
-        double *vr = vh + (size_t)r * 2 * np + 2 * c;
-        vr[0] = odd ? -v.y : v.x;
-        vr[1] = odd ? v.x : v.y;
-    }
-}
-
 // BT[i][j] = A[j][i] for i, j < n (zero elsewhere up to np).
 __global__ void k_zload_t(const zc *a, zc *bt, int n, int np) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
@@ -277,10 +259,8 @@ using namespace dsu;
 
 struct dsu_zwalker {
     int n = 0, np = 0, K = 0, kp = 0, policy = 0;
-    // real embedding of the stale rows for the matrix-core rank-k update
-    // (k_zembed_v), for delays whose embedded width 2k is at most 256
-    double *vh = nullptr;
-    int kp2 = 0;
+    // scratch of the matrix-core flush (real embedding, for delays with 2k <= 256)
+    double *flush_y = nullptr, *flush_w = nullptr;
     int flush_mode = DSU_FLUSH_AUTO;
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -309,7 +289,7 @@ static void zwalker_free(dsu_zwalker *w) {
     for (void *p : {(void *)w->wd.bt, (void *)w->wd.u, (void *)w->wd.vg, (void *)w->wd.a, w->la.phi,
                     (void *)w->wd.cinv, w->la.cinvt, w->la.part, w->la.t, w->la.b, w->la.ratio, (void *)w->wd.idx,
                     (void *)w->la.counter, (void *)w->wd.w, (void *)w->wd.fcol, (void *)w->wd.piv,
-                    (void *)w->wd.stat, (void *)w->wd.status, (void *)w->inv_tmp, (void *)w->vh})
+                    (void *)w->wd.stat, (void *)w->wd.status, (void *)w->inv_tmp, (void *)w->flush_y, (void *)w->flush_w})
         dfree(p);
     if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
@@ -342,22 +322,20 @@ static int zwalker_recompute(dsu_zwalker *w, double *logabs, double *phase) {
 }
 
 static int zwalker_flush(dsu_zwalker *w) {
-    const int k = w->k, np = w->np, kp = w->kp;
+    const int k = w->k, np = w->np;
     if (k > 0) {
-        // W = (BT U^T - E) C^{-T}, row by row (vector ALUs); then BT -= W Vg:
         // on the matrix cores through the real embedding when its width fits
-        // (2k <= 256), else as a complex product on the vector ALUs
-        hipLaunchKernelGGL(k_zflush_w, dim3(np / 4), dim3(kThreads), 0, w->stream, w->wd, np, k);
-        HIPCHK(hipGetLastError());
-        const bool mfma = w->vh && 2 * k <= w->kp2 &&
-                          (w->flush_mode == DSU_FLUSH_MFMA || (w->flush_mode == DSU_FLUSH_AUTO && k > 2));
+        // (2k <= 256), else W row by row and the complex product on the vector ALUs
+        // (us, vector / matrix: k = 1 16 / 14 at n = 64, 30 / 27 at 1024; k = 16 52 / 26 at 500)
+        const bool mfma = 2 * k <= 256 && w->flush_mode != DSU_FLUSH_VALU;
         if (mfma) {
-            const int bx = np >= 256 ? np / 256 : 1;
-            hipLaunchKernelGGL(k_zembed_v, dim3(bx, kpad(2 * k)), dim3(256), 0, w->stream, w->wd, w->vh, np, k);
-            HIPCHK(hipGetLastError());
-            HIPCHK(launch_gemm_sub(reinterpret_cast<const double *>(w->wd.w), 2 * w->wd.ldc, 2 * k, w->vh, 2 * np,
-                                   reinterpret_cast<double *>(w->wd.bt), 2 * np, np, 2 * np, w->stream));
+            const FlushArgs<double> fa{(double *)w->wd.bt, (const double *)w->wd.u, (const double *)w->wd.vg,
+                                       (const double *)w->wd.cinv, (const double *)w->la.cinvt, w->wd.idx, w->wd.ldc,
+                                       w->flush_y, w->flush_w};
+            HIPCHK((launch_flush_mfma<double, 2>(fa, np, k, w->stream)));
         } else {
+            hipLaunchKernelGGL(k_zflush_w, dim3(np / 4), dim3(kThreads), 0, w->stream, w->wd, np, k);
+            HIPCHK(hipGetLastError());
             HIPCHK((zgemm<false, true>(w->wd.w, w->wd.ldc, w->wd.vg, np, w->wd.bt, np, np, np, k, w->stream)));
         }
     }
@@ -427,9 +405,9 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     TRY(dalloc(&w->wd.piv, np));
     TRY(dalloc(&w->wd.stat, 3));
     TRY(dalloc(&w->wd.status, 1));
-    // embedded stale rows: 2 kp slots (capped at 256, the widest matrix-core update)
-    w->kp2 = std::min<int>(256, kpad(std::min<int>(2 * (int)kp, 256)));
-    TRY(dalloc(&w->vh, (size_t)w->kp2 * 2 * np));
+    const int kp2 = std::min<int>(256, 2 * (int)kp);  // padded real slots
+    TRY(dalloc(&w->flush_y, flush_scratch_elems<double>(w->np, 2 * w->np, kp2)));
+    TRY(dalloc(&w->flush_w, np * kp2));
     w->wd.ldc = w->la.ldc = (int)kp + 1;
     // coherent: the host watches the result words while the kernel runs
     if (hipHostMalloc((void **)&w->words_h, kLaWords * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=

@@ -85,3 +85,39 @@ def test_inverse_of_signed_permutation_is_exact(n):
         assert np.array_equal(w.inverse(), a.T)
         sg, ld = w.logdet()
     assert ld == 0.0 and sg == round(np.linalg.slogdet(a)[0])
+
+
+# The flush's launches: 16, 32 .. slots (one or two tiles), 64-row blocks with
+# and without padding, FP64 columns in 1, 2, 4 or 8 parts, k at and beside the
+# tile widths; the vector-ALU kernel as the other path.  Complex: 2 k real
+# slots, and k = 130 beyond the embedding's width.
+@pytest.mark.parametrize("n,k,kind", [
+    (5, 5, "fp64"), (64, 16, "fp64"), (65, 17, "fp64"), (300, 33, "fp64"), (1100, 64, "fp64"), (2100, 7, "fp64"),
+    (260, 129, "fp64"), (200, 33, "fp32"), (700, 128, "fp32"), (3, 3, "complex"), (70, 8, "complex"),
+    (70, 9, "complex"), (300, 65, "complex"), (600, 32, "complex"), (140, 130, "complex")])
+def test_flush_edges(n, k, kind):
+    require_gpu()
+    cplx, f32 = kind == "complex", kind == "fp32"
+    a = well_conditioned(51 + n, n, cplx)
+    noise = inputs.rows(7, k, n) + (1j * inputs.rows(8, k, n) if cplx else 0.0)
+    order = [(5 * m + 1) % n if n % 5 else m for m in range(k)]
+    rows = [0.9 * a[e] + 0.1 * noise[m] / np.sqrt(n) for m, e in enumerate(order)]
+    b = a.copy()
+    b[order] = rows
+    K, got = min(256, k + 1), []
+    for mode in (dsu.FLUSH_MFMA, dsu.FLUSH_VALU):
+        if mode == dsu.FLUSH_VALU and K > 64 and not cplx:
+            continue  # refused: the vector-ALU kernel holds up to 64 slots
+        with (dsu.ZWalker(a, K) if cplx else
+              dsu.Walker(a, K, precision=dsu.FP32_MIXED if f32 else dsu.FP64)) as w:
+            w.set_flush_kernel(mode)
+            for e, row in zip(order, rows):
+                w.propose(e, row)
+                w.accept()
+            assert w.pending() == k
+            w.flush()
+            got.append(w.inverse())
+    exact = np.linalg.inv(b)
+    tol = 64.0 * np.sqrt(n) * 2.0**-24 if f32 else 1e-10
+    for inv in got:
+        assert np.abs(inv - exact).max() <= tol
