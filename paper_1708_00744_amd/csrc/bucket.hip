@@ -15,7 +15,6 @@
 #include "bucket.hpp"
 
 #include <algorithm>
-#include <cstddef>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -612,6 +611,11 @@ struct dsu_batch {
     Bucket bk;
     int walkers = 0, spins = 1, ndet = 0, recompute_every = 0;
     char *store = nullptr;
+    // positions and running states of all determinants, each one array: one
+    // copy moves them all (a copy per determinant cost 14 us each: 7.2 of the
+    // 13.1 ms of a sweep of 512 determinants of n = 512 with its statistics)
+    double *pos = nullptr;
+    DetState *states = nullptr;
     double *trace_r = nullptr;
     uint8_t *trace_a = nullptr;
     long long trace_cap = 0;
@@ -637,19 +641,32 @@ static int batch_recompute_some(dsu_batch *b, const std::vector<int> &which) {
     return DSU_OK;
 }
 
+static int batch_read_states(dsu_batch *b, std::vector<DetState> *st) {
+    st->resize(b->ndet);
+    HIPCHK(hipMemcpyAsync(st->data(), b->states, sizeof(DetState) * b->ndet, hipMemcpyDeviceToHost, b->bk.stream));
+    HIPCHK(hipStreamSynchronize(b->bk.stream));
+    return DSU_OK;
+}
+
+static int batch_write_states(dsu_batch *b, const std::vector<DetState> &st) {
+    HIPCHK(hipMemcpyAsync(b->states, st.data(), sizeof(DetState) * b->ndet, hipMemcpyHostToDevice, b->bk.stream));
+    HIPCHK(hipStreamSynchronize(b->bk.stream));
+    return DSU_OK;
+}
+
 static int batch_read_bad(dsu_batch *b, std::vector<int> *bad) {
+    std::vector<DetState> st;
+    CHK(batch_read_states(b, &st));
     bad->resize(b->ndet);
-    for (int i = 0; i < b->ndet; ++i) {
-        DetState st;
-        HIPCHK(hipMemcpy(&st, b->bk.dets[i].st, sizeof(st), hipMemcpyDeviceToHost));
-        (*bad)[i] = st.bad;
-    }
+    for (int i = 0; i < b->ndet; ++i) (*bad)[i] = st[i].bad;
     return DSU_OK;
 }
 
 static void batch_free(dsu_batch *b) {
     b->bk.release();
     dfree(b->store);
+    dfree(b->pos);
+    dfree(b->states);
     dfree(b->trace_r);
     dfree(b->trace_a);
     dfree(b->inv_tmp);
@@ -695,13 +712,18 @@ extern "C" int dsu_batch_create(int32_t walkers, int32_t n, int32_t spins, int32
     int group = (int)std::min<size_t>((size_t)b->ndet, std::max<size_t>(1, ((size_t)16 << 30) / per));
     int rc = b->bk.init(sh, k_delay, box_L, hip_stream, group);
     if (rc == DSU_OK) rc = dev_alloc((void **)&b->store, sh.det_bytes() * b->ndet);
+    if (rc == DSU_OK) rc = dalloc(&b->pos, (size_t)n * 3 * b->ndet);
+    if (rc == DSU_OK) rc = dalloc(&b->states, (size_t)b->ndet);
+    if (rc == DSU_OK && hipMemcpy(b->pos, positions_host, sizeof(double) * n * 3 * b->ndet, hipMemcpyHostToDevice) !=
+                            hipSuccess)
+        rc = fail(DSU_EDEVICE, "upload of walker state failed");
+    if (rc == DSU_OK) rc = batch_write_states(b, std::vector<DetState>(b->ndet, DetState{0.0, 1, 0, 0, 0, 0}));
     if (rc != DSU_OK) {
         batch_free(b);
         delete b;
         return rc;
     }
     std::vector<DetSlot> slots(b->ndet);
-    std::vector<DetState> st(b->ndet);
     for (int i = 0; i < b->ndet; ++i) {
         const int w = i / spins;
         DetSlot &s = slots[i];
@@ -710,14 +732,8 @@ extern "C" int dsu_batch_create(int32_t walkers, int32_t n, int32_t spins, int32
         s.wid = walker_ids[w];
         s.sigma = sigma[w];
         s.spin = i % spins;
-        st[i] = DetState{0.0, 1, 0, 0, 0, 0};
-        if (hipMemcpy(s.pos, positions_host + (size_t)n * 3 * i, sizeof(double) * n * 3, hipMemcpyHostToDevice) !=
-                hipSuccess ||
-            hipMemcpy(s.st, &st[i], sizeof(DetState), hipMemcpyHostToDevice) != hipSuccess) {
-            batch_free(b);
-            delete b;
-            return fail(DSU_EDEVICE, "upload of walker state failed");
-        }
+        s.pos = b->pos + (size_t)n * 3 * i;
+        s.st = b->states + i;
     }
     rc = b->bk.set_dets(slots);
     if (rc == DSU_OK) rc = b->bk.recompute(all_indices(b->ndet), nullptr);
@@ -908,14 +924,13 @@ extern "C" int dsu_batch_set_delay(dsu_batch *b, int32_t k_delay) {
 
 extern "C" int dsu_batch_stats(dsu_batch *b, double *logdet, int32_t *sign, int64_t *accepted, int64_t *sweeps_done) {
     if (!b) return fail(DSU_EINVAL, "batch is NULL");
-    HIPCHK(hipStreamSynchronize(b->bk.stream));
+    std::vector<DetState> st;
+    CHK(batch_read_states(b, &st));
     for (int i = 0; i < b->ndet; ++i) {
-        DetState st;
-        HIPCHK(hipMemcpy(&st, b->bk.dets[i].st, sizeof(st), hipMemcpyDeviceToHost));
-        if (logdet) logdet[i] = st.logdet;
-        if (sign) sign[i] = st.sign;
-        if (accepted) accepted[i] = st.accepted;
-        if (sweeps_done) sweeps_done[i] = st.sweep;
+        if (logdet) logdet[i] = st[i].logdet;
+        if (sign) sign[i] = st[i].sign;
+        if (accepted) accepted[i] = st[i].accepted;
+        if (sweeps_done) sweeps_done[i] = st[i].sweep;
     }
     return DSU_OK;
 }
@@ -923,13 +938,10 @@ extern "C" int dsu_batch_stats(dsu_batch *b, double *logdet, int32_t *sign, int6
 extern "C" int dsu_batch_set_sweep(dsu_batch *b, int64_t sweeps_done) {
     if (!b) return fail(DSU_EINVAL, "batch is NULL");
     if (sweeps_done < 0) return fail(DSU_EINVAL, "sweeps_done %lld < 0", (long long)sweeps_done);
-    HIPCHK(hipStreamSynchronize(b->bk.stream));
-    for (int i = 0; i < b->ndet; ++i) {
-        const long long v = sweeps_done;
-        HIPCHK(hipMemcpy(reinterpret_cast<char *>(b->bk.dets[i].st) + offsetof(DetState, sweep), &v, sizeof(v),
-                         hipMemcpyHostToDevice));
-    }
-    return DSU_OK;
+    std::vector<DetState> st;
+    CHK(batch_read_states(b, &st));
+    for (DetState &x : st) x.sweep = sweeps_done;
+    return batch_write_states(b, st);
 }
 
 extern "C" int dsu_batch_get_positions(dsu_batch *b, int32_t det, double *out_host) {
@@ -973,11 +985,11 @@ extern "C" int dsu_batch_set_trace(dsu_batch *b, int32_t sweeps) {
         slots[i].trace_r = b->trace_r ? b->trace_r + (size_t)b->trace_cap * i : nullptr;
         slots[i].trace_a = b->trace_a ? b->trace_a + (size_t)b->trace_cap * i : nullptr;
         slots[i].trace_cap = b->trace_r ? b->trace_cap : 0;
-        DetState st;
-        HIPCHK(hipMemcpy(&st, slots[i].st, sizeof(st), hipMemcpyDeviceToHost));
-        st.trace_pos = 0;
-        HIPCHK(hipMemcpy(slots[i].st, &st, sizeof(st), hipMemcpyHostToDevice));
     }
+    std::vector<DetState> st;
+    CHK(batch_read_states(b, &st));
+    for (DetState &x : st) x.trace_pos = 0;
+    CHK(batch_write_states(b, st));
     return b->bk.set_dets(slots);
 }
 
