@@ -85,7 +85,14 @@ static void walker_free(dsu_walker *w) {
     if (w->own_stream && w->stream) (void)hipStreamDestroy(w->stream);
 }
 
-static int walker_recompute(dsu_walker *w, double *fresh_logdet, int *fresh_sign) {
+// Fresh inverse of the n x n matrix `slater_host` (which becomes A) or of A.
+static int walker_recompute(dsu_walker *w, const double *slater_host, double *fresh_logdet, int *fresh_sign) {
+    if (slater_host) {
+        // up in one piece into a buffer the inversion overwrites: a pitched
+        // copy of pageable rows goes row by row
+        HIPCHK(hipMemcpyAsync(w->gj.m2, slater_host, sizeof(double) * w->n * w->n, hipMemcpyHostToDevice, w->stream));
+        HIPCHK(launch_pad_rows(w->gj.m2, (double *)w->wd.a, w->n, w->np, w->stream));
+    }
     HIPCHK(launch_load_transpose(w->a_ptr, w->gj.mptr, 1, w->n, w->np, w->np, w->stream));
     const GjDesc *res = nullptr;
     HIPCHK(w->gj.invert(1, w->n, w->stream, &res));
@@ -182,10 +189,7 @@ extern "C" int dsu_walker_create(int32_t n, int32_t k_delay, int32_t precision, 
                                                           : flush_scratch_elems<float>(w->np, w->np, w->kp))));
     TRY(dev_alloc(&w->flush_w, np * kp * s));
     TRY(w->gj.alloc(1, w->np, n));
-    if (hipMemcpy2D(w->wd.a, np * sizeof(double), slater_host, n * sizeof(double), n * sizeof(double), n,
-                    hipMemcpyHostToDevice) != hipSuccess)
-        TRY(fail(DSU_EDEVICE, "matrix upload failed"));
-    TRY(walker_recompute(w, &w->logdet, &w->sign));
+    TRY(walker_recompute(w, slater_host, &w->logdet, &w->sign));
     w->idx.assign(w->kp, -1);
 #undef TRY
     *out = w;
@@ -359,12 +363,9 @@ static int walker_md_refresh(dsu_walker *w);
 extern "C" int dsu_recompute_inverse(dsu_walker *w, const double *slater_host_or_null, double *logdet_out,
                                      int32_t *sign_out, double *drift_out) {
     if (!w) return fail(DSU_EINVAL, "walker is NULL");
-    if (slater_host_or_null)
-        HIPCHK(hipMemcpy2DAsync(w->wd.a, w->np * sizeof(double), slater_host_or_null, w->n * sizeof(double),
-                                w->n * sizeof(double), w->n, hipMemcpyHostToDevice, w->stream));
     double ld;
     int sg;
-    CHK(walker_recompute(w, &ld, &sg));
+    CHK(walker_recompute(w, slater_host_or_null, &ld, &sg));
     if (w->md_on) {
         if (slater_host_or_null) {
             walker_md_free(w);  // the virtual rows belong to the old configuration

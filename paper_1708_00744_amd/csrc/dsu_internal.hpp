@@ -170,6 +170,8 @@ hipError_t launch_cast_perm(const GjDesc *gj_dev, T *const *bt_dev, int ndesc, i
 // M = A^T (A row-major n x n, padded with identity to np).
 hipError_t launch_load_transpose(const double *const *a_dev, double *const *m_dev, int ndesc, int n, int np,
                                  int lda, hipStream_t s);
+// a = in, rows of n to rows of np (a's padding is not written).
+hipError_t launch_pad_rows(const double *in, double *a, int n, int np, hipStream_t s);
 // M = A^T with A built from plane waves at the positions.
 hipError_t launch_build_pw_transpose(const double *const *pos_dev, double *const *m_dev, int ndesc, int n,
                                      int np, const int4 *kvec, double twopi_over_l, hipStream_t s);

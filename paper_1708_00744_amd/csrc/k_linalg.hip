@@ -701,42 +701,6 @@ __global__ __launch_bounds__(kThreads) void k_gj_gather(const GjDesc *__restrict
         if (wave + 4 * q < w) P[(size_t)(wave + 4 * q) * np] = t[lane][wave + 4 * q];
 }
 
-// Lane exchanges of a double within the vector unit (DPP).  dpp_f64: every
-// lane of the pattern has a source; dpp_old_f64: lanes outside the rows in
-// ROWS keep their own value.
-template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_old_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), CTRL, ROWS, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_f64(double v, int l) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                            __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-// Lane L of each row of 16 lanes to the whole row.
-template <int L> __device__ __forceinline__ double row_bcast_f64(double v) {
-    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + L, 0xf, 0xf, true);
-}
-// Maximum over groups of 4 or 8 lanes (every lane gets it).
-template <int N> __device__ __forceinline__ double group_max(double v) {
-    v = fmax(v, dpp_f64<0xB1>(v));                           // lane ^ 1
-    v = fmax(v, dpp_f64<0x4E>(v));                           // lane ^ 2
-    if constexpr (N == 8) v = fmax(v, dpp_f64<0x141>(v));    // mirrored in eight lanes
-    return v;
-}
-// Maximum over the wave, the same for every lane.
-__device__ __forceinline__ double wave_max(double v) {
-    v = group_max<8>(v);
-    v = fmax(v, dpp_f64<0x140>(v));           // mirrored in sixteen lanes
-    v = fmax(v, dpp_old_f64<0x142, 0xa>(v));  // lane 15 of a row of 16 to the next row
-    v = fmax(v, dpp_old_f64<0x143, 0xc>(v));  // lane 31 to lanes 32 .. 63
-    return lane_f64(v, 63);
-}
 // Of the lanes in `mask` (not empty) the one that holds the smallest idx.
 __device__ __forceinline__ int lowest_lane(unsigned long long mask, int idx) {
     int l = __builtin_ctzll(mask);
@@ -1388,6 +1352,18 @@ __global__ __launch_bounds__(kThreads) void k_load_transpose(const double *const
 hipError_t launch_load_transpose(const double *const *a_dev, double *const *m_dev, int ndesc, int n, int np, int lda,
                                  hipStream_t s) {
     hipLaunchKernelGGL(k_load_transpose, dim3(np / 32, np / 32, ndesc), dim3(kThreads), 0, s, a_dev, m_dev, n, np, lda);
+    return hipGetLastError();
+}
+
+// a[i][j] = in[i][j], rows of n to rows of np.
+__global__ __launch_bounds__(kThreads) void k_pad_rows(const double *__restrict__ in, double *__restrict__ a, int n,
+                                                       int np) {
+    const int j = blockIdx.x * kThreads + threadIdx.x, i = blockIdx.y;
+    if (j < n) a[(size_t)i * np + j] = in[(size_t)i * n + j];
+}
+
+hipError_t launch_pad_rows(const double *in, double *a, int n, int np, hipStream_t s) {
+    hipLaunchKernelGGL(k_pad_rows, dim3((n + kThreads - 1) / kThreads, n), dim3(kThreads), 0, s, in, a, n, np);
     return hipGetLastError();
 }
 

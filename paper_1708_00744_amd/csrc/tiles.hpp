@@ -27,6 +27,43 @@ template <> struct Vec16<double> { typedef double type __attribute__((ext_vector
 #define DSU_GLOBAL __attribute__((address_space(1)))
 template <typename T> __device__ __forceinline__ DSU_GLOBAL T *gmem(T *p) { return (DSU_GLOBAL T *)p; }
 
+// Lane exchanges of a double within the vector unit (DPP).  dpp_f64: every
+// lane of the pattern has a source; dpp_old_f64: lanes outside the rows in
+// ROWS keep their own value.
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_old_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// Lane L of each row of 16 lanes to the whole row.
+template <int L> __device__ __forceinline__ double row_bcast_f64(double v) {
+    return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + L, 0xf, 0xf, true);
+}
+// Maximum over groups of 4 or 8 lanes (every lane gets it).
+template <int N> __device__ __forceinline__ double group_max(double v) {
+    v = fmax(v, dpp_f64<0xB1>(v));                           // lane ^ 1
+    v = fmax(v, dpp_f64<0x4E>(v));                           // lane ^ 2
+    if constexpr (N == 8) v = fmax(v, dpp_f64<0x141>(v));    // mirrored in eight lanes
+    return v;
+}
+// Maximum over the wave, the same for every lane.
+__device__ __forceinline__ double wave_max(double v) {
+    v = group_max<8>(v);
+    v = fmax(v, dpp_f64<0x140>(v));           // mirrored in sixteen lanes
+    v = fmax(v, dpp_old_f64<0x142, 0xa>(v));  // lane 15 of a row of 16 to the next row
+    v = fmax(v, dpp_old_f64<0x143, 0xc>(v));  // lane 31 to lanes 32 .. 63
+    return lane_f64(v, 63);
+}
+
 // The hardware hands consecutive workgroups to the 8 XCDs in turn; renumber
 // them so that each XCD (own L2) works on a contiguous range of logical blocks,
 // i.e. on the same determinant's U and Vg.

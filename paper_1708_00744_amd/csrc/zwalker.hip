@@ -40,10 +40,12 @@ struct ZWalkerDev {
     zc *cinv;          // kp x (kp + 1): C_k^{-1} in pending order
     int *idx;          // kp pending electrons
     zc *w;             // np x (kp + 1): flush scratch W
-    zc *fcol;          // np: Gauss-Jordan multipliers
-    int *piv;          // np: Gauss-Jordan row interchanges
-    double *stat;      // log|det|, arg det, largest pivot modulus
-    int *status;       // 1 if a pivot is singular to working precision
+    zc *work;          // np x np: the inversion's other buffer; also dsu_zget_inverse's output
+    zc *panel;         // np x 16: a group's factored columns
+    zc *pval;          // np: pivots
+    int *slot;         // np: the pivot a row was taken for
+    int *piv;          // np: the row taken for a pivot
+    double *stat;      // log|det|, arg det without the row order's sign, 1 if singular to working precision
     int ldc;           // kp + 1
 };
 
@@ -148,103 +150,307 @@ __global__ __launch_bounds__(kThreads) void k_zflush_w(ZWalkerDev w, int np, int
     }
 }
 
-// BT[i][j] = A[j][i] for i, j < n (zero elsewhere up to np).
-__global__ void k_zload_t(const zc *a, zc *bt, int n, int np) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-    if (j >= np) return;
-    bt[(size_t)i * np + j] = (i < n && j < n) ? a[(size_t)j * np + i] : make_double2(0.0, 0.0);
+// ---------------------------------------------------------------------------
+// Fresh inverse: in-place Gauss-Jordan on M = A^T with partial pivoting, WS
+// columns (a group) at a time.  A launch pair per column with the rows moved
+// in memory cost 12 us a column, the matrix's pitched upload 5 ms; now a launch
+// pair per group (33 + 6 us at n = 600) and one flat upload.  New matrix in,
+// inverse out at n = 600: 12.0 -> 2.1 ms.
+//  * k_zgj_group, one workgroup, thread t holds rows t + NT r of the group's
+//    columns in registers, so a pivot step is one exchange through LDS and one
+//    barrier;
+//  * k_zgj_update applies the group's rank-WS update to all other columns, from
+//    one buffer to another (the pivot rows it needs are those of the old one).
+// Rows are not interchanged: slot[i] names the pivot row i was taken for (-1:
+// none yet).  With row p_j taken for pivot j the result holds, in row p_i and
+// column j, element (i, p_j) of the inverse; k_zgj_gather puts it in place.
+// The pivot is the largest |re| + |im| (within sqrt(2) of the largest modulus,
+// without its square root or the overflow of squares).
+// ---------------------------------------------------------------------------
+
+// M[i][j] = A[j][i] for i, j < n (zero elsewhere up to np), through LDS; slots
+// cleared.  A: `in`, rows of ldi; where that is the caller's own n x n matrix
+// (ldi = n), also copied to a (rows of np; its padding is zero already).
+__global__ __launch_bounds__(kThreads) void k_zgj_load(const zc *in, int ldi, zc *a, zc *m, int *slot, int n, int np) {
+    __shared__ zc t[32][33];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+#pragma unroll
+    for (int q = 0; q < 32; q += 8) {
+        const int r = j0 + y + q, c = i0 + x;  // row r, column c of A
+        const bool on = r < n && c < n;
+        const zc v = on ? la_load(in + (size_t)r * ldi + c) : make_double2(0.0, 0.0);
+        t[y + q][x] = v;
+        if (in != a && on) a[(size_t)r * np + c] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 32; q += 8) m[(size_t)(i0 + y + q) * np + j0 + x] = t[x][y + q];
+    if (blockIdx.x == 0 && threadIdx.x < 32) slot[i0 + threadIdx.x] = -1;
 }
 
-// One Gauss-Jordan step on column kk (one workgroup): partial pivoting by
-// modulus (lowest row on ties), row interchange, pivot row scaled by 1/p with
-// 1/p left in the pivot position, multipliers of the other rows saved and
-// their column-kk entries cleared; log|p|, arg p (+ pi per interchange) and
-// the largest pivot modulus accumulated; a pivot at or below n 2^-52 times the
-// largest so far marks the matrix singular.
-__global__ __launch_bounds__(1024) void k_zgj_pivot(ZWalkerDev w, int ld, int n, int kk) {
-    __shared__ double s_v[1024];
-    __shared__ int s_i[1024];
-    const int tid = threadIdx.x;
-    zc *m = w.bt;
-    // a row index in [kk, n) is always chosen (NaN moduli lose every
-    // comparison, so a column of NaN keeps row kk and is flagged below)
-    double best = -1.0;
-    int bi = kk;
-    for (int i = kk + tid; i < n; i += 1024) {
-        const zc v = m[(size_t)i * ld + kk];
-        const double a = hypot(v.x, v.y);
-        if (a > best) { best = a; bi = i; }
+// Pivots k0 .. k0 + w - 1 on the group's columns; factored columns to panel
+// (np x WS), pivot values to pval, the rows taken to piv and slot.  A pivot step
+// is bound by its serial chain (search, exchange, reciprocal) and by 4 WS RPT
+// FP64 multiply-adds a thread, on one compute unit, so:
+//  * WS RPT = 32 complex values a thread on as few waves as hold the rows: what
+//    a wave does once a step serves RPT rows of each lane;
+//  * the pivot row sits one column a lane (in each 16 lanes) and enters the
+//    multiply-adds as row broadcasts;
+//  * the columns rotate by one a step (the multiply-adds write one register to
+//    the left), so the pivot column is always the first, every index is fixed
+//    and the body of one step stays in the instruction cache.
+template <int WS, int RPT>
+__global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc *__restrict__ panel, int *slot,
+                                                   int *piv, zc *pval, int np, int n, int k0, int w) {
+    __shared__ zc s_row[WS];
+    __shared__ double s_key[8];
+    __shared__ int s_at[8];
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+    double ax[RPT][WS], ay[RPT][WS];  // re, im
+    int mine[RPT];                    // the pivot each row was taken for; -2: no row
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const int i = tid + nt * r;
+        const bool in = i < n;
+        mine[r] = in ? slot[i] : -2;
+        const zc *src = m + (size_t)(in ? i : 0) * np + k0;
+#pragma unroll
+        for (int c = 0; c < WS; ++c) {
+            const zc v = la_load(src + c);
+            ax[r][c] = in ? v.x : 0.0;
+            ay[r][c] = in ? v.y : 0.0;
+        }
     }
-    s_v[tid] = best;
-    s_i[tid] = bi;
-    __syncthreads();
-    for (int o = 512; o > 0; o >>= 1) {
-        if (tid < o) {
-            const double a = s_v[tid + o];
-            const int ia = s_i[tid + o];
-            if (a > s_v[tid] || (a == s_v[tid] && ia < s_i[tid])) {
-                s_v[tid] = a;
-                s_i[tid] = ia;
+#pragma unroll 1
+    for (int s = 0; s < WS; ++s) {
+        double fx[RPT], fy[RPT];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            fx[r] = ax[r][0];
+            fy[r] = ay[r][0];
+        }
+        if (s >= w) {  // past the last column: only the rotation
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+#pragma unroll
+                for (int c = 1; c < WS; ++c) {
+                    ax[r][c - 1] = ax[r][c];
+                    ay[r][c - 1] = ay[r][c];
+                }
+                ax[r][WS - 1] = fx[r];
+                ay[r][WS - 1] = fy[r];
+            }
+            continue;
+        }
+        // this wave's candidate (a NaN ranks below every number, a row already taken below NaN)
+        double best = -1.0;
+        int bi = tid;
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            const double v = fabs(fx[r]) + fabs(fy[r]), key = mine[r] != -1 ? -1.0 : (v == v ? v : -0.5);
+            if (key > best) {
+                best = key;
+                bi = tid + nt * r;
             }
         }
+        const double top = wave_max(best);
+        if (lane == __builtin_ctzll(__ballot(best == top))) {
+            s_key[wave] = top;
+            s_at[wave] = bi;
+        }
         __syncthreads();
-    }
-    const int p = s_i[0];
-    const double pabs = s_v[0];
-    if (p != kk)
-        for (int j = tid; j < n; j += 1024) {
-            const zc t = m[(size_t)kk * ld + j];
-            m[(size_t)kk * ld + j] = m[(size_t)p * ld + j];
-            m[(size_t)p * ld + j] = t;
+        // every wave picks the winner (same values, same result)
+        const double key = (lane & 7) < nw ? s_key[lane & 7] : -1.0;
+        const int at = s_at[lane & 7];
+        const double all = lane_f64(group_max<8>(key), 0);
+        const int p = __builtin_amdgcn_readlane(at, __builtin_ctzll(__ballot(key == all)));
+        bool own[RPT];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            own[r] = p == tid + nt * r;
+            if (own[r])
+#pragma unroll
+                for (int c = 0; c < WS; ++c) s_row[c] = make_double2(ax[r][c], ay[r][c]);
         }
+        __syncthreads();
+        const zc rv = s_row[lane & (WS - 1)];
+        const double px = row_bcast_f64<0>(rv.x), py = row_bcast_f64<0>(rv.y);
+        const double d = 1.0 / (px * px + py * py), ix = px * d, iy = -py * d;
+        const double sx = __builtin_fma(rv.x, ix, -(rv.y * iy)), sy = __builtin_fma(rv.x, iy, rv.y * ix);
+        if (tid == 0) {
+            pval[k0 + s] = make_double2(px, py);
+            piv[k0 + s] = p;
+        }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+            if (own[r]) {  // the pivot row itself: scaled
+                mine[r] = k0 + s;
+                fx[r] = fy[r] = 0.0;
+#pragma unroll
+                for (int c = 1; c < WS; ++c) {
+                    const double x = ax[r][c], y = ay[r][c];
+                    ax[r][c] = __builtin_fma(x, ix, -(y * iy));
+                    ay[r][c] = __builtin_fma(x, iy, y * ix);
+                }
+            }
+        static_for(std::make_integer_sequence<int, WS - 1>{}, [&](auto c_c) __attribute__((always_inline)) {
+            constexpr int c = decltype(c_c)::value + 1;
+            const double qx = row_bcast_f64<c>(sx), qy = row_bcast_f64<c>(sy);
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
+                ax[r][c - 1] = __builtin_fma(-fx[r], qx, __builtin_fma(fy[r], qy, ax[r][c]));
+                ay[r][c - 1] = __builtin_fma(-fx[r], qy, __builtin_fma(-fy[r], qx, ay[r][c]));
+            }
+        });
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            ax[r][WS - 1] = own[r] ? ix : __builtin_fma(fy[r], iy, -(fx[r] * ix));
+            ay[r][WS - 1] = own[r] ? iy : -__builtin_fma(fx[r], iy, fy[r] * ix);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const int i = tid + nt * r;
+        if (i >= n) continue;
+        if (mine[r] >= k0) slot[i] = mine[r];
+        zc *dst = panel + (size_t)i * WS;
+#pragma unroll
+        for (int c = 0; c < WS; ++c) dst[c] = make_double2(ax[r][c], ay[r][c]);
+    }
+}
+
+// dst[i][c] = (row i taken in this group ? 0 : src[i][c]) + sum_j panel[i][j] src[p_j][c]
+// outside the group's columns, panel[i][c - k0] there.  A workgroup: 16 rows x 64
+// columns, four rows a thread; all loads are issued before the products, whose
+// operands are read from LDS (held in registers they spilled: 27 us a launch at
+// n = 600 against 6).
+template <int WS>
+__global__ __launch_bounds__(kThreads) void k_zgj_update(const zc *__restrict__ src, zc *__restrict__ dst,
+                                                         const zc *__restrict__ panel, const int *__restrict__ slot,
+                                                         const int *__restrict__ piv, int np, int n, int k0, int w) {
+    __shared__ zc s_t[16][WS], s_q[WS][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = blockIdx.x * 64 + lane, i0 = blockIdx.y * 16;
+    constexpr int NQ = (WS + 3) / 4;
+    zc q[NQ], o[4];
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) {
+        const int j = wave + 4 * h;
+        q[h] = la_load(src + (size_t)piv[k0 + (j < w ? j : 0)] * np + c);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wave + 4 * r;
+        o[r] = i < n && slot[i] < k0 ? la_load(src + (size_t)i * np + c) : make_double2(0.0, 0.0);
+    }
+    for (int v = tid; v < 16 * WS; v += kThreads)
+        s_t[v / WS][v % WS] =
+            i0 + v / WS < n && v % WS < w ? la_load(panel + (size_t)i0 * WS + v) : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int h = 0; h < NQ; ++h)
+        if (wave + 4 * h < WS) s_q[wave + 4 * h][lane] = q[h];
     __syncthreads();
-    const zc pv = m[(size_t)kk * ld + kk];
+#pragma unroll 4
+    for (int j = 0; j < w; ++j) {
+        const zc x = s_q[j][lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = zfma(s_t[wave + 4 * r][j], x, o[r]);
+    }
+    const bool own = c >= k0 && c < k0 + w;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + wave + 4 * r;
+        if (own) o[r] = s_t[wave + 4 * r][c - k0];
+        if (i < n) dst[(size_t)i * np + c] = o[r];
+    }
+}
+
+// BT[i][c] = M[p_i][slot c] for i, c < n, zero elsewhere up to np.
+__global__ __launch_bounds__(kThreads) void k_zgj_gather(const zc *__restrict__ m, zc *__restrict__ bt,
+                                                         const int *__restrict__ slot, const int *__restrict__ piv,
+                                                         int n, int np) {
+    const int c = blockIdx.x * kThreads + threadIdx.x, i = blockIdx.y;
+    if (c >= np) return;
+    bt[(size_t)i * np + c] = i < n && c < n ? la_load(m + (size_t)piv[i] * np + slot[c]) : make_double2(0.0, 0.0);
+}
+
+// stat[0] = sum log|p|, stat[1] = sum arg p; stat[2] = 1 if a pivot's modulus
+// is at or below n 2^-52 times the largest up to it (or no number).  One
+// workgroup, thread t the pivots t cnt .. + cnt.
+__global__ __launch_bounds__(1024) void k_zgj_stat(const zc *__restrict__ pval, double *stat, int n) {
+    __shared__ double s_mx[2][1024];
+    __shared__ double s_sum[2][16];
+    __shared__ int s_bad;
+    const int tid = threadIdx.x, cnt = (n + 1023) / 1024, q0 = tid * cnt, q1 = q0 + cnt < n ? q0 + cnt : n;
+    double ld = 0.0, ph = 0.0, mx = 0.0;
+    if (tid == 0) s_bad = 0;
+    for (int q = q0; q < q1; ++q) {
+        const zc p = pval[q];
+        const double v = hypot(p.x, p.y);
+        ld += log(v);
+        ph += atan2(p.y, p.x);
+        mx = fmax(mx, v);
+    }
+    s_mx[0][tid] = mx;
+    int b = 0;
+    for (int o = 1; o < 1024; o *= 2, b ^= 1) {  // inclusive prefix maxima
+        __syncthreads();
+        s_mx[b ^ 1][tid] = tid >= o ? fmax(s_mx[b][tid], s_mx[b][tid - o]) : s_mx[b][tid];
+    }
+    __syncthreads();
+    mx = tid > 0 ? s_mx[b][tid - 1] : 0.0;
+    for (int q = q0; q < q1; ++q) {
+        const double v = hypot(pval[q].x, pval[q].y);
+        mx = fmax(mx, v);
+        if (!(v > (double)n * 0x1p-52 * mx)) s_bad = 1;
+    }
+    ld = la_wave_sum(ld);
+    ph = la_wave_sum(ph);
+    if ((tid & 63) == 0) {
+        s_sum[0][tid >> 6] = ld;
+        s_sum[1][tid >> 6] = ph;
+    }
+    __syncthreads();
     if (tid == 0) {
-        w.piv[kk] = p;
-        const double mx = fmax(w.stat[2], pabs);
-        if (!(pabs > (double)n * 0x1p-52 * mx)) *w.status = 1;
-        w.stat[0] += log(pabs);
-        w.stat[1] += atan2(pv.y, pv.x) + (p != kk ? M_PI : 0.0);
-        w.stat[2] = mx;
-    }
-    __syncthreads();
-    const zc inv = zinv(pv);
-    for (int j = tid; j < n; j += 1024) {
-        zc *q = m + (size_t)kk * ld + j;
-        *q = j == kk ? inv : zmul(*q, inv);
-    }
-    for (int i = tid; i < n; i += 1024) {
-        if (i == kk) {
-            w.fcol[i] = make_double2(0.0, 0.0);
-        } else {
-            w.fcol[i] = m[(size_t)i * ld + kk];
-            m[(size_t)i * ld + kk] = make_double2(0.0, 0.0);
+        ld = ph = 0.0;
+        for (int q = 0; q < 16; ++q) {
+            ld += s_sum[0][q];
+            ph += s_sum[1][q];
         }
+        stat[0] = ld;
+        stat[1] = ph;
+        stat[2] = s_bad ? 1.0 : 0.0;
     }
 }
 
-// Rows i != kk: row_i -= f_i row_kk.
-__global__ void k_zgj_elim(ZWalkerDev w, int ld, int n, int kk) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-    if (j >= n || i == kk) return;
-    const zc f = w.fcol[i];
-    zc *q = w.bt + (size_t)i * ld + j;
-    *q = zsub(*q, zmul(f, w.bt[(size_t)kk * ld + j]));
-}
-
-// Undo the row interchanges on the inverse's columns, last interchange first.
-__global__ void k_zgj_unperm(ZWalkerDev w, int ld, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    zc *r = w.bt + (size_t)i * ld;
-    for (int kk = n - 1; kk >= 0; --kk) {
-        const int p = w.piv[kk];
-        if (p != kk) {
-            const zc t = r[kk];
-            r[kk] = r[p];
-            r[p] = t;
-        }
+// One inversion, of the n x n matrix `host` (which becomes A) or of A: M starts in the buffer from which an even or odd
+// number of updates ends in `work`, and is gathered from there into BT.
+template <int WS, int RPT>
+static hipError_t zgj_invert(const zc *host, zc *a, zc *bt, zc *work, zc *panel, int *slot, int *piv, zc *pval,
+                             double *stat, int n, int np, hipStream_t s) {
+    const int groups = (n + WS - 1) / WS;
+    zc *src = groups % 2 ? bt : work, *dst = groups % 2 ? work : bt;
+    if (host) {  // up in one piece (a pitched copy of pageable rows goes row by row: 3 ms at n = 600)
+        const hipError_t e = hipMemcpyAsync(dst, host, sizeof(zc) * n * n, hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return e;
     }
+    hipLaunchKernelGGL(k_zgj_load, dim3(np / 32, np / 32), dim3(kThreads), 0, s, (const zc *)(host ? dst : a),
+                       host ? n : np, a, src, slot, n, np);
+    const int nt = round_up((n + RPT - 1) / RPT, 64);
+    for (int k0 = 0; k0 < n; k0 += WS) {
+        const int w = n - k0 < WS ? n - k0 : WS;
+        hipLaunchKernelGGL((k_zgj_group<WS, RPT>), dim3(1), dim3(nt), 0, s, (const zc *)src, panel, slot, piv, pval, np,
+                           n, k0, w);
+        hipLaunchKernelGGL((k_zgj_update<WS>), dim3(np / 64, (n + 15) / 16), dim3(kThreads), 0, s, (const zc *)src, dst,
+                           (const zc *)panel, (const int *)slot, (const int *)piv, np, n, k0, w);
+        zc *t = src;
+        src = dst;
+        dst = t;
+    }
+    hipLaunchKernelGGL(k_zgj_gather, dim3((np + kThreads - 1) / kThreads, np), dim3(kThreads), 0, s, (const zc *)work, bt,
+                       (const int *)slot, (const int *)piv, n, np);
+    hipLaunchKernelGGL(k_zgj_stat, dim3(1), dim3(1024), 0, s, (const zc *)pval, stat, n);
+    return hipGetLastError();
 }
 
 // out[i][j] = BT[j][i] (A^{-1}, n x n).
@@ -269,7 +475,7 @@ struct dsu_zwalker {
     double *words_h = nullptr;              // pinned host words the look-ahead kernel writes R into
     double *row_stage = nullptr;            // mapped pinned host staging of a proposal row
     const double *row_stage_dev = nullptr;  // its device address
-    zc *inv_tmp = nullptr;
+    std::vector<int> piv_h;                 // host copy of the pivot rows
     int k = 0, slots = 0;
     std::vector<int> idx;
     bool has_prop = false;
@@ -288,8 +494,8 @@ static double wrap_phase(double p) {
 static void zwalker_free(dsu_zwalker *w) {
     for (void *p : {(void *)w->wd.bt, (void *)w->wd.u, (void *)w->wd.vg, (void *)w->wd.a, w->la.phi,
                     (void *)w->wd.cinv, w->la.cinvt, w->la.part, w->la.t, w->la.b, w->la.ratio, (void *)w->wd.idx,
-                    (void *)w->la.counter, (void *)w->wd.w, (void *)w->wd.fcol, (void *)w->wd.piv,
-                    (void *)w->wd.stat, (void *)w->wd.status, (void *)w->inv_tmp, (void *)w->flush_y, (void *)w->flush_w})
+                    (void *)w->la.counter, (void *)w->wd.w, (void *)w->wd.work, (void *)w->wd.panel,
+                    (void *)w->wd.pval, (void *)w->wd.slot, (void *)w->wd.piv, (void *)w->wd.stat, (void *)w->flush_y, (void *)w->flush_w})
         dfree(p);
     if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
@@ -297,27 +503,35 @@ static void zwalker_free(dsu_zwalker *w) {
 }
 
 // Fresh inverse from A: BT = (A^T)^{-1} by in-place Gauss-Jordan on A^T.
-static int zwalker_recompute(dsu_zwalker *w, double *logabs, double *phase) {
+static int zwalker_recompute(dsu_zwalker *w, const double *slater_host, double *logabs, double *phase) {
     const int n = w->n, np = w->np;
-    hipLaunchKernelGGL(k_zload_t, dim3((np + 255) / 256, np), dim3(256), 0, w->stream, (const zc *)w->wd.a, w->wd.bt,
-                       n, np);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemsetAsync(w->wd.stat, 0, 3 * sizeof(double), w->stream));
-    HIPCHK(hipMemsetAsync(w->wd.status, 0, sizeof(int), w->stream));
-    for (int kk = 0; kk < n; ++kk) {
-        hipLaunchKernelGGL(k_zgj_pivot, dim3(1), dim3(1024), 0, w->stream, w->wd, np, n, kk);
-        hipLaunchKernelGGL(k_zgj_elim, dim3((n + 255) / 256, n), dim3(256), 0, w->stream, w->wd, np, n, kk);
-    }
-    hipLaunchKernelGGL(k_zgj_unperm, dim3((n + 255) / 256), dim3(256), 0, w->stream, w->wd, np, n);
-    HIPCHK(hipGetLastError());
+    const ZWalkerDev &d = w->wd;
+    // 32 complex values a thread, on at most 512 threads
+    auto invert = n <= 1024   ? zgj_invert<16, 2>
+                  : n <= 2048 ? zgj_invert<8, 4>
+                  : n <= 4096 ? zgj_invert<4, 8>
+                  : n <= 8192 ? zgj_invert<2, 16>
+                              : zgj_invert<1, 32>;
+    HIPCHK(invert(reinterpret_cast<const zc *>(slater_host), d.a, d.bt, d.work, d.panel, d.slot, d.piv, d.pval, d.stat, n, np, w->stream));
     double st[3];
-    int bad = 0;
-    HIPCHK(hipMemcpyAsync(st, w->wd.stat, sizeof(st), hipMemcpyDeviceToHost, w->stream));
-    HIPCHK(hipMemcpyAsync(&bad, w->wd.status, sizeof(int), hipMemcpyDeviceToHost, w->stream));
+    w->piv_h.resize(n);
+    HIPCHK(hipMemcpyAsync(st, d.stat, sizeof(st), hipMemcpyDeviceToHost, w->stream));
+    HIPCHK(hipMemcpyAsync(w->piv_h.data(), d.piv, sizeof(int) * n, hipMemcpyDeviceToHost, w->stream));
     HIPCHK(hipStreamSynchronize(w->stream));
-    if (bad) return fail(DSU_ESINGULAR, "Slater matrix is singular");
+    if (st[2] != 0.0) return fail(DSU_ESINGULAR, "Slater matrix is singular");
+    // the sign of the row order: n minus its number of cycles (an element seen is marked ~)
+    int odd = n & 1;
+    for (int i = 0; i < n; ++i) {
+        if (w->piv_h[i] < 0) continue;
+        odd ^= 1;
+        for (int q = i; w->piv_h[q] >= 0;) {
+            const int to = w->piv_h[q];
+            w->piv_h[q] = ~to;
+            q = to;
+        }
+    }
     *logabs = st[0];
-    *phase = wrap_phase(st[1]);
+    *phase = wrap_phase(st[1] + (odd ? M_PI : 0.0));
     return DSU_OK;
 }
 
@@ -401,10 +615,12 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     w->la.cinv = w->wd.cinv;
     w->la.idx = w->wd.idx;
     TRY(dalloc(&w->wd.w, np * (kp + 1)));
-    TRY(dalloc(&w->wd.fcol, np));
+    TRY(dalloc(&w->wd.work, np * np));
+    TRY(dalloc(&w->wd.panel, np * 16));
+    TRY(dalloc(&w->wd.pval, np));
+    TRY(dalloc(&w->wd.slot, np));
     TRY(dalloc(&w->wd.piv, np));
     TRY(dalloc(&w->wd.stat, 3));
-    TRY(dalloc(&w->wd.status, 1));
     const int kp2 = std::min<int>(256, 2 * (int)kp);  // padded real slots
     TRY(dalloc(&w->flush_y, flush_scratch_elems<double>(w->np, 2 * w->np, kp2)));
     TRY(dalloc(&w->flush_w, np * kp2));
@@ -429,10 +645,7 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
             TRY(fail(DSU_EDEVICE, "hipHostGetDevicePointer failed"));
         w->la.words = static_cast<double *>(dptr);
     }
-    if (hipMemcpy2D(w->wd.a, np * sizeof(zc), slater_host, n * sizeof(zc), n * sizeof(zc), n, hipMemcpyHostToDevice) !=
-        hipSuccess)
-        TRY(fail(DSU_EDEVICE, "matrix upload failed"));
-    TRY(zwalker_recompute(w, &w->logabs, &w->phase));
+    TRY(zwalker_recompute(w, slater_host, &w->logabs, &w->phase));
     w->idx.assign(w->kp, -1);
 #undef TRY
     *out = w;
@@ -514,11 +727,8 @@ extern "C" int dsu_zflush(dsu_zwalker *w) {
 extern "C" int dsu_zrecompute_inverse(dsu_zwalker *w, const double *slater_host_or_null, double *logabs_out,
                                       double *phase_out, double *drift_out) {
     if (!w) return fail(DSU_EINVAL, "walker is NULL");
-    if (slater_host_or_null)
-        HIPCHK(hipMemcpy2DAsync(w->wd.a, w->np * sizeof(zc), slater_host_or_null, w->n * sizeof(zc), w->n * sizeof(zc),
-                                w->n, hipMemcpyHostToDevice, w->stream));
     double la, ph;
-    CHK(zwalker_recompute(w, &la, &ph));
+    CHK(zwalker_recompute(w, slater_host_or_null, &la, &ph));
     if (drift_out) *drift_out = w->logabs - la;
     w->logabs = la;
     w->phase = ph;
@@ -534,11 +744,10 @@ extern "C" int dsu_zrecompute_inverse(dsu_zwalker *w, const double *slater_host_
 extern "C" int dsu_zget_inverse(dsu_zwalker *w, double *out_host) {
     if (!w || !out_host) return fail(DSU_EINVAL, "NULL argument");
     CHK(zwalker_flush(w));
-    if (!w->inv_tmp) CHK(dalloc(&w->inv_tmp, (size_t)w->n * w->n));
     hipLaunchKernelGGL(k_zuntranspose, dim3((w->n + 255) / 256, w->n), dim3(256), 0, w->stream, (const zc *)w->wd.bt,
-                       w->inv_tmp, w->n, w->np);
+                       w->wd.work, w->n, w->np);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(out_host, w->inv_tmp, sizeof(zc) * w->n * w->n, hipMemcpyDeviceToHost, w->stream));
+    HIPCHK(hipMemcpyAsync(out_host, w->wd.work, sizeof(zc) * w->n * w->n, hipMemcpyDeviceToHost, w->stream));
     HIPCHK(hipStreamSynchronize(w->stream));
     return DSU_OK;
 }

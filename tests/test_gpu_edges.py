@@ -121,3 +121,41 @@ def test_flush_edges(n, k, kind):
     tol = 64.0 * np.sqrt(n) * 2.0**-24 if f32 else 1e-10
     for inv in got:
         assert np.abs(inv - exact).max() <= tol
+
+
+# Fresh inverses.  Complex: groups of 16 columns (15, 16, 17: a short, a full and
+# a short second group), 8 above n = 1024, 4 above 2048; rows in permuted order
+# make every pivot leave its place.  Real: a ragged matrix goes up unpadded.
+@pytest.mark.parametrize("n,cplx", [(1, True), (15, True), (16, True), (17, True), (64, True), (513, True),
+                                    (1024, True), (1025, True), (2049, True), (1, False), (65, False), (200, False)])
+def test_fresh_inverse_edges(n, cplx):
+    require_gpu()
+    a = [well_conditioned(40 + n + q, n, cplx)[np.random.default_rng(n + q).permutation(n)] for q in range(2)]
+    # singular values within about [1, 3]: backward error of order n 2^-53, times the condition and the pivot growth
+    tol = 64.0 * n * 2.0**-53 + 2.0**-52
+    with (dsu.ZWalker(a[0], 4) if cplx else dsu.Walker(a[0], 4)) as w:
+        for m in (None, a[1], None):
+            if m is not None or n > 1:
+                w.recompute(m)
+            ref = a[0] if m is None else m
+            assert np.abs(w.inverse() - np.linalg.inv(ref)).max() <= tol
+            s, ld = np.linalg.slogdet(ref)
+            got = w.logdet()
+            phase = np.exp(1j * got[1]) if cplx else got[0]
+            assert abs(phase - s) <= n * tol and abs((got[0] if cplx else got[1]) - ld) <= n * tol
+            a[0] = ref
+
+
+@pytest.mark.parametrize("n", [3, 40])
+def test_complex_singular_and_nan(n):
+    require_gpu()
+    a = well_conditioned(70 + n, n, True)
+    for bad in ("zero column", "nan"):
+        b = a.copy()
+        if bad == "zero column":
+            b[:, n // 2] = 0.0
+        else:
+            b[n // 2, :] = np.nan
+        with dsu.ZWalker(a, 4) as w:
+            with pytest.raises(dsu.DsuError):
+                w.recompute(b)
