@@ -5,7 +5,7 @@
 
 namespace dsu {
 
-// One pass over BT per window.  Per 64-row block:
+// One pass over BT per window (NEXT: another window follows).  Per 64-row block:
 //   W    = (y - E) C^{-T}          (from this block's rows of y, on matrix cores)
 //   for each column chunk of BT (on chip once):
 //     BT  -= W Vg[cur]              (eq. (4), row-local)
@@ -23,7 +23,15 @@ template <typename T> __device__ __forceinline__ int tcol(int m) {
 }
 
 template <typename T, int KP> struct StreamCfg {
-    static constexpr int CW = Phase3Cfg<T, KP>::CW;
+    // columns a chunk: two workgroups fit a compute unit's LDS (all but K = 256),
+    // so one's products cover the other's loads and barriers.  FP64, 32
+    // determinants of n = 1000, against one workgroup: K = 64 224 -> 195 us a
+    // launch (46 TFLOP/s, 3.1 TB/s), K = 128 387 -> 304 (59 TFLOP/s); a third of
+    // that from the operands read ahead and NEXT known to the compiler, which
+    // also gives K = 32 141 -> 138.
+    static constexpr int CW = sizeof(T) == 8 && KP == 64    ? 32
+                              : sizeof(T) == 8 && KP == 128 ? 16
+                                                            : Phase3Cfg<T, KP>::CW;
     static constexpr int VEC = 16 / (int)sizeof(T);
     static constexpr int LDVT = KP + VEC;  // V chunk stored transposed: [column][slot]
     static constexpr int LDU = CW + VEC;
@@ -36,10 +44,10 @@ template <typename T, int KP> struct StreamCfg {
     static_assert(NV >= 1 && NV * kThreads == KP * (CW / VEC), "staging split");
 };
 
-template <typename T, int KP>
-__global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__restrict__ descs, int np, int nblk,
-                                                           int kp, int kslots, int cur, int has_next, int e0n,
-                                                           int kwn) {
+template <typename T, int KP, bool NEXT>
+__global__ __launch_bounds__(kThreads, KP <= 128 ? 2 : 1) void k_flush_stream(const DetDesc<T> *__restrict__ descs,
+                                                                             int np, int nblk, int kp, int kslots,
+                                                                             int cur, int e0n, int kwn) {
     typedef StreamCfg<T, KP> C;
     typedef typename Mma<T>::acc_t acc_t;
     typedef typename Vec16<T>::type vec_t;
@@ -101,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
     const int lrow = 16 * wave + (lane & 15);
     DSU_GLOBAL T *rp = gmem(dd.bt) + (size_t)(r0 + lrow) * np + 4 * (lane >> 4);
     const int g = r0 + lrow - e0n;
-    const bool wv = has_next && g >= 0 && g < kwn;
+    const bool wv = NEXT && g >= 0 && g < kwn;
     DSU_GLOBAL T *vp = gmem(cur ? dd.vg : dd.vg2) + (size_t)(wv ? g : 0) * np + 4 * (lane >> 4);
     // staging of V and U: this thread's 16-byte pieces (row r, column cc of a chunk)
     int goff[NV], voff[NV], uoff[NV];
@@ -119,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         sv[q] = *(DSU_GLOBAL const vec_t *)(vcur + goff[q]);
-        if (has_next) su[q] = *(DSU_GLOBAL const vec_t *)(unext + goff[q]);
+        if constexpr (NEXT) su[q] = *(DSU_GLOBAL const vec_t *)(unext + goff[q]);
     }
 #pragma unroll
     for (int h = 0; h < NT * HV; ++h) nx[h] = *(DSU_GLOBAL const vec_t *)(rp + (h / HV) * 16 + (h % HV) * VEC);
@@ -127,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
     for (int q = 0; q < NV; ++q) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) lds[voff[q] + e * LDVT] = sv[q][e];
-        if (has_next) *reinterpret_cast<vec_t *>(lds + CW * LDVT + uoff[q]) = su[q];
+        if constexpr (NEXT) *reinterpret_cast<vec_t *>(lds + CW * LDVT + uoff[q]) = su[q];
     }
     __syncthreads();
 
@@ -148,22 +156,29 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
                 sv[q] = *(DSU_GLOBAL const vec_t *)(vcur + goff[q] + c1);
-                if (has_next) su[q] = *(DSU_GLOBAL const vec_t *)(unext + goff[q] + c1);
+                if constexpr (NEXT) su[q] = *(DSU_GLOBAL const vec_t *)(unext + goff[q] + c1);
             }
 #pragma unroll
             for (int h = 0; h < NT * HV; ++h)
                 nx[h] = *(DSU_GLOBAL const vec_t *)(rp + c1 + (h / HV) * 16 + (h % HV) * VEC);
         }
         const T *ap = Vt + tcol<T>(lane & 15) * LDVT + (lane >> 4) * KQ;
+        // operands of the next group of products are read from LDS while the
+        // current group runs
+        vec_t a[2][NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) a[0][t] = *reinterpret_cast<const vec_t *>(ap + 16 * t * LDVT);
 #pragma unroll
         for (int j = 0; j < KQ / VEC; ++j) {
-            vec_t a[NT];
+            if (j + 1 < KQ / VEC)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) a[t] = *reinterpret_cast<const vec_t *>(ap + 16 * t * LDVT + j * VEC);
+                for (int t = 0; t < NT; ++t)
+                    a[(j + 1) & 1][t] = *reinterpret_cast<const vec_t *>(ap + 16 * t * LDVT + (j + 1) * VEC);
+            __builtin_amdgcn_sched_barrier(0);  // keep those reads ahead of this group's products
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = Mma<T>::mma(a[t][e], wa[j * VEC + e], acc[t]);
+                for (int t = 0; t < NT; ++t) acc[t] = Mma<T>::mma(a[j & 1][t][e], wa[j * VEC + e], acc[t]);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -175,21 +190,30 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
                 *(DSU_GLOBAL vec_t *)(rp + c0 + 16 * t + h * VEC) = o;
                 if (wv) *(DSU_GLOBAL vec_t *)(vp + c0 + 16 * t + h * VEC) = o;
             }
-        if (has_next) {
+        if constexpr (NEXT) {
+            const T *up = Us + (lane & 15) * LDU + 4 * (lane >> 4);
+            constexpr int JT = KP / 16, UB = JT >= 8 ? 1 : 2;
+            vec_t ub[UB][JT];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                vec_t ub[KP / 16][HV];
+            for (int jt = 0; jt < JT; ++jt) ub[0][jt] = *reinterpret_cast<const vec_t *>(up + 16 * jt * LDU);
 #pragma unroll
-                for (int jt = 0; jt < KP / 16; ++jt)
+            for (int q = 0; q < NT * HV; ++q) {  // q = HV t + h: columns 16 t + 4 (lane / 16) + VEC h + 0 .. VEC - 1
+                if (UB == 2 && q + 1 < NT * HV) {
 #pragma unroll
-                    for (int h = 0; h < HV; ++h)
-                        ub[jt][h] = *reinterpret_cast<const vec_t *>(Us + (16 * jt + (lane & 15)) * LDU + 16 * t +
-                                                                     4 * (lane >> 4) + h * VEC);
+                    for (int jt = 0; jt < JT; ++jt)
+                        ub[(q + 1) % UB][jt] = *reinterpret_cast<const vec_t *>(
+                            up + 16 * jt * LDU + 16 * ((q + 1) / HV) + VEC * ((q + 1) % HV));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (UB == 1 && q > 0)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int jt = 0; jt < JT; ++jt)
+                        ub[0][jt] = *reinterpret_cast<const vec_t *>(up + 16 * jt * LDU + 16 * (q / HV) + VEC * (q % HV));
 #pragma unroll
-                    for (int jt = 0; jt < KP / 16; ++jt)
-                        accy[jt] = Mma<T>::mma(acc[t][i], ub[jt][i / VEC][i % VEC], accy[jt]);
+                for (int e = 0; e < VEC; ++e)
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt)
+                        accy[jt] = Mma<T>::mma(acc[q / HV][VEC * (q % HV) + e], ub[q % UB][jt][e], accy[jt]);
             }
         }
         if (c1 < np) {
@@ -199,12 +223,12 @@ __global__ __launch_bounds__(kThreads) void k_flush_stream(const DetDesc<T> *__r
             for (int q = 0; q < NV; ++q) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) nb[voff[q] + e * LDVT] = sv[q][e];
-                if (has_next) *reinterpret_cast<vec_t *>(nb + CW * LDVT + uoff[q]) = su[q];
+                if constexpr (NEXT) *reinterpret_cast<vec_t *>(nb + CW * LDVT + uoff[q]) = su[q];
             }
         }
         __syncthreads();
     }
-    if (has_next) {
+    if constexpr (NEXT) {
         const int drow = 16 * wave + Mma<T>::row0(lane);
 #pragma unroll
         for (int t = 0; t < KP / 16; ++t)
@@ -477,14 +501,23 @@ hipError_t launch_flush_stream(const DetDesc<T> *d, int ndesc, int np, int ktile
     }
     const int nblk = np / kRowBlock;
     const dim3 grid(ndesc * nblk);
-#define DSU_S(KPV)                                                                                           \
-    if (ktile == KPV) {                                                                                      \
-        hipLaunchKernelGGL((k_flush_stream<T, KPV>), grid, dim3(kThreads), 0, s, d, np, nblk, kp, kslots, cur, \
-                           has_next, e0n, kwn);                                                              \
-        return hipGetLastError();                                                                            \
+    auto launch = [&](auto kp_c) {
+        constexpr int KP = decltype(kp_c)::value;
+        if (has_next)
+            hipLaunchKernelGGL((k_flush_stream<T, KP, true>), grid, dim3(kThreads), 0, s, d, np, nblk, kp, kslots, cur,
+                               e0n, kwn);
+        else
+            hipLaunchKernelGGL((k_flush_stream<T, KP, false>), grid, dim3(kThreads), 0, s, d, np, nblk, kp, kslots, cur,
+                               e0n, kwn);
+        return hipGetLastError();
+    };
+    if (ktile == 16) return launch(std::integral_constant<int, 16>{});
+    if (ktile == 256) return launch(std::integral_constant<int, 256>{});
+    if constexpr (sizeof(T) == 8) {
+        if (ktile == 32) return launch(std::integral_constant<int, 32>{});
+        if (ktile == 64) return launch(std::integral_constant<int, 64>{});
+        if (ktile == 128) return launch(std::integral_constant<int, 128>{});
     }
-    DSU_S(16) DSU_S(32) DSU_S(64) DSU_S(128) DSU_S(256)
-#undef DSU_S
     return hipErrorInvalidValue;
 }
 template hipError_t launch_flush_stream<float>(const DetDesc<float> *, int, int, int, int, int, int, int, int, int,

@@ -180,8 +180,9 @@ __device__ __forceinline__ void rowblock_plus_wv(T *__restrict__ rows, int ld, i
 // as zero beyond kslots.  C is staged in LDS chunk by chunk (converted to T
 // and zero padded), so the product is a branch-free loop over LDS operands.
 template <typename T, int KP> struct WCfg {
-    // chunk budget: 32 KB, or 16 KB when the Y' block itself is large (FP64, K = 256)
-    static constexpr int budget = KP * (int)sizeof(T) >= 2048 ? 16384 : 32768;
+    // chunk budget: 32 KB, less when the Y' block itself is large (FP64): 8 KB at
+    // K = 128 (both in 80 KB, half a compute unit's LDS), 16 KB at K = 256
+    static constexpr int budget = sizeof(T) == 8 && KP == 128 ? 8192 : (KP * (int)sizeof(T) >= 2048 ? 16384 : 32768);
     static constexpr int JC = (KP * 64 * (int)sizeof(T) <= budget) ? 64
                               : (KP * 32 * (int)sizeof(T) <= budget ? 32 : (KP * 16 * (int)sizeof(T) <= budget ? 16 : 8));
     static constexpr int JCE = JC < KP ? JC : KP;
