@@ -88,6 +88,7 @@ struct Resident {
 struct BucketState {
     Bucket bk;
     std::vector<int> members;  // slot ids, in descriptor order
+    int fresh = 0;             // determinants at the end of the list that have no inverse yet
     bool busy = false;
     bool dirty = false;
     hipEvent_t done = nullptr;
@@ -160,8 +161,11 @@ static int refresh_bucket(dsu_server *s, BucketState *b) {
     return b->bk.set_dets(d);
 }
 
-// Admit one request (its bucket must be idle).  DSU_EBUDGET if it does not fit now.
-static int admit(dsu_server *s, const dsu_request &r, double now_s, int result_index, int *slot_out) {
+// Place one request in the arena and in its bucket (which must be idle), its
+// state uploaded in stream order; start_fresh must follow before the bucket's
+// next sweep, and r.positions stay valid until then.  DSU_EBUDGET if it does not
+// fit now.
+static int place(dsu_server *s, const dsu_request &r, double now_s, int result_index, int *slot_out) {
     if (r.n < 1 || r.n > 32768 || (r.spins != 1 && r.spins != 2) || r.sweeps < 0 || !r.positions)
         return fail(DSU_EINVAL, "bad request %llu", (unsigned long long)r.request_id);
     const size_t bytes = walker_bytes(r.n, r.spins, s->K, s->prec);
@@ -192,7 +196,7 @@ static int admit(dsu_server *s, const dsu_request &r, double now_s, int result_i
     char *base = s->arena_base + off;
     hipStream_t st = b->bk.stream;
     HIPCHK(hipMemsetAsync(base, 0, bytes, st));
-    const DetState init{0.0, 1, 0, 0, 0, 0};
+    static const DetState init{0.0, 1, 0, 0, 0, 0};
     for (int sp = 0; sp < r.spins; ++sp) {
         DetSlot d = sh.carve(base + sh.det_bytes() * sp);
         d.seed = r.seed;
@@ -204,28 +208,28 @@ static int admit(dsu_server *s, const dsu_request &r, double now_s, int result_i
         HIPCHK(hipMemcpyAsync(d.st, &init, sizeof(DetState), hipMemcpyHostToDevice, st));
         w.dets.push_back(d);
     }
-    HIPCHK(hipStreamSynchronize(st));
     const int slot = s->next_slot++;
     s->resident[slot] = w;
     b->members.push_back(slot);
-    rc = refresh_bucket(s, b);
-    if (rc == DSU_OK) {
-        // FP64 inverse of the new walker's determinants (the last members),
-        // enqueued ahead of the bucket's next sweep; a singular start is
-        // reported when that sweep completes.
-        std::vector<int> which;
-        for (int i = 0; i < r.spins; ++i) which.push_back((int)b->bk.dets.size() - r.spins + i);
-        rc = b->bk.recompute_async(which);
-    }
-    if (rc != DSU_OK) {
-        b->members.pop_back();
-        s->resident.erase(slot);
-        s->arena.release(off, bytes);
-        (void)refresh_bucket(s, b);
-        return rc;
-    }
+    b->dirty = true;
+    b->fresh += r.spins;
     if (slot_out) *slot_out = slot;
     return DSU_OK;
+}
+
+// FP64 inverses of the determinants placed since the last call, all of them in
+// as few passes as the workspace allows, enqueued ahead of the bucket's next
+// sweep; a singular start is reported when that sweep completes.  (One pass per
+// request, each waiting for the one before, took half of the time of 24
+// saturating requests: the panel chains of buckets of different n, which run
+// side by side, and of a bucket's own requests were done one after the other.)
+static int start_fresh(dsu_server *s, BucketState *b) {
+    if (!b->fresh) return DSU_OK;
+    CHK(refresh_bucket(s, b));  // waits for the uploads
+    std::vector<int> which;
+    for (int i = (int)b->bk.dets.size() - b->fresh; i < (int)b->bk.dets.size(); ++i) which.push_back(i);
+    b->fresh = 0;
+    return b->bk.recompute_async(which);
 }
 
 static int read_result(dsu_server *s, int slot, dsu_result *out) {
@@ -365,8 +369,14 @@ extern "C" int dsu_server_add(dsu_server *s, const dsu_request *req, int32_t *sl
     auto it = s->buckets.find(req->n);
     if (it != s->buckets.end() && it->second->busy) return fail(DSU_ESTATE, "bucket busy");
     int slot = -1;
-    CHK(admit(s, *req, 0.0, -1, &slot));
+    CHK(place(s, *req, 0.0, -1, &slot));
     BucketState *b = s->buckets[req->n].get();
+    const int rc = start_fresh(s, b);
+    if (rc != DSU_OK) {
+        b->fresh = 0;
+        retire(s, slot);
+        return rc;
+    }
     HIPCHK(hipStreamSynchronize(b->bk.stream));
     const std::vector<int> bad = flag_singular(s, b);
     if (std::find(bad.begin(), bad.end(), slot) != bad.end()) {
@@ -491,14 +501,19 @@ extern "C" int dsu_server_run(dsu_server *s, const dsu_request *reqs, int32_t co
                 continue;
             }
             int slot = -1;
-            const int rc = admit(s, r, now_s(), *it, &slot);
+            const int rc = place(s, r, now_s(), *it, &slot);
             if (rc == DSU_EBUDGET) {
                 ++it;
                 continue;
             }
-            if (rc != DSU_OK) return rc;
+            if (rc != DSU_OK) {
+                for (auto &kv : s->buckets) (void)hipStreamSynchronize(kv.second->bk.stream);  // uploads of the caller's arrays
+                return rc;
+            }
             it = waiting.erase(it);
         }
+        for (auto &kv : s->buckets)
+            if (!kv.second->busy) CHK(start_fresh(s, kv.second.get()));
         // launch the next sweep of every idle, non-empty bucket
         bool any_busy = false;
         for (auto &kv : s->buckets) {
