@@ -2,11 +2,10 @@
 // entry points built on it.
 //
 // A sweep of every member determinant is a chain of windows of K proposals
-// (electrons e0..e0+kw-1), three launches per window:
-//   props  : draw the next window's kw moves and evaluate their proposed
-//            orbital rows U (k_window_rows, beside the decisions on a second
-//            stream)
-//   decide : sequential Metropolis decisions with the bordered inverse of
+// (electrons e0..e0+kw-1), two launches per window:
+//   decide : draw the next window's kw moves and evaluate their proposed
+//            orbital rows U (window_rows, in blocks of their own) beside the
+//            sequential Metropolis decisions with the bordered inverse of
 //            eq. (3)'s C matrix (k_window_decide_gj / k_window_decide), the
 //            look-ahead products G taken from the previous pass over BT
 //   flush  : one pass over BT: the en-bloc Woodbury update of eq. (4), and,
@@ -96,8 +95,10 @@ int Bucket::init(const BucketShape &shape, int k_delay, double box_l, void *stre
     L = box_l;
     twopi_l = 2.0 * M_PI / box_l;
     CHK(make_stream(stream_or_null, &stream, &own_stream));
-    HIPCHK(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
-    for (hipEvent_t &e : ev_ring_) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    if (rows_beside) {
+        HIPCHK(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+        for (hipEvent_t &e : ev_ring_) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
     CHK(dalloc(&kvec, (size_t)sh.n));
     std::vector<int4> kv(sh.n);
     build_kvectors(sh.n, kv.data());
@@ -227,19 +228,14 @@ int Bucket::set_dets(const std::vector<DetSlot> &d) {
 int Bucket::set_delay(int k) {
     if (k < 1 || k > sh.kmax) return fail(DSU_EINVAL, "delay %d outside [1, %d] of this batch", k, sh.kmax);
     HIPCHK(hipStreamSynchronize(stream));
-    HIPCHK(hipStreamSynchronize(side));
     K = k;
     drop_graph();
     return DSU_OK;
 }
 
 void Bucket::drop_graph() {
-    // a launched graph may still be running on either stream: destroy it only
-    // once both have drained
-    if (gexec_ || graph_) {
-        if (stream) (void)hipStreamSynchronize(stream);
-        if (side) (void)hipStreamSynchronize(side);
-    }
+    // a launched graph may still be running: destroy it only once the stream has drained
+    if ((gexec_ || graph_) && stream) (void)hipStreamSynchronize(stream);
     if (gexec_) (void)hipGraphExecDestroy(gexec_);
     if (graph_) (void)hipGraphDestroy(graph_);
     gexec_ = nullptr;
@@ -273,7 +269,6 @@ template <typename F> int Bucket::timed(int phase, F fn, hipStream_t on) {
 int Bucket::harvest_events() {
     if (ev_used_.empty()) return DSU_OK;
     HIPCHK(hipStreamSynchronize(stream));
-    HIPCHK(hipStreamSynchronize(side));
     for (auto &e : ev_used_) {
         float ms = 0;
         HIPCHK(hipEventElapsedTime(&ms, e.second.first, e.second.second));
@@ -286,9 +281,9 @@ int Bucket::harvest_events() {
     return DSU_OK;
 }
 
-// Streaming sweep: prime (proposals of window 0, y = BT U^T for all rows,
-// decisions of window 0), then per window w: proposals of w+1, one-pass flush
-// of w producing y for w+1, decisions of w+1.
+// Streaming sweep: prime (proposals of window 0, y = BT U^T for all rows), then
+// per window w: decisions of w with the proposals of w+1, one-pass flush of w
+// producing y for w+1.
 template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
     const DetDesc<T> *dd = (const DetDesc<T> *)ddesc_;
     const int nd = (int)dets.size();
@@ -301,27 +296,26 @@ template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
     CHK(timed(PH_G, [&] { return launch_window_prime<T>(dd, nd, sh.np, kt, sh.kp, 0, stream); }));
     int ring = 0;
     for (int w = 0; w < nwin; ++w) {
-        const int cur = w & 1, nxt = cur ^ 1;
+        const int cur = w & 1;
         const bool has_next = w + 1 < nwin;
-        const int e0 = w * K, e0n = (w + 1) * K, kwn = has_next ? kw_of(w + 1) : 0;
-        // The next window's proposals depend only on sweep-start positions of
-        // its own electrons: draw them on the side stream while this window is
-        // decided.  Their U/proposal buffers were last read by the previous
-        // flush, which the fork point follows.
+        const int e0n = (w + 1) * K, kwn = has_next ? kw_of(w + 1) : 0;
+        // the next window's proposals: its U and proposal buffers were last read
+        // by the previous flush and decisions
         hipEvent_t fork = ev_ring_[ring++ & 7], join = ev_ring_[ring++ & 7];
-        if (has_next) {
+        if (rows_beside && has_next) {
             HIPCHK(hipEventRecord(fork, stream));
             HIPCHK(hipStreamWaitEvent(side, fork, 0));
             CHK(timed(PH_ROWS, [&] {
-                return launch_window_props<T>(dd, nd, sh.n, sh.np, kt, e0n, kwn, kvec, twopi_l, nxt, 0, kmax_comp,
+                return launch_window_props<T>(dd, nd, sh.n, sh.np, kt, e0n, kwn, kvec, twopi_l, cur ^ 1, 0, kmax_comp,
                                               side);
             }, side));
             HIPCHK(hipEventRecord(join, side));
         }
         CHK(timed(PH_DECIDE, [&] {
-            return launch_window_decide<T>(dd, nd, kt, sh.kp, e0, kw_of(w), force, w + 1 == nwin, cur, stream);
+            return launch_window_decide<T>(dd, nd, sh.n, sh.np, kt, sh.kp, w * K, kw_of(w), e0n, rows_beside ? 0 : kwn,
+                                           kvec, twopi_l, kmax_comp, force, !has_next, cur, stream);
         }));
-        if (has_next) HIPCHK(hipStreamWaitEvent(stream, join, 0));
+        if (rows_beside && has_next) HIPCHK(hipStreamWaitEvent(stream, join, 0));
         CHK(timed(PH_FLUSH, [&] {
             return launch_flush_stream<T>(dd, nd, sh.np, kt, sh.kp, kw_of(w), cur, has_next ? 1 : 0, e0n, kwn, stream);
         }));

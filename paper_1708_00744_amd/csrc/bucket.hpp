@@ -44,7 +44,12 @@ class Bucket {
     double L = 0.0, twopi_l = 0.0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    hipStream_t side = nullptr;  // proposals of the next window, beside the current window's decisions
+    // Before init: the later windows' proposals in launches of their own on a
+    // second stream instead of blocks of the decisions' launches.  An event pair
+    // a window makes it the slower form at every size; the serving pool keeps it
+    // for walkers below n = 1024 (see there).
+    bool rows_beside = false;
+    hipStream_t side = nullptr;
     int4 *kvec = nullptr;
     int kmax_comp = 0;  // largest |component| of the plane-wave integer vectors
     std::vector<DetSlot> dets;

@@ -185,10 +185,13 @@ hipError_t launch_untranspose(const T *bt, double *out, int n, int np, hipStream
 // Batched window kernels.  ktile = padded delay of the launch (template tile
 // count, 16..256), kp = padded delay the buffers were allocated for (stride),
 // nmax = largest |component| of the plane-wave integer vectors.
-// Decisions of one window: the look-ahead products G come from y (formed by
-// the previous pass over BT), proposals from prop (pbuf 0) or prop2 (1).
+// Decisions of one window (electrons e0 .. e0 + kw - 1): the look-ahead products
+// G come from y (formed by the previous pass over BT), proposals from prop (pbuf
+// 0) or prop2 (1).  Beside them, unless kwn = 0, the next window's proposals and
+// rows (electrons e0n .. e0n + kwn - 1) into the other buffers.
 template <typename T>
-hipError_t launch_window_decide(const DetDesc<T> *d, int ndesc, int ktile, int kp, int e0, int kw, int force_accept,
+hipError_t launch_window_decide(const DetDesc<T> *d, int ndesc, int n, int np, int ktile, int kp, int e0, int kw,
+                                int e0n, int kwn, const int4 *kvec, double twopi_over_l, int nmax, int force_accept,
                                 int last_window, int pbuf, hipStream_t s);
 
 // Streaming path (one pass over BT per window):

@@ -73,10 +73,19 @@ __device__ __forceinline__ double pw_orbital(int4 kv, double twopi_l, double x, 
 }
 
 // ------------------------------------------------------- window proposals
-// grid (ndesc, nsplit): every block draws the window's kw moves (cheap) and
-// fills its column range of U (proposed orbital rows, zero past kw and n) and
-// Vg (the stale BT rows e0..e0+kw-1, zero past kw).  Block 0 of a determinant
-// also stores the proposals for the decision kernel.
+// `parts` blocks a determinant: every block draws the window's kw moves (cheap)
+// and fills its column range of U (proposed orbital rows, zero past kw and n) and
+// Vg (the stale BT rows e0..e0+kw-1, zero past kw).  Part 0 also stores the
+// proposals for the decision kernel.
+//
+// A sweep's first window has a launch of its own (k_window_rows); every later
+// window's proposals depend only on sweep-start positions of its own electrons
+// and are drawn by further blocks of the launch that decides the window before
+// (k_window_decide*).  Launches of their own on a second stream, with an event
+// pair a window, cost 7 to 20 us a window more than the work they hid.  A sweep,
+// before and after: FP64 n = 100, K = 8, one determinant 465 -> 220 us; n = 1000,
+// K = 64, 8 of them 2711 -> 2167, 32 of them 4134 -> 3801; FP32 n = 512, K = 32,
+// 512 of them 5683 -> 5398; n = 4096, K = 128, 32 of them 78.9 -> 75.7 ms.
 //
 // Orbitals from per-axis phase factors: with q = 2 pi / L,
 // exp(i q (nx x + ny y + nz z)) = Ex^nx Ey^ny Ez^nz and E^-n = conj(E^n), so a
@@ -87,14 +96,26 @@ __device__ __forceinline__ double pw_orbital(int4 kv, double twopi_l, double x, 
 constexpr int kPwTab = 24;
 constexpr int kPwGroup = 32;
 
+struct RowsArgs {
+    int n, np, ktile, e0, kw;   // the window: electrons e0 .. e0 + kw - 1, tile of ktile slots
+    const int4 *kvec;
+    double twopi_l;
+    int buf, copy_vg, nmax;     // U / proposal buffer; nmax: largest |component| of kvec
+};
+
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__restrict__ descs, int n, int np,
-                                                          int ktile, int e0, int kw, const int4 *__restrict__ kvec,
-                                                          double twopi_l, int buf, int copy_vg, int nmax) {
+__device__ __forceinline__ void window_rows(const DetDesc<T> &d, const RowsArgs &ra, int part, int parts) {
 #pragma clang fp contract(off)
-    __shared__ double s_r[DSU_KMAX_LDS][3];
-    __shared__ double s_c[kPwGroup][3][kPwTab + 1], s_s[kPwGroup][3][kPwTab + 1];
-    const DetDesc<T> d = descs[blockIdx.x];
+    // proposed positions, then cos and sin of the group's phases, nmax + 1 a
+    // position and axis (only that many: 11 KB at n = 512 instead of 44, so that a
+    // launch finds room beside the flush)
+    extern __shared__ double s_rows[];
+    const int n = ra.n, np = ra.np, ktile = ra.ktile, e0 = ra.e0, kw = ra.kw, buf = ra.buf, copy_vg = ra.copy_vg;
+    const int nmax = ra.nmax, nt = nmax + 1;
+    const int4 *__restrict__ kvec = ra.kvec;
+    const double twopi_l = ra.twopi_l;
+    double(*s_r)[3] = reinterpret_cast<double(*)[3]>(s_rows);
+    double *s_c = s_rows + 3 * ktile, *s_s = s_c + 3 * kPwGroup * nt;
     const int tid = threadIdx.x;
     const long long sweep = d.st->sweep;
     for (int a = tid; a < kw; a += kThreads) {
@@ -105,14 +126,14 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
         const double y = d.pos[3 * e + 1] + d.sigma * g[1];
         const double z = d.pos[3 * e + 2] + d.sigma * g[2];
         s_r[a][0] = x; s_r[a][1] = y; s_r[a][2] = z;
-        if (blockIdx.y == 0) {
+        if (part == 0) {
             double *pr = buf ? d.prop2 : d.prop;
             pr[4 * a + 0] = x; pr[4 * a + 1] = y; pr[4 * a + 2] = z; pr[4 * a + 3] = u;
         }
     }
     __syncthreads();
-    const int cols = np / gridDim.y;
-    const int c_begin = blockIdx.y * cols;
+    const int cols = np / parts;
+    const int c_begin = part * cols;
     T *uo = buf ? d.u2 : d.u;
     T *vo = buf ? d.vg2 : d.vg;
     if (nmax > kPwTab) {
@@ -135,8 +156,8 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
             const int a = v / (3 * (nmax + 1)), r = v % (3 * (nmax + 1)), ax = r / (nmax + 1), m = r % (nmax + 1);
             double sn = 0.0, cs = 1.0;
             if (a0 + a < kw) sincos(twopi_l * ((double)m * s_r[a0 + a][ax]), &sn, &cs);
-            s_c[a][ax][m] = cs;
-            s_s[a][ax][m] = sn;
+            s_c[(3 * a + ax) * nt + m] = cs;
+            s_s[(3 * a + ax) * nt + m] = sn;
         }
         __syncthreads();
         if (cols == kThreads) {
@@ -159,8 +180,8 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
                             double re = 1.0, im = 0.0;
 #pragma unroll
                             for (int ax = 0; ax < 3; ++ax) {
-                                const double fc = s_c[a][ax][mm[ax]];
-                                const double fs = ng[ax] ? -s_s[a][ax][mm[ax]] : s_s[a][ax][mm[ax]];
+                                const int at = (3 * a + ax) * nt + mm[ax];
+                                const double fc = s_c[at], fs = ng[ax] ? -s_s[at] : s_s[at];
                                 const double t = re * fc - im * fs;
                                 im = re * fs + im * fc;
                                 re = t;
@@ -189,8 +210,8 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
 #pragma unroll
                         for (int ax = 0; ax < 3; ++ax) {
                             const int m = ax_n[ax] < 0 ? -ax_n[ax] : ax_n[ax];
-                            const double fc = s_c[a][ax][m];
-                            const double fs = ax_n[ax] < 0 ? -s_s[a][ax][m] : s_s[a][ax][m];
+                            const double fc = s_c[(3 * a + ax) * nt + m];
+                            const double fs = ax_n[ax] < 0 ? -s_s[(3 * a + ax) * nt + m] : s_s[(3 * a + ax) * nt + m];
                             const double t = re * fc - im * fs;
                             im = re * fs + im * fc;
                             re = t;
@@ -208,13 +229,27 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
 }
 
 template <typename T>
+__global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__restrict__ descs, RowsArgs ra) {
+    const DetDesc<T> d = descs[blockIdx.x];
+    window_rows(d, ra, blockIdx.y, gridDim.y);
+}
+
+// Blocks a determinant's rows are split over, and a block's LDS.
+static int rows_parts(int np) {
+    int parts = np / 256;
+    if (parts < 1) parts = 1;
+    while (np % parts) --parts;
+    return parts;
+}
+static size_t rows_lds(int ktile, int nmax) {
+    return sizeof(double) * (3 * ktile + (nmax <= kPwTab ? 6 * kPwGroup * (nmax + 1) : 0));
+}
+
+template <typename T>
 hipError_t launch_window_props(const DetDesc<T> *d, int ndesc, int n, int np, int ktile, int e0, int kw,
                                const int4 *kvec, double twopi_over_l, int buf, int copy_vg, int nmax, hipStream_t s) {
-    int nsplit = np / 256;
-    if (nsplit < 1) nsplit = 1;
-    while (np % nsplit) --nsplit;
-    hipLaunchKernelGGL((k_window_rows<T>), dim3(ndesc, nsplit), dim3(kThreads), 0, s, d, n, np, ktile, e0, kw, kvec,
-                       twopi_over_l, buf, copy_vg, nmax);
+    const RowsArgs ra{n, np, ktile, e0, kw, kvec, twopi_over_l, buf, copy_vg, nmax};
+    hipLaunchKernelGGL((k_window_rows<T>), dim3(ndesc, rows_parts(np)), dim3(kThreads), rows_lds(ktile, nmax), s, d, ra);
     return hipGetLastError();
 }
 template hipError_t launch_window_props<float>(const DetDesc<float> *, int, int, int, int, int, int, const int4 *,
@@ -234,10 +269,19 @@ template <int KP> struct DecideCfg {
     static constexpr int lds_c = c_lds ? KP * ld : 1;
 };
 
+// Blocks from ndesc on draw the next window's proposals and rows, `parts` a
+// determinant (here and in k_window_decide_gj).
 template <typename T, int KP>
 __global__ __launch_bounds__(DecideCfg<KP>::threads) void k_window_decide(const DetDesc<T> *__restrict__ descs,
-                                                                          int kp, int e0, int kw, int force_accept,
+                                                                          int ndesc, RowsArgs ra, int parts, int kp,
+                                                                          int e0, int kw, int force_accept,
                                                                           int last_window, int pbuf) {
+    static_assert(DecideCfg<KP>::threads == kThreads, "the rows' blocks");
+    if ((int)blockIdx.x >= ndesc) {
+        const DetDesc<T> d = descs[(blockIdx.x - ndesc) / parts];
+        window_rows(d, ra, (blockIdx.x - ndesc) % parts, parts);
+        return;
+    }
     typedef DecideCfg<KP> C;
     constexpr int LD = C::ld, NT = C::threads;
     __shared__ double s_g[C::lds_g];
@@ -360,8 +404,14 @@ __global__ __launch_bounds__(DecideCfg<KP>::threads) void k_window_decide(const 
 // register index is fixed).  A step is one LDS exchange of the pivot row and
 // one barrier; the pivot column comes from one lane of each wave.
 template <typename T, int KP>
-__global__ __launch_bounds__(256) void k_window_decide_gj(const DetDesc<T> *__restrict__ descs, int kp, int e0,
-                                                          int kw, int force_accept, int last_window, int pbuf) {
+__global__ __launch_bounds__(256) void k_window_decide_gj(const DetDesc<T> *__restrict__ descs, int ndesc,
+                                                          RowsArgs ra, int parts, int kp, int e0, int kw,
+                                                          int force_accept, int last_window, int pbuf) {
+    if ((int)blockIdx.x >= ndesc) {
+        const DetDesc<T> d = descs[(blockIdx.x - ndesc) / parts];
+        window_rows(d, ra, (blockIdx.x - ndesc) % parts, parts);
+        return;
+    }
     constexpr int RW = KP / 4, CPL = KP > 64 ? KP / 64 : 1, NC = 64 * CPL;
     static_assert(KP >= 16 && KP <= 128 && RW % 4 == 0, "window tile");
     __shared__ double s_row[2][2][NC];
@@ -541,29 +591,28 @@ __global__ __launch_bounds__(256) void k_window_decide_gj(const DetDesc<T> *__re
 }
 
 template <typename T>
-hipError_t launch_window_decide(const DetDesc<T> *d, int ndesc, int ktile, int kp, int e0, int kw, int force_accept,
+hipError_t launch_window_decide(const DetDesc<T> *d, int ndesc, int n, int np, int ktile, int kp, int e0, int kw,
+                                int e0n, int kwn, const int4 *kvec, double twopi_over_l, int nmax, int force_accept,
                                 int last_window, int pbuf, hipStream_t s) {
-#define DSU_G(KPV)                                                                                                \
+    const RowsArgs ra{n, np, ktile, e0n, kwn, kvec, twopi_over_l, pbuf ^ 1, 0, nmax};
+    const int parts = rows_parts(np);
+    const dim3 grid(ndesc * (kwn ? 1 + parts : 1));
+    const size_t lds = kwn ? rows_lds(ktile, nmax) : 0;
+#define DSU_G(KERNEL, KPV)                                                                                           \
     if (ktile == KPV) {                                                                                           \
-        hipLaunchKernelGGL((k_window_decide_gj<T, KPV>), dim3(ndesc), dim3(256), 0, s, d, kp, e0, kw,             \
-                           force_accept, last_window, pbuf);                                                      \
-        return hipGetLastError();                                                                                 \
+        hipLaunchKernelGGL((KERNEL<T, KPV>), grid, dim3(kThreads), lds, s, d, ndesc, ra, parts, kp, e0, kw,          \
+                           force_accept, last_window, pbuf);                                                         \
+        return hipGetLastError();                                                                                    \
     }
-#define DSU_D(KPV)                                                                                                \
-    if (ktile == KPV) {                                                                                           \
-        hipLaunchKernelGGL((k_window_decide<T, KPV>), dim3(ndesc), dim3(DecideCfg<KPV>::threads), 0, s, d, kp,    \
-                           e0, kw, force_accept, last_window, pbuf);                                              \
-        return hipGetLastError();                                                                                 \
-    }
-    DSU_G(16) DSU_G(32) DSU_G(64) DSU_G(128) DSU_D(256)
-#undef DSU_D
+    DSU_G(k_window_decide_gj, 16) DSU_G(k_window_decide_gj, 32) DSU_G(k_window_decide_gj, 64)
+    DSU_G(k_window_decide_gj, 128) DSU_G(k_window_decide, 256)
 #undef DSU_G
     return hipErrorInvalidValue;
 }
-template hipError_t launch_window_decide<float>(const DetDesc<float> *, int, int, int, int, int, int, int, int,
-                                                hipStream_t);
-template hipError_t launch_window_decide<double>(const DetDesc<double> *, int, int, int, int, int, int, int, int,
-                                                 hipStream_t);
+template hipError_t launch_window_decide<float>(const DetDesc<float> *, int, int, int, int, int, int, int, int, int,
+                                                const int4 *, double, int, int, int, int, hipStream_t);
+template hipError_t launch_window_decide<double>(const DetDesc<double> *, int, int, int, int, int, int, int, int, int,
+                                                 const int4 *, double, int, int, int, int, hipStream_t);
 
 // ------------------------------------------------------- streaming path
 // y[i][a] = BT[i,:] . U[buf][a,:] for every row i (the look-ahead products of
