@@ -482,12 +482,201 @@ __global__ __launch_bounds__(kThreads, 2) void k_flush_stream32(const DetDesc<fl
     }
 }
 
+// The same pass for few determinants (at most one workgroup of 64 rows a compute
+// unit), where k_flush_stream32's 128-row workgroups leave half of the units
+// idle and its waves, one per SIMD, each run both halves of a chunk's products.
+// Here two waves share 32 rows: wave half h updates columns 32 h .. + 31 of the
+// chunk, hands them to the other through LDS, and forms half of the next
+// window's slots from all 64.  Every element gets the same operations in the same
+// order.  Per launch, against 128-row workgroups: K = 64, n = 2048, 8 determinants
+// 192 -> 120 us, n = 1024, 16 of them 102 -> 64, n = 200, 10 31 -> 19; K = 128, n =
+// 4096, 4 determinants 626 -> 391, n = 1024, 16 169 -> 106.  (Its LDS allows one
+// workgroup a unit: past 256 of them a second round costs more than it gains.)
+template <int KP> struct Split32Cfg {
+    static constexpr int CW = 64, KH = KP / 2, NV = KP * (CW / 4) / kThreads;
+    static constexpr int LDVT = KP + 4, LDU = CW + 4, LDY = KP + 4, LDX = CW + 4;
+    static constexpr int buf = CW * LDVT + KP * LDU, xch = 64 * LDX;
+    static constexpr int elems = 2 * buf + xch;
+    static_assert(64 * LDY <= 2 * buf && elems * 4 <= 160 * 1024, "LDS");
+};
+
+template <int KP, bool NEXT>
+__global__ __launch_bounds__(kThreads, 1) void k_flush_split32(const DetDesc<float> *__restrict__ descs, int np,
+                                                               int nblk, int kp, int kslots, int cur, int e0n,
+                                                               int kwn) {
+    typedef Split32Cfg<KP> C;
+    typedef typename Vec16<float>::type vec_t;
+    constexpr int CW = C::CW, LDVT = C::LDVT, LDU = C::LDU, LDY = C::LDY, LDX = C::LDX, NV = C::NV, KH = C::KH;
+    constexpr int JT = KP / 64;  // 32-slot tiles of a wave
+    __shared__ __attribute__((aligned(16))) float lds[C::elems];
+    float *xch = lds + 2 * C::buf;
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int d = b / nblk, r0 = (b % nblk) * kRowBlock;
+    const DetDesc<float> dd = descs[d];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = wave >> 1, h = wave & 1;
+    DSU_GLOBAL const float *vcur = gmem<const float>(cur ? dd.vg2 : dd.vg);
+    DSU_GLOBAL const float *unext = gmem<const float>(cur ? dd.u : dd.u2);
+    DSU_GLOBAL float *y = gmem(dd.y);
+
+    // W = (y - E) C^{-T} of the 64 rows, kept as B operands of the wave's 32
+    float wa[KH];
+    {
+        constexpr int NQ = 16 * KP / kThreads;
+        f32x4 yv[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int v = tid + q * kThreads, i = v / (KP / 4), jq = v % (KP / 4);
+            yv[q] = *(DSU_GLOBAL const f32x4 *)(y + (size_t)(r0 + i) * kp + 4 * jq);
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int v = tid + q * kThreads, i = v / (KP / 4), jq = v % (KP / 4);
+            *reinterpret_cast<f32x4 *>(lds + i * LDY + 4 * jq) = yv[q];
+        }
+        __syncthreads();
+        for (int j = tid; j < kslots; j += kThreads) {
+            const int e = dd.idx[j] - r0;
+            if (e >= 0 && e < kRowBlock) lds[e * LDY + j] -= 1.0f;
+        }
+        __syncthreads();
+        f32x4 w[KP / 16];
+        w_from_y32<KP>(lds, LDY, dd.cfl32, w);
+#pragma unroll
+        for (int t = 0; t < KP / 16; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lds[(16 * wave + 4 * (lane >> 4) + i) * LDY + 16 * t + (lane & 15)] = w[t][i];
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < KH; ++s) wa[s] = -lds[(32 * rg + (lane & 31)) * LDY + (lane >> 5) * KH + s];
+        __syncthreads();
+    }
+
+    // this lane's BT row and its first column in the wave's tile of a chunk
+    const int lrow = 32 * rg + (lane & 31), lcol = 32 * h + 4 * (lane >> 5);
+    DSU_GLOBAL float *rp = gmem(dd.bt) + (size_t)(r0 + lrow) * np + lcol;
+    const int g = r0 + lrow - e0n;
+    const bool wv = NEXT && g >= 0 && g < kwn;
+    DSU_GLOBAL float *vp = gmem(cur ? dd.vg : dd.vg2) + (size_t)(wv ? g : 0) * np + lcol;
+    int goff[NV], voff[NV], uoff[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        const int v = tid + q * kThreads, r = v / (CW / 4), cc = (v % (CW / 4)) * 4;
+        goff[q] = r * np + cc;
+        voff[q] = cc * LDVT + r;
+        uoff[q] = r * LDU + cc;
+    }
+    vec_t sv[NV], su[NV], nx[4];
+    auto fetch = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            sv[q] = *(DSU_GLOBAL const vec_t *)(vcur + goff[q] + c);
+            if constexpr (NEXT) su[q] = *(DSU_GLOBAL const vec_t *)(unext + goff[q] + c);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) nx[q] = *(DSU_GLOBAL const vec_t *)(rp + c + 8 * q);
+    };
+    auto stage = [&](float *dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[voff[q] + e * LDVT] = sv[q][e];
+            if constexpr (NEXT) *reinterpret_cast<vec_t *>(dst + CW * LDVT + uoff[q]) = su[q];
+        }
+    };
+    fetch(0);
+    stage(lds);
+    __syncthreads();
+
+    f32x16 accy[JT];
+#pragma unroll
+    for (int t = 0; t < JT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) accy[t][i] = 0.0f;
+    int cb = 0;
+    for (int c0 = 0; c0 < np; c0 += CW, cb ^= 1) {
+        const float *Vt = lds + cb * C::buf;
+        const float *Us = Vt + CW * LDVT;
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = nx[i / 4][i % 4];
+        const int c1 = c0 + CW;
+        if (c1 < np) fetch(c1);
+        const float *ap = Vt + (32 * h + (lane & 31)) * LDVT + (lane >> 5) * KH;
+        vec_t a[2];
+        a[0] = *reinterpret_cast<const vec_t *>(ap);
+#pragma unroll
+        for (int j = 0; j < KH / 4; ++j) {
+            if (j + 1 < KH / 4) a[(j + 1) & 1] = *reinterpret_cast<const vec_t *>(ap + 4 * (j + 1));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j & 1][e], wa[4 * j + e], acc, 0, 0, 0);
+        }
+        float *xp = xch + lrow * LDX + 4 * (lane >> 5);  // + 32 t + 8 q: columns of tile t, group q
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const vec_t o = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+            if constexpr (NEXT) *reinterpret_cast<vec_t *>(xp + 32 * h + 8 * q) = o;
+            *(DSU_GLOBAL vec_t *)(rp + c0 + 8 * q) = o;
+            if (wv) *(DSU_GLOBAL vec_t *)(vp + c0 + 8 * q) = o;
+        }
+        if constexpr (NEXT) {
+            const float *up = Us + (32 * JT * h + (lane & 31)) * LDU + 4 * (lane >> 5);
+            __syncthreads();  // the other wave's tile (read below, rewritten after the chunk's last barrier)
+            vec_t xa[2], ub[2][JT];
+            auto operands = [&](int q) __attribute__((always_inline)) {
+                xa[q & 1] = *reinterpret_cast<const vec_t *>(xp + 32 * (q / 4) + 8 * (q % 4));
+#pragma unroll
+                for (int jt = 0; jt < JT; ++jt)
+                    ub[q & 1][jt] =
+                        *reinterpret_cast<const vec_t *>(up + 32 * jt * LDU + 32 * (q / 4) + 8 * (q % 4));
+            };
+            operands(0);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q + 1 < 8) operands(q + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int jt = 0; jt < JT; ++jt)
+                        accy[jt] =
+                            __builtin_amdgcn_mfma_f32_32x32x2f32(xa[q & 1][e], ub[q & 1][jt][e], accy[jt], 0, 0, 0);
+            }
+        }
+        if (c1 < np) stage(lds + (cb ^ 1) * C::buf);
+        __syncthreads();
+    }
+    if constexpr (NEXT) {
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                y[(size_t)(r0 + 32 * rg + 8 * (i / 4) + 4 * (lane >> 5) + i % 4) * kp + 32 * (JT * h + jt) +
+                  (lane & 31)] = accy[jt][i];
+    }
+}
+
 template <typename T>
 hipError_t launch_flush_stream(const DetDesc<T> *d, int ndesc, int np, int ktile, int kp, int kslots, int cur,
                                int has_next, int e0n, int kwn, hipStream_t s) {
     if (sizeof(T) == 4 && (ktile == 32 || ktile == 64 || ktile == 128)) {
         const int nblk = (np + kRowBlock32 - 1) / kRowBlock32;
         const DetDesc<float> *df = (const DetDesc<float> *)d;
+        // one 64-row workgroup a compute unit at most: the split form
+        if (ktile >= 64 && ndesc * (np / kRowBlock) <= 256) {
+            const int nb = np / kRowBlock;
+            auto launch = [&](auto kp_c, auto next_c) {
+                hipLaunchKernelGGL((k_flush_split32<decltype(kp_c)::value, decltype(next_c)::value>), dim3(ndesc * nb),
+                                   dim3(kThreads), 0, s, df, np, nb, kp, kslots, cur, e0n, kwn);
+                return hipGetLastError();
+            };
+            auto both = [&](auto kp_c) {
+                return has_next ? launch(kp_c, std::true_type{}) : launch(kp_c, std::false_type{});
+            };
+            return ktile == 64 ? both(std::integral_constant<int, 64>{}) : both(std::integral_constant<int, 128>{});
+        }
         if (ktile == 32)
             hipLaunchKernelGGL((k_flush_stream32<32>), dim3(ndesc * nblk), dim3(kThreads), 0, s, df, np, nblk, kp,
                                kslots, cur, has_next, e0n, kwn);

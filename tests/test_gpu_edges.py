@@ -159,3 +159,24 @@ def test_complex_singular_and_nan(n):
         with dsu.ZWalker(a, 4) as w:
             with pytest.raises(dsu.DsuError):
                 w.recompute(b)
+
+
+# FP32 sweeps at K = 64 and 128: up to 256 blocks of 64 rows take the split flush,
+# more the 128-row one (257 blocks of n = 64; 129 determinants of two blocks); n <=
+# K is one window, without a next one.  A determinant's trajectory depends on its
+# own seed alone, and both forms do the same operations in the same order.
+@pytest.mark.parametrize("n,K,walkers", [(64, 64, 257), (50, 128, 257), (128, 64, 129), (100, 64, 129),
+                                         (128, 128, 129), (65, 50, 129), (300, 100, 52)])
+def test_flush_forms_agree(n, K, walkers):
+    require_gpu()
+    pos = np.stack([inputs.positions(9, w, n, 10.0) for w in range(walkers)])
+
+    def run(sel):
+        with dsu.Batch(n, pos[sel], [9] * len(sel), sel, 0.3, K, precision=dsu.FP32_MIXED, box_l=10.0) as b:
+            b.sweep(2)
+            st = b.stats()
+            return [(st["logdet"][q], st["sign"][q], st["accepted"][q], b.positions(q)) for q in range(3)]
+
+    many, few = run(list(range(walkers))), run([0, 1, 2])
+    for a, b in zip(many, few):
+        assert a[:3] == b[:3] and np.array_equal(a[3], b[3])
