@@ -504,7 +504,9 @@ __global__ __launch_bounds__(kThreads) void k_gj_rowsrc(const GjDesc *__restrict
 //     m2[i][c] = T[i][c - k0]                                 (the panel's columns)
 // One workgroup per 64 RT rows (wave w: RT row tiles of 16 rows, their W
 // fragments in registers), FP64 16x16x4 matrix cores, the columns in chunks
-// of CW = 32 or 64 (two or four 16-wide tiles):
+// of CW = 32 or 64 (two or four 16-wide tiles; 16 for a pair, whose Q chunk then
+// takes 32 KB of LDS and leaves room for three workgroups a compute unit instead
+// of two: 362 -> 328 us a launch at N = 1024, 64 determinants, 52 TFLOP/s):
 //  * Q chunks go global -> LDS directly (no registers), double-buffered in two
 //    arrays the compiler can tell apart, so the next chunk's copy stays in
 //    flight while the current chunk's products read the other array; each B
@@ -522,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void k_gj_rowsrc(const GjDesc *__restrict
 // that are Q1, q2 the rows Q2.  R2's columns are T2 (the tail below), R1's
 // are written afterwards by k_gj_pair_fix.
 template <int KP, int RT, int CW, bool PAIR = false>
-__global__ __launch_bounds__(kThreads, 2) void k_gj_update(const GjDesc *__restrict__ descs, int np, int nblk, int k0,
+__global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDesc *__restrict__ descs, int np, int nblk, int k0,
                                                         int w) {
     constexpr int NT = CW / 16, RB = 64 * RT;
     constexpr int PIECES = KP * CW / 2;         // 16-byte pieces of one Q chunk
@@ -982,58 +984,59 @@ __global__ __launch_bounds__(kThreads) void k_gj_apply(const GjDesc *__restrict_
 // PAIR form (same notation: R1, R2, P1, P2, T1, T2, Q1, Q2, M1).
 // ---------------------------------------------------------------------------
 
-// After the first panel: R2's columns of M1 = P1 M + (T1 - E1) Q1 become the
-// second panel, and T1 moves to panel_b.  Rows are independent, so each block
-// rewrites the rows it read.  One block per 64 rows.  In the three pair
-// kernels every global load of a thread is issued before its first store (the
-// stores may alias the loads for all the compiler knows, which would otherwise
-// serialise them), and the 64-term products run in two halves of 32 through
-// 32 KB of LDS (three blocks a compute unit instead of two).
-constexpr int kPairLoads = 64 * 64 / kThreads;  // elements of a 64 x 64 tile per thread
-constexpr int kPairHalf = kPairLoads / 2;       // element q holds index grp + 4 q: q < 8 is the first half
+// In the three pair kernels a wave takes 16 of a block's 64 rows (columns in
+// k_gj_pair_q2) and forms the 64-term products on matrix cores, one operand in
+// registers from global memory, the other in LDS.  On the vector units, 16
+// results a thread with one operand broadcast from LDS, the LDS reads bound
+// them.  A matrix-core step adds its four products in ascending order, so each
+// element keeps its chain of multiply-adds.  Per launch (N = 1024, 64
+// determinants), before and after: slab 35 -> 28 us, q2 51 -> 41, fix 56 -> 37.
 
-__global__ __launch_bounds__(kThreads) void k_gj_pair_slab(const GjDesc *__restrict__ descs, int np, int k0) {
-    __shared__ double s_t[32][64];  // (T1 - E1)[r0 + i][l] at s_t[l - 32 h][i], half h of l at a time
-    __shared__ double s_q[32][64];  // Q1[l][R2 column j] at s_q[l - 32 h][j]
+// After the first panel: R2's columns of M1 = P1 M + (T1 - E1) Q1 become the
+// second panel, and T1 moves to panel_b.  One block per 64 rows; a wave rewrites
+// the rows it read.  Transposed (D' = Q1^T (T1 - E1)^T) so that results lie along
+// the column-major panel; operand row m of a tile is column pair_col(m), so that
+// a lane's four results are neighbours in their row of P1 M.
+__device__ __forceinline__ int pair_col(int m) { return 4 * (m & 3) + (m >> 2); }
+constexpr int kPairLd = 80;  // doubles a row of an LDS operand [l][64]: lanes of l and l + 1 in different banks
+__global__ __launch_bounds__(kThreads, 3) void k_gj_pair_slab(const GjDesc *__restrict__ descs, int np, int k0) {
+    __shared__ double s_q[64 * kPairLd];  // Q1[l][R2 column j]
     const GjDesc g = descs[blockIdx.y];
-    const int r0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = lane >> 4;
+    const int row = blockIdx.x * 64 + 16 * wave + lr;
     DSU_GLOBAL const double *m = gmem<const double>(g.m);
     DSU_GLOBAL double *pb = gmem(g.panel_b), *pa = gmem(g.panel);
-    // element q of this thread: column / row a = grp + 4 q, the other index lane
-    double tv[kPairLoads], qv[kPairLoads], acc[16];
-    int qr[kPairLoads];
+    double tv[16], qv[16];
+    int qr[16];
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) qr[q] = g.rowsrc[k0 + grp + 4 * q];
-    // lane = row, 16 columns a thread (one 128-byte line of its row of P1 M)
-    DSU_GLOBAL const double *mr = m + (size_t)g.rowsrc[r0 + lane] * np + k0 + 64 + 16 * grp;
+    for (int q = 0; q < 16; ++q) qr[q] = g.rowsrc[k0 + wave + 4 * q];
+    DSU_GLOBAL const double *mr = m + (size_t)g.rowsrc[row] * np + k0 + 64 + 4 * lk;
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) {
-        tv[q] = pa[(size_t)(grp + 4 * q) * np + r0 + lane];
+    for (int q = 0; q < 16; ++q) {
+        tv[q] = pa[(size_t)(4 * q + lk) * np + row];
         qv[q] = m[(size_t)qr[q] * np + k0 + 64 + lane];
     }
+    f64x4 acc[4];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = mr[q];
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) pb[(size_t)(grp + 4 * q) * np + r0 + lane] = tv[q];
+        for (int i = 0; i < 4; ++i) acc[t][i] = mr[16 * t + i];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h) __syncthreads();  // the first half read by every wave
-#pragma unroll
-        for (int q = kPairHalf * h; q < kPairHalf * (h + 1); ++q) {
-            const int a = grp + 4 * q;
-            s_t[a - 32 * h][lane] = tv[q] - (r0 + lane == k0 + a ? 1.0 : 0.0);
-            s_q[a - 32 * h][lane] = qv[q];
-        }
-        __syncthreads();
-        for (int l = 0; l < 32; ++l) {
-            const double t = s_t[l][lane];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[q] = __builtin_fma(t, s_q[l][16 * grp + q], acc[q]);
-        }
+    for (int q = 0; q < 16; ++q) {
+        pb[(size_t)(4 * q + lk) * np + row] = tv[q];
+        s_q[(wave + 4 * q) * kPairLd + lane] = qv[q];
+        tv[q] -= row == k0 + 4 * q + lk ? 1.0 : 0.0;
     }
-    // column-major stores, coalesced
+    __syncthreads();
+    const double *qp = s_q + lk * kPairLd + pair_col(lr);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) pa[(size_t)(16 * grp + q) * np + r0 + lane] = acc[q];
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = Mma<double>::mma(qp[4 * q * kPairLd + 16 * t], tv[q], acc[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pa[(size_t)(16 * t + 4 * lk + i) * np + row] = acc[t][i];
 }
 
 // After the second panel: rowsrc_b = P2 (its own swaps), rowsrc = P2 P1 (row
@@ -1063,113 +1066,93 @@ __global__ __launch_bounds__(kThreads) void k_gj_pair_rowsrc(const GjDesc *__res
 
 // Q2[j] = M1[P2 row k0 + 64 + j] = M[rowsrc[k0 + 64 + j]] + (T1 - E1)[r_j] Q1,
 // r_j = rowsrc_b[k0 + 64 + j], for all columns (R1's and R2's are not used).
-// One block per 64 columns; loads first and halves of 32, as above.
+// One block per 64 columns.
 __global__ __launch_bounds__(kThreads) void k_gj_pair_q2(const GjDesc *__restrict__ descs, int np, int k0) {
-    __shared__ double s_w[32][64];  // (T1 - E1)[r_j][l] at s_w[l - 32 h][j]
-    __shared__ double s_q[32][64];  // Q1[l][c0 + c] at s_q[l - 32 h][c]
+    __shared__ double s_q[64 * kPairLd];  // Q1[l][c0 + c]
     const GjDesc g = descs[blockIdx.y];
-    const int c0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
+    const int c0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = lane >> 4;
     DSU_GLOBAL const double *m = gmem<const double>(g.m), *pb = gmem<const double>(g.panel_b);
-    double wv[kPairLoads], qv[kPairLoads], acc[16];
-    int qr[kPairLoads], sr[16];
-    const int r = g.rowsrc_b[k0 + 64 + lane];  // r_j of j = lane
+    double wv[16], qv[16];
+    int qr[16], sr[4];
+    const int r = g.rowsrc_b[k0 + 64 + 16 * wave + lr];  // r_j of this lane's operand row
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) qr[q] = g.qrow[grp + 4 * q];
+    for (int q = 0; q < 16; ++q) qr[q] = g.qrow[wave + 4 * q];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) sr[q] = g.rowsrc[k0 + 64 + 16 * grp + q];
+    for (int i = 0; i < 4; ++i) sr[i] = g.rowsrc[k0 + 64 + 16 * wave + lk + 4 * i];
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) {
+    for (int q = 0; q < 16; ++q) {
         qv[q] = m[(size_t)qr[q] * np + c0 + lane];
-        wv[q] = pb[(size_t)(grp + 4 * q) * np + r];
+        wv[q] = pb[(size_t)(4 * q + lk) * np + r];
     }
-    // lane = column, 16 rows of Q2 a thread
+    f64x4 acc[4];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = m[(size_t)sr[q] * np + c0 + lane];
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h) __syncthreads();
+        for (int i = 0; i < 4; ++i) acc[t][i] = m[(size_t)sr[i] * np + c0 + 16 * t + lr];
 #pragma unroll
-        for (int q = kPairHalf * h; q < kPairHalf * (h + 1); ++q) {
-            const int a = grp + 4 * q;
-            s_q[a - 32 * h][lane] = qv[q];
-            s_w[a - 32 * h][lane] = wv[q] - (r == k0 + a ? 1.0 : 0.0);
-        }
-        __syncthreads();
-        for (int l = 0; l < 32; ++l) {
-            const double qq = s_q[l][lane];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[q] = __builtin_fma(s_w[l][16 * grp + q], qq, acc[q]);
-        }
+    for (int q = 0; q < 16; ++q) {
+        s_q[(wave + 4 * q) * kPairLd + lane] = qv[q];
+        wv[q] -= r == k0 + 4 * q + lk ? 1.0 : 0.0;
     }
-    // row-major stores, coalesced
+    __syncthreads();
+    const double *qp = s_q + lk * kPairLd + lr;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) g.q2[(size_t)(16 * grp + q) * np + c0 + lane] = acc[q];
+    for (int q = 0; q < 16; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = Mma<double>::mma(wv[q], qp[4 * q * kPairLd + 16 * t], acc[t]);
+    DSU_GLOBAL double *q2 = gmem(g.q2) + (size_t)(16 * wave + lk) * np + c0 + lr;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q2[(size_t)(4 * i) * np + 16 * t] = acc[t][i];
 }
 
 // R1's columns of the pair's result: m2[i][k0 + j] = (P2 T1)[i][j] +
 // (T2 - E2)[i] (P2 T1)[R2][j] (T1 is M1's R1 block, Q2's R1 columns are its
 // rows at P2's pivots).  Runs after the update, which leaves those columns
-// to it.  One block per 64 rows; loads first, as above.  The 32 KB of LDS
-// first hold (P2 T1) of the block's rows at [i][j ^ i] (an XOR swizzle: the
-// row-wise stores and column-wise reads both spread over the LDS banks), then
-// per half h of l: (T2 - E2)[r0 + i][l] at [l - 32 h][i] in the first 16 KB
-// and (P2 T1)[R2 row l][j] at [l - 32 h][j ^ l] in the second.
+// to it.  One block per 64 rows; the LDS array first holds the block's rows of
+// P2 T1, then R2's, both at [j][row] (rows of 66: column reads spread over the
+// banks).
 __global__ __launch_bounds__(kThreads) void k_gj_pair_fix(const GjDesc *__restrict__ descs, int np, int k0) {
-    __shared__ double s_buf[64 * 64];
+    constexpr int LD = 66;
+    __shared__ double s_x[64 * LD];
     const GjDesc g = descs[blockIdx.y];
-    const int r0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
+    const int r0 = blockIdx.x * 64, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = lane >> 4;
     DSU_GLOBAL const double *pa = gmem<const double>(g.panel), *pb = gmem<const double>(g.panel_b);
-    double av[kPairLoads], x1[kPairLoads], x2[kPairLoads], acc[16];
-    const int rb = g.rowsrc_b[r0 + lane], rz = g.rowsrc_b[k0 + 64 + lane];
+    const int row = r0 + 16 * wave + lr, rb = g.rowsrc_b[r0 + lane], rz = g.rowsrc_b[k0 + 64 + lane];
+    double av[16], x1[16], x2[16];
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) {
-        const int a = grp + 4 * q;
-        av[q] = pa[(size_t)a * np + r0 + lane];
+    for (int q = 0; q < 16; ++q) {
+        const int a = wave + 4 * q;
         x1[q] = pb[(size_t)a * np + rb];
+        av[q] = pa[(size_t)(4 * q + lk) * np + row];
         x2[q] = pb[(size_t)a * np + rz];
     }
 #pragma unroll
-    for (int q = 0; q < kPairLoads; ++q) {
-        const int a = grp + 4 * q;
-        s_buf[lane * 64 + (a ^ lane)] = x1[q];
-    }
+    for (int q = 0; q < 16; ++q) s_x[(wave + 4 * q) * LD + lane] = x1[q];
     __syncthreads();
-    // lane = column, 16 rows a thread
+    f64x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[t][i] = s_x[(16 * t + lr) * LD + 16 * wave + lk + 4 * i];
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-        const int i = 16 * grp + q;
-        acc[q] = s_buf[i * 64 + (lane ^ i)];
+        s_x[(wave + 4 * q) * LD + lane] = x2[q];
+        av[q] -= row == k0 + 64 + 4 * q + lk ? 1.0 : 0.0;
     }
-    double *s_a = s_buf, *s_z = s_buf + 32 * 64;
-    // half h of l (a compile-time constant, so every register index is fixed)
-    auto half = [&](auto h_c) __attribute__((always_inline)) {
-        constexpr int h = decltype(h_c)::value;
-        __syncthreads();  // every wave done with the previous contents
+    __syncthreads();
+    const double *zp = s_x + lr * LD + lk;
 #pragma unroll
-        for (int q = kPairHalf * h; q < kPairHalf * (h + 1); ++q) {
-            const int a = grp + 4 * q;
-            s_a[(a - 32 * h) * 64 + lane] = av[q] - (r0 + lane == k0 + 64 + a ? 1.0 : 0.0);
-        }
-        if ((lane >> 5) == h)
+    for (int q = 0; q < 16; ++q)
 #pragma unroll
-            for (int q = 0; q < kPairLoads; ++q) {
-                const int a = grp + 4 * q;
-                s_z[(lane - 32 * h) * 64 + (a ^ lane)] = x2[q];
-            }
-        __syncthreads();
-#pragma unroll 4
-        for (int l = 0; l < 32; ++l) {
-            const int la = 32 * h + l;
-            const double z = s_z[l * 64 + (lane ^ la)];
+        for (int t = 0; t < 4; ++t) acc[t] = Mma<double>::mma(av[q], zp[16 * t * LD + 4 * q], acc[t]);
+    DSU_GLOBAL double *dst = gmem(g.m2) + (size_t)(r0 + 16 * wave + lk) * np + k0 + lr;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) acc[q] = __builtin_fma(s_a[l * 64 + 16 * grp + q], z, acc[q]);
-        }
-    };
-    half(std::integral_constant<int, 0>{});
-    half(std::integral_constant<int, 1>{});
-    // row-major stores, coalesced
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) g.m2[(size_t)(r0 + 16 * grp + q) * np + k0 + lane] = acc[q];
+        for (int i = 0; i < 4; ++i) dst[(size_t)(4 * i) * np + 16 * t] = acc[t][i];
 }
 
 template <int RT, int CW>
@@ -1252,7 +1235,7 @@ hipError_t launch_gj_invert(const GjDesc *set_a, const GjDesc *set_b, int ndesc,
             factor(cur, k0 + 64, 64, false);
             hipLaunchKernelGGL(k_gj_pair_rowsrc, dim3(ndesc), dim3(kThreads), (size_t)np * sizeof(int), s, cur, np, k0);
             hipLaunchKernelGGL(k_gj_pair_q2, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
-            hipLaunchKernelGGL((k_gj_update<128, 1, 32, true>), dim3(ndesc * (np / 64)), dim3(kThreads), 0, s, cur, np,
+            hipLaunchKernelGGL((k_gj_update<128, 1, 16, true>), dim3(ndesc * (np / 64)), dim3(kThreads), 0, s, cur, np,
                                np / 64, k0, 64);
             hipLaunchKernelGGL(k_gj_pair_fix, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
             k0 += 128;
