@@ -524,8 +524,8 @@ __global__ __launch_bounds__(kThreads) void k_gj_rowsrc(const GjDesc *__restrict
 // that are Q1, q2 the rows Q2.  R2's columns are T2 (the tail below), R1's
 // are written afterwards by k_gj_pair_fix.
 template <int KP, int RT, int CW, bool PAIR = false>
-__global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDesc *__restrict__ descs, int np, int nblk, int k0,
-                                                        int w) {
+__global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDesc *__restrict__ descs, int np,
+                                                                      int nblk, int parts, int k0, int w) {
     constexpr int NT = CW / 16, RB = 64 * RT;
     constexpr int PIECES = KP * CW / 2;         // 16-byte pieces of one Q chunk
     constexpr int IPW = PIECES / kThreads;      // direct copies per wave per chunk (64 pieces each)
@@ -534,7 +534,11 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
     __shared__ __attribute__((aligned(16))) double q_even[KP * CW];
     __shared__ __attribute__((aligned(16))) double q_odd[KP * CW];
     const int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int d = b / nblk, r0 = (b % nblk) * RB;
+    const int d = b / (nblk * parts), r0 = (b % nblk) * RB;
+    // this workgroup's columns: a part of whole chunk pairs
+    const int cols = (np / (2 * CW) + parts - 1) / parts * (2 * CW), cbeg = b / nblk % parts * cols;
+    const int cend = cbeg + cols < np ? cbeg + cols : np;
+    if (cbeg >= cend) return;
     const GjDesc g = descs[d];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = lane >> 4;
     DSU_GLOBAL const double *msrc = gmem(g.m);
@@ -604,15 +608,15 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
         }
     typedef Mma<double>::acc_t acc_set[RT][NT];
     acc_set acc_e, acc_o;
-    copy_q(0, q_even);
+    copy_q(cbeg, q_even);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc_e[rt][t][i] = src[rt][i][16 * t];
+            for (int i = 0; i < 4; ++i) acc_e[rt][t][i] = src[rt][i][cbeg + 16 * t];
     // chunk c0 runs its products on `cur` (loaded with its source rows) and Q
-    // in q_cur; `oth` holds chunk c0 - CW's results (c0 > 0), is stored, and
+    // in q_cur; `oth` holds chunk c0 - CW's results (c0 > cbeg), is stored, and
     // takes chunk c0 + CW's source rows (the last chunk re-reads its own rows,
     // so the load is unconditional)
     auto chunk = [&](int c0, const double *q_cur, double *q_nxt, acc_set &cur, acc_set &oth)
@@ -621,7 +625,7 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
         // and with them for everything issued before); every wave is done
         // reading q_nxt
         __syncthreads();
-        if (c0 > 0)
+        if (c0 > cbeg)
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -629,8 +633,8 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
 #pragma unroll
                     for (int i = 0; i < 4; ++i) dst[rt][i][c0 - CW + 16 * t] = oth[rt][t][i];
         const int c1 = c0 + CW;
-        if (c1 < np) copy_q(c1, q_nxt);
-        const int cl = c1 < np ? c1 : c0;
+        if (c1 < cend) copy_q(c1, q_nxt);
+        const int cl = c1 < cend ? c1 : c0;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -650,7 +654,7 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
     };
     // np is a multiple of 2 CW (the launcher's choice of CW): chunks come in
     // pairs, and the loop body is straight-line code over fixed register sets
-    for (int c0 = 0; c0 < np; c0 += 2 * CW) {
+    for (int c0 = cbeg; c0 < cend; c0 += 2 * CW) {
         chunk(c0, q_even, q_odd, acc_e, acc_o);
         chunk(c0 + CW, q_odd, q_even, acc_o, acc_e);
     }
@@ -659,12 +663,13 @@ __global__ __launch_bounds__(kThreads, PAIR ? 3 : 2) void k_gj_update(const GjDe
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dst[rt][i][np - CW + 16 * t] = acc_o[rt][t][i];
+            for (int i = 0; i < 4; ++i) dst[rt][i][cend - CW + 16 * t] = acc_o[rt][t][i];
     // The panel's columns (a pair's second panel): the lane that stored each of
     // them overwrites it with the factored panel (same thread, same address:
     // program order holds).
     const int tk0 = PAIR ? k0 + KP / 2 : k0, tw = PAIR ? KP / 2 : w;
-    for (int c0 = tk0 - tk0 % CW; c0 < tk0 + tw; c0 += CW)
+    const int tbeg = tk0 - tk0 % CW, tend = tk0 + tw < cend ? tk0 + tw : cend;
+    for (int c0 = tbeg > cbeg ? tbeg : cbeg; c0 < tend; c0 += CW)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int c = c0 + 16 * t + lr;
@@ -1155,13 +1160,28 @@ __global__ __launch_bounds__(kThreads) void k_gj_pair_fix(const GjDesc *__restri
         for (int i = 0; i < 4; ++i) dst[(size_t)(4 * i) * np + 16 * t] = acc[t][i];
 }
 
+// Column parts of an update launch: doubled while the launch has fewer than 512
+// workgroups (two a compute unit) and a part keeps 128 columns or more.  One part
+// left most units idle for few determinants.  An inverse, one part and so: N =
+// 1024, one determinant 3.08 -> 2.53 ms, 4 of them 3.17 -> 2.70; N = 2048, one 8.65
+// -> 6.49, 4 9.07 -> 7.77; N = 4096, 2 29.6 -> 23.7; from 512 workgroups on nothing
+// changes (N = 1024, 64: 6.4 ms).
+static int gj_update_parts(int ndesc, int np) {
+    int parts = 1;
+    while (ndesc * (np / 64) * parts < 512 && np / (2 * parts) >= 128) parts *= 2;
+    return parts;
+}
+
 template <int RT, int CW>
 static void launch_gj_update(const GjDesc *descs_dev, int ndesc, int np, int nb, int k0, int w, hipStream_t s) {
-    const int nblk = np / (64 * RT);
-    const dim3 grid(ndesc * nblk);
-    if (nb == 16) hipLaunchKernelGGL((k_gj_update<16, RT, CW>), grid, dim3(kThreads), 0, s, descs_dev, np, nblk, k0, w);
-    else if (nb == 32) hipLaunchKernelGGL((k_gj_update<32, RT, CW>), grid, dim3(kThreads), 0, s, descs_dev, np, nblk, k0, w);
-    else hipLaunchKernelGGL((k_gj_update<64, RT, CW>), grid, dim3(kThreads), 0, s, descs_dev, np, nblk, k0, w);
+    const int nblk = np / (64 * RT), parts = gj_update_parts(ndesc, np);
+    const dim3 grid(ndesc * nblk * parts);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, descs_dev, np, nblk, parts, k0, w);
+    };
+    if (nb == 16) launch(k_gj_update<16, RT, CW>);
+    else if (nb == 32) launch(k_gj_update<32, RT, CW>);
+    else launch(k_gj_update<64, RT, CW>);
 }
 
 // Factor the panel [k0, k0 + w); gather = false: the panel buffer already
@@ -1235,8 +1255,9 @@ hipError_t launch_gj_invert(const GjDesc *set_a, const GjDesc *set_b, int ndesc,
             factor(cur, k0 + 64, 64, false);
             hipLaunchKernelGGL(k_gj_pair_rowsrc, dim3(ndesc), dim3(kThreads), (size_t)np * sizeof(int), s, cur, np, k0);
             hipLaunchKernelGGL(k_gj_pair_q2, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
-            hipLaunchKernelGGL((k_gj_update<128, 1, 16, true>), dim3(ndesc * (np / 64)), dim3(kThreads), 0, s, cur, np,
-                               np / 64, k0, 64);
+            const int parts = gj_update_parts(ndesc, np);
+            hipLaunchKernelGGL((k_gj_update<128, 1, 16, true>), dim3(ndesc * (np / 64) * parts), dim3(kThreads), 0, s,
+                               cur, np, np / 64, parts, k0, 64);
             hipLaunchKernelGGL(k_gj_pair_fix, dim3(np / 64, ndesc), dim3(kThreads), 0, s, cur, np, k0);
             k0 += 128;
         } else {

@@ -180,3 +180,22 @@ def test_flush_forms_agree(n, K, walkers):
     many, few = run(list(range(walkers))), run([0, 1, 2])
     for a, b in zip(many, few):
         assert a[:3] == b[:3] and np.array_equal(a[3], b[3])
+
+
+# Recomputes: the update's column parts by the number of determinants (np = 256, 320
+# ragged in thirds, 512, 1024: 2 to 8 parts for one determinant, one part from 512
+# workgroups on); a determinant's inverse does not depend on its company.
+@pytest.mark.parametrize("n,many", [(250, 128), (300, 103), (512, 64), (1024, 32)])
+def test_recompute_parts_agree(n, many):
+    require_gpu()
+    pos = np.stack([inputs.positions(21, w, n, 10.0) for w in range(many)])
+
+    def run(count):
+        with dsu.Batch(n, pos[:count], [21] * count, list(range(count)), 0.1, 16, precision=dsu.FP64, box_l=10.0) as b:
+            st = b.stats()
+            return st["logdet"][0], st["sign"][0], b.inverse(0)
+
+    one, all_ = run(1), run(many)
+    assert one[:2] == all_[:2] and np.array_equal(one[2], all_[2])
+    kv = dsu.plane_wave_rows(n, 10.0, pos[0])
+    assert np.abs(one[2] @ kv - np.eye(n)).max() <= 1e-16 * n * np.linalg.cond(kv)
