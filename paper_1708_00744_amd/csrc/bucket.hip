@@ -228,14 +228,18 @@ int Bucket::set_dets(const std::vector<DetSlot> &d) {
 int Bucket::set_delay(int k) {
     if (k < 1 || k > sh.kmax) return fail(DSU_EINVAL, "delay %d outside [1, %d] of this batch", k, sh.kmax);
     HIPCHK(hipStreamSynchronize(stream));
+    if (side) HIPCHK(hipStreamSynchronize(side));
     K = k;
     drop_graph();
     return DSU_OK;
 }
 
 void Bucket::drop_graph() {
-    // a launched graph may still be running: destroy it only once the stream has drained
-    if ((gexec_ || graph_) && stream) (void)hipStreamSynchronize(stream);
+    // a launched graph may still be running: destroy it only once its streams have drained
+    if (gexec_ || graph_) {
+        if (stream) (void)hipStreamSynchronize(stream);
+        if (side) (void)hipStreamSynchronize(side);
+    }
     if (gexec_) (void)hipGraphExecDestroy(gexec_);
     if (graph_) (void)hipGraphDestroy(graph_);
     gexec_ = nullptr;

@@ -132,8 +132,10 @@ __device__ __forceinline__ void window_rows(const DetDesc<T> &d, const RowsArgs 
         }
     }
     __syncthreads();
-    const int cols = np / parts;
-    const int c_begin = part * cols;
+    // this part's groups of 64 columns
+    const int g_begin = (np >> 6) * part / parts, ng = (np >> 6) * (part + 1) / parts - g_begin;
+    const int cols = 64 * ng, c_begin = 64 * g_begin;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     T *uo = buf ? d.u2 : d.u;
     T *vo = buf ? d.vg2 : d.vg;
     if (nmax > kPwTab) {
@@ -160,17 +162,22 @@ __device__ __forceinline__ void window_rows(const DetDesc<T> &d, const RowsArgs 
             s_s[(3 * a + ax) * nt + m] = sn;
         }
         __syncthreads();
-        if (cols == kThreads) {
-            // one column per thread (uniform): its plane wave decoded once, the
-            // group's proposals unrolled into independent chains; the same
-            // operations per orbital as below
-            const int c = c_begin + tid;
+        // a wave takes 64 columns, one a lane, its plane wave decoded once, and
+        // the group's proposals (all of them, or 8 where the columns do not spread
+        // evenly over the waves) unrolled into independent chains.  (Element by
+        // element, each decoding its plane wave, sizes that are no multiple of 256
+        // took 48 us a launch against 36 at n = 1400, K = 64, 16 determinants, 50
+        // against 41 at n = 700, 60 of them.)
+        const int step = ng % 4 ? 8 : ga, chunks = (ga + step - 1) / step;
+        for (int u = wave; u < ng * chunks; u += kThreads / 64) {
+            const int c = c_begin + 64 * (u / chunks) + lane, a_begin = step * (u % chunks);
+            const int a_end = min(a_begin + step, ga);
             const bool live = c < n;
             const int4 kv = live ? kvec[c] : make_int4(0, 0, 0, 0);
             const int mm[3] = {kv.x < 0 ? -kv.x : kv.x, kv.y < 0 ? -kv.y : kv.y, kv.z < 0 ? -kv.z : kv.z};
-            const bool ng[3] = {kv.x < 0, kv.y < 0, kv.z < 0};
+            const bool ng3[3] = {kv.x < 0, kv.y < 0, kv.z < 0};
 #pragma unroll 4
-            for (int a = 0; a < ga; ++a) {
+            for (int a = a_begin; a < a_end; ++a) {
                 const int ag = a0 + a;
                 T val = T(0), vgv = T(0);
                 if (ag < kw) {
@@ -181,7 +188,7 @@ __device__ __forceinline__ void window_rows(const DetDesc<T> &d, const RowsArgs 
 #pragma unroll
                             for (int ax = 0; ax < 3; ++ax) {
                                 const int at = (3 * a + ax) * nt + mm[ax];
-                                const double fc = s_c[at], fs = ng[ax] ? -s_s[at] : s_s[at];
+                                const double fc = s_c[at], fs = ng3[ax] ? -s_s[at] : s_s[at];
                                 const double t = re * fc - im * fs;
                                 im = re * fs + im * fc;
                                 re = t;
@@ -195,35 +202,6 @@ __device__ __forceinline__ void window_rows(const DetDesc<T> &d, const RowsArgs 
                 uo[(size_t)ag * np + c] = val;
                 if (copy_vg) vo[(size_t)ag * np + c] = vgv;
             }
-            continue;
-        }
-        for (int v = tid; v < ga * cols; v += kThreads) {
-            const int a = v / cols, c = c_begin + v % cols, ag = a0 + a;
-            T val = T(0), vgv = T(0);
-            if (ag < kw) {
-                if (c < n) {
-                    const int4 kv = kvec[c];
-                    double o = 1.0;
-                    if (kv.w != 0) {
-                        const int ax_n[3] = {kv.x, kv.y, kv.z};
-                        double re = 1.0, im = 0.0;
-#pragma unroll
-                        for (int ax = 0; ax < 3; ++ax) {
-                            const int m = ax_n[ax] < 0 ? -ax_n[ax] : ax_n[ax];
-                            const double fc = s_c[(3 * a + ax) * nt + m];
-                            const double fs = ax_n[ax] < 0 ? -s_s[(3 * a + ax) * nt + m] : s_s[(3 * a + ax) * nt + m];
-                            const double t = re * fc - im * fs;
-                            im = re * fs + im * fc;
-                            re = t;
-                        }
-                        o = kv.w == 1 ? re : im;
-                    }
-                    val = T(o);
-                }
-                if (copy_vg) vgv = d.bt[(size_t)(e0 + ag) * np + c];
-            }
-            uo[(size_t)ag * np + c] = val;
-            if (copy_vg) vo[(size_t)ag * np + c] = vgv;
         }
     }
 }
@@ -234,13 +212,8 @@ __global__ __launch_bounds__(kThreads) void k_window_rows(const DetDesc<T> *__re
     window_rows(d, ra, blockIdx.y, gridDim.y);
 }
 
-// Blocks a determinant's rows are split over, and a block's LDS.
-static int rows_parts(int np) {
-    int parts = np / 256;
-    if (parts < 1) parts = 1;
-    while (np % parts) --parts;
-    return parts;
-}
+// Blocks a determinant's rows are split over (256 columns each or a little more), and a block's LDS.
+static int rows_parts(int np) { return np < 512 ? 1 : np / 256; }
 static size_t rows_lds(int ktile, int nmax) {
     return sizeof(double) * (3 * ktile + (nmax <= kPwTab ? 6 * kPwGroup * (nmax + 1) : 0));
 }

@@ -199,3 +199,19 @@ def test_recompute_parts_agree(n, many):
     assert one[:2] == all_[:2] and np.array_equal(one[2], all_[2])
     kv = dsu.plane_wave_rows(n, 10.0, pos[0])
     assert np.abs(one[2] @ kv - np.eye(n)).max() <= 1e-16 * n * np.linalg.cond(kv)
+
+
+# Proposal rows: column groups of 64 over the blocks and waves (np = 192: three groups
+# on four waves; 320: five; 576: two blocks of four and five), short last windows.
+@pytest.mark.parametrize("n,K", [(130, 16), (300, 32), (520, 64)])
+def test_rows_splits_match_oracle(n, K):
+    require_gpu()
+    pos = inputs.positions(31, 0, n, 10.0)
+    with dsu.Batch(n, pos[None], [31], [0], 0.3, K, precision=dsu.FP64, box_l=10.0) as b:
+        b.set_trace(1)
+        b.sweep(1)
+        r, acc = b.trace(0)
+    t = oracle.walker_run(n, 10.0, 31, 0, 0, 0.3, pos, 1)
+    assert np.array_equal(acc, t.accepted)
+    # ratios: FP64 sums of n terms through an inverse of condition ~1e4 at most, absolute below 1e-2
+    assert (np.abs(r - t.ratio) / np.maximum(np.abs(t.ratio), 1e-2)).max() < 1e-8
