@@ -368,12 +368,12 @@ def c3_batched(cache, burn, n=512, walkers=512, K=32, sweeps=100, recompute_ever
 
 def walker_propose(n=4096, K=128, moves=256):
     """The host-driven walker's look-ahead ratio (eq. (3)) as its own launch:
-    k_walker_propose reads the stale column BT[e, :] and the k pending rows of
+    k_lookahead reads the stale column BT[e, :] and the k pending rows of
     U and Vg, (2k + 1) n s bytes at k pending moves (s = 4 in FP32).  An FP32
     walker of N = 4096 with K = 128, rows already on the device, every move
     accepted (so k runs 0..127 in each window).  HIP events on the walker's
-    stream bracket each dsu_propose_ratio_dev (the row's conversion and the
-    look-ahead kernel; the host's wait is outside them): achieved algorithmic
+    stream bracket each dsu_propose_ratio_dev (the look-ahead kernel; the
+    host's wait is outside them): achieved algorithmic
     bytes per second over all proposals, against HBM."""
     import torch
     from paper_1708_00744_amd import dsu, inputs
@@ -400,7 +400,7 @@ def walker_propose(n=4096, K=128, moves=256):
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
     gpu_s = sum(a.elapsed_time(b) for a, b in ev) / 1e3
-    return {"kernel": "k_walker_propose<float>", "n": n, "K": K, "proposals": moves,
+    return {"kernel": "k_lookahead<float>", "n": n, "K": K, "proposals": moves,
             "algorithmic_bytes": nbytes, "gpu_ms_per_proposal": 1e3 * gpu_s / moves,
             "achieved_GBps": nbytes / gpu_s / 1e9, "frac_of_hbm_peak": nbytes / gpu_s / 1e9 / PEAK_HBM,
             "wall_moves_per_s": moves / wall,

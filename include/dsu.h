@@ -347,10 +347,11 @@ int dsu_batch_set_residual_watchdog(dsu_batch *b, int32_t samples, double thresh
  * single 64-column panels where fewer than 128 columns remain or the padded
  * n exceeds 4096), chunk = columns of the single-panel trailing update per
  * step (32, or 64 when n rounded up to a multiple of 64 is a multiple of
- * 128; a pair's update takes 32), apply_columns = 1 or 4 (accepted and
+ * 128; a pair's update takes 16), apply_columns = 1 or 4 (accepted and
  * reported back; the update of a panel's columns after each group of pivots
  * is one kernel for every n, so it has no effect).  0 keeps the built-in
- * choice for this n.  Results agree to FP64 rounding whatever the choice.  Waits for the batch's stream; DSU_EINVAL for other values. */
+ * choice for this n.  Results agree to FP64 rounding whatever the choice.
+ * Waits for the batch's stream; DSU_EINVAL for other values. */
 int dsu_batch_set_recompute_tiles(dsu_batch *b, int32_t panel, int32_t chunk, int32_t apply_columns);
 /* The blocking in use (any output may be NULL). */
 int dsu_batch_get_recompute_tiles(dsu_batch *b, int32_t *panel, int32_t *chunk, int32_t *apply_columns);
