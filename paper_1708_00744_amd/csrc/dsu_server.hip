@@ -83,12 +83,12 @@ struct Resident {
     double admit_s = 0.0, last_s = 0.0;
     int result_index = -1;
     int status = DSU_OK;  // DSU_ESINGULAR once an inverse of the walker came out singular
+    bool started = false; // its first inverses are on the bucket's stream (start_fresh)
 };
 
 struct BucketState {
     Bucket bk;
     std::vector<int> members;  // slot ids, in descriptor order
-    int fresh = 0;             // determinants at the end of the list that have no inverse yet
     bool busy = false;
     bool dirty = false;
     hipEvent_t done = nullptr;
@@ -168,8 +168,8 @@ static int refresh_bucket(dsu_server *s, BucketState *b) {
 }
 
 // Place one request in the arena and in its bucket (which must be idle), its
-// state uploaded in stream order; start_fresh must follow before the bucket's
-// next sweep, and r.positions stay valid until then.  DSU_EBUDGET if it does not
+// state uploaded in stream order; start_fresh follows before the call that
+// placed it returns, and r.positions stay valid until then.  DSU_EBUDGET if it does not
 // fit now.
 static int place(dsu_server *s, const dsu_request &r, double now_s, int result_index, int *slot_out) {
     if (r.n < 1 || r.n > 32768 || (r.spins != 1 && r.spins != 2) || r.sweeps < 0 || !r.positions)
@@ -201,41 +201,34 @@ static int place(dsu_server *s, const dsu_request &r, double now_s, int result_i
     w.result_index = result_index;
     char *base = s->arena_base + off;
     hipStream_t st = b->bk.stream;
-    HIPCHK(hipMemsetAsync(base, 0, bytes, st));
     static const DetState init{0.0, 1, 0, 0, 0, 0};
-    for (int sp = 0; sp < r.spins; ++sp) {
-        DetSlot d = sh.carve(base + sh.det_bytes() * sp);
-        d.seed = r.seed;
-        d.wid = r.request_id;
-        d.sigma = r.sigma;
-        d.spin = sp;
-        HIPCHK(hipMemcpyAsync(d.pos, r.positions + (size_t)sp * r.n * 3, sizeof(double) * r.n * 3,
-                              hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(d.st, &init, sizeof(DetState), hipMemcpyHostToDevice, st));
-        w.dets.push_back(d);
+    auto upload = [&]() -> int {
+        HIPCHK(hipMemsetAsync(base, 0, bytes, st));
+        for (int sp = 0; sp < r.spins; ++sp) {
+            DetSlot d = sh.carve(base + sh.det_bytes() * sp);
+            d.seed = r.seed;
+            d.wid = r.request_id;
+            d.sigma = r.sigma;
+            d.spin = sp;
+            HIPCHK(hipMemcpyAsync(d.pos, r.positions + (size_t)sp * r.n * 3, sizeof(double) * r.n * 3,
+                                  hipMemcpyHostToDevice, st));
+            HIPCHK(hipMemcpyAsync(d.st, &init, sizeof(DetState), hipMemcpyHostToDevice, st));
+            w.dets.push_back(d);
+        }
+        return DSU_OK;
+    };
+    rc = upload();
+    if (rc != DSU_OK) {
+        (void)hipStreamSynchronize(st);  // what was enqueued reads the caller's array and writes the arena
+        s->arena.release(off, bytes);
+        return rc;
     }
     const int slot = s->next_slot++;
     s->resident[slot] = w;
     b->members.push_back(slot);
     b->dirty = true;
-    b->fresh += r.spins;
     if (slot_out) *slot_out = slot;
     return DSU_OK;
-}
-
-// FP64 inverses of the determinants placed since the last call, all of them in
-// as few passes as the workspace allows, enqueued ahead of the bucket's next
-// sweep; a singular start is reported when that sweep completes.  (One pass per
-// request, each waiting for the one before, took half of the time of 24
-// saturating requests: the panel chains of buckets of different n, which run
-// side by side, and of a bucket's own requests were done one after the other.)
-static int start_fresh(dsu_server *s, BucketState *b) {
-    if (!b->fresh) return DSU_OK;
-    CHK(refresh_bucket(s, b));  // waits for the uploads
-    std::vector<int> which;
-    for (int i = (int)b->bk.dets.size() - b->fresh; i < (int)b->bk.dets.size(); ++i) which.push_back(i);
-    b->fresh = 0;
-    return b->bk.recompute_async(which);
 }
 
 static int read_result(dsu_server *s, int slot, dsu_result *out) {
@@ -284,6 +277,44 @@ static void retire(dsu_server *s, int slot) {
         it->second->dirty = true;
     }
     s->resident.erase(slot);
+}
+
+// FP64 inverses of a bucket's walkers that have none yet, all of them in as few
+// passes as the workspace allows, enqueued ahead of the bucket's next sweep; a
+// singular start is reported when that sweep completes.  (One pass per request,
+// each waiting for the one before, took half of the time of 24 saturating
+// requests: the panel chains of buckets of different n, which run side by side,
+// and of a bucket's own requests were done one after the other.)  On an error
+// those walkers leave the pool: a resident walker always has its inverses.
+// Either way the caller's arrays are read to the end.
+static int start_fresh(dsu_server *s, BucketState *b) {
+    std::vector<int> which, slots;
+    int pos = 0;
+    for (int slot : b->members) {
+        const Resident &w = s->resident[slot];
+        if (!w.started) slots.push_back(slot);
+        for (int sp = 0; sp < w.spins; ++sp, ++pos)
+            if (!w.started) which.push_back(pos);
+    }
+    if (which.empty()) return DSU_OK;
+    int rc = refresh_bucket(s, b);  // waits for the uploads
+    if (rc == DSU_OK) rc = b->bk.recompute_async(which);
+    if (rc != DSU_OK) (void)hipStreamSynchronize(b->bk.stream);
+    for (int slot : slots) {
+        if (rc == DSU_OK) s->resident[slot].started = true;
+        else retire(s, slot);
+    }
+    return rc;
+}
+
+// start_fresh for every bucket; the first error, after all were tried.
+static int start_all_fresh(dsu_server *s) {
+    int first = DSU_OK;
+    for (auto &kv : s->buckets) {
+        const int rc = start_fresh(s, kv.second.get());
+        if (first == DSU_OK) first = rc;
+    }
+    return first;
 }
 
 // After a completed sweep of bucket b: recompute the walkers that are due.
@@ -379,8 +410,7 @@ extern "C" int dsu_server_add(dsu_server *s, const dsu_request *req, int32_t *sl
     BucketState *b = s->buckets[req->n].get();
     const int rc = start_fresh(s, b);
     if (rc != DSU_OK) {
-        b->fresh = 0;
-        retire(s, slot);
+        drop_empty_buckets(s);
         return rc;
     }
     HIPCHK(hipStreamSynchronize(b->bk.stream));
@@ -398,6 +428,7 @@ extern "C" int dsu_server_step(dsu_server *s) {
     if (!s) return fail(DSU_EINVAL, "server is NULL");
     for (auto &kv : s->buckets) {
         BucketState *b = kv.second.get();
+        CHK(start_fresh(s, b));
         if (b->dirty) CHK(refresh_bucket(s, b));
         if (b->members.empty()) continue;
         CHK(b->bk.sweep(0));
@@ -491,7 +522,9 @@ extern "C" int dsu_server_run(dsu_server *s, const dsu_request *reqs, int32_t co
             CHK(recompute_due(s, b));
         }
         drop_empty_buckets(s);
-        // admission, first fit in arrival order, into idle buckets
+        // admission, first fit in arrival order, into idle buckets; a request that
+        // is refused ends the run, and those placed before it stay resident
+        int refused = DSU_OK;
         for (auto it = waiting.begin(); it != waiting.end();) {
             const dsu_request &r = reqs[*it];
             auto bit = s->buckets.find(r.n);
@@ -513,13 +546,14 @@ extern "C" int dsu_server_run(dsu_server *s, const dsu_request *reqs, int32_t co
                 continue;
             }
             if (rc != DSU_OK) {
-                for (auto &kv : s->buckets) (void)hipStreamSynchronize(kv.second->bk.stream);  // uploads of the caller's arrays
-                return rc;
+                refused = rc;
+                break;
             }
             it = waiting.erase(it);
         }
-        for (auto &kv : s->buckets)
-            if (!kv.second->busy) CHK(start_fresh(s, kv.second.get()));
+        const int fresh_rc = start_all_fresh(s);
+        CHK(refused);
+        CHK(fresh_rc);
         // launch the next sweep of every idle, non-empty bucket
         bool any_busy = false;
         for (auto &kv : s->buckets) {

@@ -1,0 +1,60 @@
+"""The serving pool where a call ends early or a walker leaves between sweeps:
+the walkers that stay give the numbers they give alone, bit for bit."""
+import pytest
+
+from gpu_util import require_gpu
+from paper_1708_00744_amd import dsu, inputs
+
+pytestmark = pytest.mark.gpu
+
+L, K = 10.0, 16
+
+
+def request(rid, n, spins=1, sweeps=3, arrival_s=0.0, sigma=0.2):
+    pos = inputs.positions(17, rid, spins * n, L).reshape(spins, n, 3)
+    return {"request_id": rid, "n": n, "spins": spins, "seed": 17, "sigma": sigma, "sweeps": sweeps,
+            "arrival_s": arrival_s, "positions": pos}
+
+
+def add(server, r):
+    return server.add(r["request_id"], r["n"], r["spins"], r["seed"], r["sigma"], r["sweeps"], r["positions"])
+
+
+def pool(prec, recompute_every=0):
+    return dsu.Server(K, precision=prec, box_l=L, budget_bytes=1 << 30, recompute_every=recompute_every)
+
+
+def alone(prec, r, sweeps, recompute_every=0):
+    with pool(prec, recompute_every) as s:
+        slot = add(s, r)
+        for _ in range(sweeps):
+            s.step()
+        return s.result(slot, remove=True)
+
+
+def numbers(result):
+    return {q: result[q] for q in ("request_id", "status", "sweeps_done", "logdet", "sign", "accepted")}
+
+
+@pytest.mark.parametrize("prec", [dsu.FP64, dsu.FP32_MIXED])
+@pytest.mark.parametrize("bad", [{"spins": 3}, {"sweeps": -1}])
+def test_refused_run_leaves_walkers_with_their_inverses(prec, bad):
+    """A request that is refused ends the run; those placed before it stay
+    resident, are swept by later steps and leave or are joined as any other."""
+    require_gpu()
+    reqs = [request(1, 96), request(2, 96, spins=2), request(3, 64)]
+    with pool(prec) as s:
+        with pytest.raises(dsu.DsuError) as ex:
+            s.run(reqs + [request(4, 80, **bad)])
+        assert ex.value.code == dsu.EINVAL
+        assert s.usage()[1] == 3
+        s.step()
+        gone = s.result(0, remove=True)
+        late = request(5, 96)
+        slot = add(s, late)
+        s.step()
+        rest = [s.result(q, remove=True) for q in (1, 2, slot)]
+        assert s.usage() == (0, 0)
+    assert numbers(gone) == numbers(alone(prec, reqs[0], 1))
+    for got, r, sweeps in zip(rest, reqs[1:] + [late], (2, 2, 1)):
+        assert numbers(got) == numbers(alone(prec, r, sweeps))
