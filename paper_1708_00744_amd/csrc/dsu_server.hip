@@ -320,6 +320,9 @@ static int start_all_fresh(dsu_server *s) {
 // After a completed sweep of bucket b: recompute the walkers that are due.
 static int recompute_due(dsu_server *s, BucketState *b) {
     if (s->recompute_every <= 0) return DSU_OK;
+    // positions count the members, so those that left at this boundary leave the
+    // descriptors first: their memory may already be another walker's
+    if (b->dirty) CHK(refresh_bucket(s, b));
     std::vector<int> which;
     int pos = 0;
     for (int slot : b->members) {

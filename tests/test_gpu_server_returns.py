@@ -58,3 +58,19 @@ def test_refused_run_leaves_walkers_with_their_inverses(prec, bad):
     assert numbers(gone) == numbers(alone(prec, reqs[0], 1))
     for got, r, sweeps in zip(rest, reqs[1:] + [late], (2, 2, 1)):
         assert numbers(got) == numbers(alone(prec, r, sweeps))
+
+
+@pytest.mark.parametrize("prec", [dsu.FP64, dsu.FP32_MIXED])
+def test_recompute_where_another_walker_leaves(prec):
+    """Recomputes every three sweeps; the walker first in the list leaves at the
+    sweep after which the others are due.  The inverse a recompute gives differs
+    from the updated one by rounding, so the numbers after further sweeps tell
+    whether it took place, and on which walker."""
+    require_gpu()
+    reqs = [request(11, 96, spins=2, sweeps=3), request(12, 96, sweeps=7), request(13, 96, spins=2, sweeps=7)]
+    with pool(prec, recompute_every=3) as s:
+        results, _ = s.run(reqs)
+        assert s.usage() == (0, 0)
+    for got, r in zip(results, reqs):
+        assert numbers(got) == numbers(alone(prec, r, r["sweeps"], recompute_every=3))
+    assert alone(prec, reqs[1], 7)["logdet"] != results[1]["logdet"]  # the recomputes show in the numbers
