@@ -456,6 +456,12 @@ extern "C" int dsu_server_result(dsu_server *s, int32_t slot, dsu_result *out, i
     const int n = s->resident[slot].n;
     auto it = s->buckets.find(n);
     if (it != s->buckets.end() && it->second->busy) return fail(DSU_ESTATE, "bucket busy");
+    // a step leaves its recomputes on the stream: they set the state read here
+    // and write the memory a removal gives back
+    if (it != s->buckets.end()) {
+        HIPCHK(hipStreamSynchronize(it->second->bk.stream));
+        (void)flag_singular(s, it->second.get());
+    }
     CHK(read_result(s, slot, out));
     if (remove) {
         retire(s, slot);

@@ -1,5 +1,7 @@
 """The serving pool where a call ends early or a walker leaves between sweeps:
 the walkers that stay give the numbers they give alone, bit for bit."""
+import time
+
 import pytest
 
 from gpu_util import require_gpu
@@ -74,3 +76,22 @@ def test_recompute_where_another_walker_leaves(prec):
     for got, r in zip(results, reqs):
         assert numbers(got) == numbers(alone(prec, r, r["sweeps"], recompute_every=3))
     assert alone(prec, reqs[1], 7)["logdet"] != results[1]["logdet"]  # the recomputes show in the numbers
+
+
+def test_result_after_a_step_with_a_recompute():
+    """The step's recompute takes milliseconds at this size; the result read
+    right after the step is the one read later, and the walker can leave."""
+    require_gpu()
+    r = request(21, 1024, sweeps=4, sigma=0.05)
+    with pool(dsu.FP32_MIXED, recompute_every=1) as s:
+        slot = add(s, r)
+        s.step()
+        first = s.result(slot)
+        time.sleep(0.2)
+        assert numbers(s.result(slot)) == numbers(first)
+        s.step()
+        last = s.result(slot, remove=True)
+        slot = add(s, r)  # the same memory again
+        s.step()
+        assert numbers(s.result(slot)) == numbers(first)
+    assert numbers(last) == numbers(alone(dsu.FP32_MIXED, r, 2, recompute_every=1))
