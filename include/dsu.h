@@ -454,7 +454,10 @@ int dsu_server_usage(dsu_server *s, size_t *used_bytes, int32_t *resident_walker
  * admission never waits for them).  sweep_latency_ms (optional,
  * capacity latency_cap) receives every per-walker sweep latency: the time
  * between consecutive sweep completions of a walker (the first measured from
- * its admission); *latency_count is the number written. */
+ * its admission); *latency_count is the number written.  DSU_ESTATE with
+ * resident walkers.  A malformed request ends the run with DSU_EINVAL when its
+ * turn comes: sweeps under way are waited for and counted, and the walkers
+ * admitted before it stay resident (dsu_server_step, dsu_server_result). */
 int dsu_server_run(dsu_server *s, const dsu_request *reqs, int32_t count, dsu_result *results,
                    double *sweep_latency_ms, int64_t latency_cap, int64_t *latency_count);
 

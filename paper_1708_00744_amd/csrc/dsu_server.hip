@@ -352,6 +352,15 @@ static std::vector<int> flag_singular(dsu_server *s, BucketState *b) {
     return slots;
 }
 
+// Wait for the sweep bucket b has under way; its walkers have one more done.
+static int end_sweep(dsu_server *s, BucketState *b) {
+    HIPCHK(hipEventSynchronize(b->done));
+    b->busy = false;
+    (void)flag_singular(s, b);
+    for (int slot : b->members) s->resident[slot].sweeps_done += 1;
+    return recompute_due(s, b);
+}
+
 // Slot of the walker that owns determinant `pos` of bucket b (descriptor order).
 static int slot_of_det(dsu_server *s, BucketState *b, int pos) {
     for (int slot : b->members) {
@@ -440,12 +449,7 @@ extern "C" int dsu_server_step(dsu_server *s) {
     }
     for (auto &kv : s->buckets) {
         BucketState *b = kv.second.get();
-        if (!b->busy) continue;
-        HIPCHK(hipEventSynchronize(b->done));
-        b->busy = false;
-        (void)flag_singular(s, b);
-        for (int slot : b->members) s->resident[slot].sweeps_done += 1;
-        CHK(recompute_due(s, b));
+        if (b->busy) CHK(end_sweep(s, b));
     }
     return DSU_OK;
 }
@@ -561,7 +565,12 @@ extern "C" int dsu_server_run(dsu_server *s, const dsu_request *reqs, int32_t co
             it = waiting.erase(it);
         }
         const int fresh_rc = start_all_fresh(s);
-        CHK(refused);
+        if (refused != DSU_OK) {
+            // sweeps under way end and count, as after a step
+            for (auto &kv : s->buckets)
+                if (kv.second->busy) CHK(end_sweep(s, kv.second.get()));
+            return refused;
+        }
         CHK(fresh_rc);
         // launch the next sweep of every idle, non-empty bucket
         bool any_busy = false;

@@ -95,3 +95,20 @@ def test_result_after_a_step_with_a_recompute():
         s.step()
         assert numbers(s.result(slot)) == numbers(first)
     assert numbers(last) == numbers(alone(dsu.FP32_MIXED, r, 2, recompute_every=1))
+
+
+def test_refused_run_counts_the_sweeps_under_way():
+    """A request refused while another size is being swept: the sweep ends, is
+    counted, and the walker can be read, stepped and removed."""
+    require_gpu()
+    long = request(31, 512, sweeps=5000, sigma=0.05)
+    with pool(dsu.FP32_MIXED) as s:
+        with pytest.raises(dsu.DsuError) as ex:
+            s.run([long, request(32, 64, spins=3, arrival_s=0.05)])
+        assert ex.value.code == dsu.EINVAL
+        done = s.result(0)["sweeps_done"]
+        assert 0 < done < 5000
+        assert numbers(s.result(0)) == numbers(alone(dsu.FP32_MIXED, long, done))
+        s.step()
+        assert numbers(s.result(0, remove=True)) == numbers(alone(dsu.FP32_MIXED, long, done + 1))
+        assert s.usage() == (0, 0)
