@@ -379,10 +379,11 @@ int dsu_batch_get_trace(dsu_batch *b, int32_t det, double *ratio_host, uint8_t *
  * stream it runs on, 2 only the flush launches (phase 3: fewer events
  * between kernels, so the rest of the sweep runs as untimed), 0 none (and
  * sweeps may replay a captured graph again); any other value is DSU_EINVAL.
- * Each call clears the totals.  dsu_batch_kernel_time returns (count,
- * total ms) for one phase: 0 proposals (of a sweep's first window; the later
- * ones are drawn by the decisions' launches), 1 look-ahead products, 2
- * decisions, 3 flush, 4 recompute. */
+ * Each call clears the totals.  With 1, every window's proposals have a launch
+ * of their own before the decisions' (which otherwise draw all but the first
+ * window's): the same numbers, each phase's time by itself, a slower sweep.
+ * dsu_batch_kernel_time returns (count, total ms) for one phase: 0 proposals,
+ * 1 look-ahead products, 2 decisions, 3 flush, 4 recompute. */
 int dsu_batch_set_timing(dsu_batch *b, int32_t enable);
 int dsu_batch_kernel_time(dsu_batch *b, int32_t phase, int64_t *launches, double *total_ms);
 /* Capture one sweep into a hipGraph and replay it for dsu_batch_sweep

@@ -294,6 +294,8 @@ template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
     const int kt = kpad(K);
     const int nwin = (sh.n + K - 1) / K;
     auto kw_of = [&](int w) { return std::min(K, sh.n - w * K); };
+    // proposals in launches of their own, so that each phase has a time
+    const bool rows_apart = rows_beside || timing == 1;
     CHK(timed(PH_ROWS, [&] {
         return launch_window_props<T>(dd, nd, sh.n, sh.np, kt, 0, kw_of(0), kvec, twopi_l, 0, 1, kmax_comp, stream);
     }));
@@ -309,14 +311,17 @@ template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
         if (rows_beside && has_next) {
             HIPCHK(hipEventRecord(fork, stream));
             HIPCHK(hipStreamWaitEvent(side, fork, 0));
+        }
+        if (rows_apart && has_next) {
+            const hipStream_t on = rows_beside ? side : stream;
             CHK(timed(PH_ROWS, [&] {
                 return launch_window_props<T>(dd, nd, sh.n, sh.np, kt, e0n, kwn, kvec, twopi_l, cur ^ 1, 0, kmax_comp,
-                                              side);
-            }, side));
-            HIPCHK(hipEventRecord(join, side));
+                                              on);
+            }, on));
         }
+        if (rows_beside && has_next) HIPCHK(hipEventRecord(join, side));
         CHK(timed(PH_DECIDE, [&] {
-            return launch_window_decide<T>(dd, nd, sh.n, sh.np, kt, sh.kp, w * K, kw_of(w), e0n, rows_beside ? 0 : kwn,
+            return launch_window_decide<T>(dd, nd, sh.n, sh.np, kt, sh.kp, w * K, kw_of(w), e0n, rows_apart ? 0 : kwn,
                                            kvec, twopi_l, kmax_comp, force, !has_next, cur, stream);
         }));
         if (rows_beside && has_next) HIPCHK(hipStreamWaitEvent(stream, join, 0));
