@@ -6,7 +6,7 @@
   the best K depends on the architecture and the matrix size, and the paper
   suggests leaving its choice to an autotuner).
 * tune_recompute: the blocking of the FP64 recompute (panel width, update
-  chunk, apply columns per workgroup) with the shortest recompute.
+  chunk) with the shortest recompute.
 
 Results are cached in tuning.json next to this file, keyed by workload.
 Run `python -m paper_1708_00744_amd.tune` on the GPU to fill the cache.
@@ -110,8 +110,9 @@ def recompute_key(n, walkers, precision):
 def recompute_candidates(n):
     """Blockings of the FP64 recompute worth timing at this n: panel width
     (128 = pairs of 64-column panels sharing one trailing update, from n = 256
-    while the padded size is at most 4096), update chunk (64 only where the
-    padded size is a multiple of 128) and apply columns per workgroup."""
+    while the padded size is at most 4096) and update chunk (64 only where the
+    padded size is a multiple of 128).  The third entry, the apply columns, has
+    no effect and is the same in all."""
     np_ = -(-n // 64) * 64
     if n < 64:
         panels = (16, 32)
@@ -120,7 +121,7 @@ def recompute_candidates(n):
     else:
         panels = (32, 64)
     chunks = (32, 64) if np_ % 128 == 0 else (32,)
-    return [(p, c, a) for p in panels for c in chunks for a in (1, 4)]
+    return [(p, c, 1) for p in panels for c in chunks]
 
 
 def tune_recompute(n, walkers, precision=dsu.FP32_MIXED, reps=2, seed=1000):
