@@ -126,7 +126,7 @@ static int bucket_for(dsu_server *s, int n, BucketState **out) {
     std::unique_ptr<BucketState> b(new BucketState());
     const BucketShape sh = BucketShape::make(n, s->K, s->prec);
     // the recompute workspace (four determinants per pass) is charged to the
-    // budget: carved from the arena, held while the server lives
+    // budget: carved from the arena, held while a walker of that size is resident
     b->ws_bytes = bucket_ws_bytes(n);
     if (!s->arena.alloc(b->ws_bytes, &b->ws_off))
         return fail(DSU_EBUDGET, "recompute workspace of size %d does not fit the free budget now", n);
@@ -320,9 +320,6 @@ static int start_all_fresh(dsu_server *s) {
 // After a completed sweep of bucket b: recompute the walkers that are due.
 static int recompute_due(dsu_server *s, BucketState *b) {
     if (s->recompute_every <= 0) return DSU_OK;
-    // positions count the members, so those that left at this boundary leave the
-    // descriptors first: their memory may already be another walker's
-    if (b->dirty) CHK(refresh_bucket(s, b));
     std::vector<int> which;
     int pos = 0;
     for (int slot : b->members) {
@@ -332,6 +329,9 @@ static int recompute_due(dsu_server *s, BucketState *b) {
         for (int sp = 0; sp < w.spins; ++sp, ++pos)
             if (due) which.push_back(pos);
     }
+    // positions count the members, so those that left at this boundary leave the
+    // descriptors first: their memory may already be another walker's
+    if (b->dirty && !which.empty()) CHK(refresh_bucket(s, b));
     return b->bk.recompute_async(which);
 }
 

@@ -85,7 +85,7 @@ __device__ __forceinline__ double pw_orbital(int4 kv, double twopi_l, double x, 
 // pair a window, cost 7 to 20 us a window more than the work they hid.  A sweep,
 // before and after: FP64 n = 100, K = 8, one determinant 465 -> 220 us; n = 1000,
 // K = 64, 8 of them 2711 -> 2167, 32 of them 4134 -> 3801; FP32 n = 512, K = 32,
-// 512 of them 5683 -> 5398; n = 4096, K = 128, 32 of them 78.9 -> 75.7 ms.
+// 512 of them 5683 -> 5398; n = 4096, K = 128, 32 of them 77.0 -> 76.0 ms.
 //
 // Orbitals from per-axis phase factors: with q = 2 pi / L,
 // exp(i q (nx x + ny y + nz z)) = Ex^nx Ey^ny Ez^nz and E^-n = conj(E^n), so a

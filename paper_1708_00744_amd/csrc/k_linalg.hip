@@ -1210,16 +1210,16 @@ __global__ __launch_bounds__(1024) void k_gj_perm(const GjDesc *__restrict__ des
 }
 
 GjTiles gj_tiles_default(int n, int np) {
-    // measured on MI355X (before k_gj_group; the ranking of the panels is kept
-    // because the blocking decides the rounding): 64-column panels from N =
-    // 512, in pairs from 1024 (4096: 146 ms against 162 for 32 inverses, 2048:
-    // 45 against 47 ms for 64, 1024: 26.2 against 26.8 ms for 256; at 512
-    // single panels are faster); 64-column update chunks where np pairs them
-    // up (3 % faster than 32 at N = 4096)
+    // measured on MI355X: 64-column panels from N = 512 (512: 7.0 ms against
+    // 9.2 with 32 columns for 512 inverses), in pairs from 1024 (4096: 119 ms
+    // against 139 for 32 inverses, 2048: 32.9 against 37.0 ms for 64, 1024:
+    // 18.6 against 20.4 ms for 256; at 512 7.1 against 7.0); 64-column update
+    // chunks where np pairs them up (4096, single panels: 139 against 146 ms; 512:
+    // 7.4 against 7.0)
     GjTiles t;
     t.nb = n >= 1024 && np <= 4096 ? 128 : (n >= 512 ? 64 : (n >= 64 ? 32 : 16));
     t.cw = np % 128 == 0 ? 64 : 32;
-    t.cpb = np >= 2048 ? 4 : 1;
+    t.cpb = np >= 2048 ? 4 : 1;  // reported back, without effect
     return t;
 }
 
