@@ -288,7 +288,7 @@ int Bucket::harvest_events() {
 // Streaming sweep: prime (proposals of window 0, y = BT U^T for all rows), then
 // per window w: decisions of w with the proposals of w+1, one-pass flush of w
 // producing y for w+1.
-template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
+template <typename T> int Bucket::enqueue_sweep_stream_t(int force, const std::function<void()> &between) {
     const DetDesc<T> *dd = (const DetDesc<T> *)ddesc_;
     const int nd = (int)dets.size();
     const int kt = kpad(K);
@@ -328,12 +328,14 @@ template <typename T> int Bucket::enqueue_sweep_stream_t(int force) {
         CHK(timed(PH_FLUSH, [&] {
             return launch_flush_stream<T>(dd, nd, sh.np, kt, sh.kp, kw_of(w), cur, has_next ? 1 : 0, e0n, kwn, stream);
         }));
+        if (has_next && between) between();
     }
     return DSU_OK;
 }
 
-int Bucket::enqueue_sweep(int force) {
-    return sh.prec == DSU_FP64 ? enqueue_sweep_stream_t<double>(force) : enqueue_sweep_stream_t<float>(force);
+int Bucket::enqueue_sweep(int force, const std::function<void()> &between) {
+    return sh.prec == DSU_FP64 ? enqueue_sweep_stream_t<double>(force, between)
+                               : enqueue_sweep_stream_t<float>(force, between);
 }
 
 int Bucket::build_graph(int force) {
@@ -356,14 +358,14 @@ int Bucket::build_graph(int force) {
     return DSU_OK;
 }
 
-int Bucket::sweep(int force) {
+int Bucket::sweep(int force, const std::function<void()> &between) {
     if (dets.empty()) return DSU_OK;
     if (use_graph && !timing) {
         if (!gexec_ || graph_force_ != force) CHK(build_graph(force));
         HIPCHK(hipGraphLaunch(gexec_, stream));
         return DSU_OK;
     }
-    return enqueue_sweep(force);
+    return enqueue_sweep(force, between);
 }
 
 template <typename T> int Bucket::recompute_async_t(const std::vector<int> &which) {

@@ -5,6 +5,7 @@
 // block for dsu_batch, an arena for dsu_server), so members can join and
 // leave between sweeps.
 #pragma once
+#include <functional>
 #include <utility>
 #include <vector>
 
@@ -65,7 +66,8 @@ class Bucket {
     int set_dets(const std::vector<DetSlot> &d);
     int set_delay(int k);
     // One sweep of every member, stream ordered.
-    int sweep(int force_accept);
+    // `between` (optional) is called after the launches of every window but the last.
+    int sweep(int force_accept, const std::function<void()> &between = nullptr);
     // FP64 recompute of the listed members (indices into dets); waits for it
     // and reports a singular matrix.  drift_dev (optional, per listed member)
     // receives running-minus-fresh log|det|.
@@ -119,13 +121,13 @@ class Bucket {
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> ev_used_;
 
     int ensure_capacity(int n);
-    int enqueue_sweep(int force_accept);
+    int enqueue_sweep(int force_accept, const std::function<void()> &between = nullptr);
     int build_graph(int force_accept);
     void drop_graph();
     hipEvent_t ev_ring_[8] = {};
     template <typename F> int timed(int phase, F fn, hipStream_t on = nullptr);
     template <typename T> int upload_t();
-    template <typename T> int enqueue_sweep_stream_t(int force_accept);
+    template <typename T> int enqueue_sweep_stream_t(int force_accept, const std::function<void()> &between);
     template <typename T> int recompute_async_t(const std::vector<int> &which);
 };
 
