@@ -115,3 +115,23 @@ def test_large_permutation_inverse_is_exact(n, cplx):
         assert got[0] == 0.0 and abs(np.exp(1j * got[1]) - sign) <= 8 * n * 2.0**-53
     else:
         assert got == (int(sign.real), 0.0)
+
+
+def test_multidet_replaced_by_another_size():
+    """A larger, then a smaller expansion on one walker: the ratios of a walker
+    that had the smaller one alone, bit for bit."""
+    require_gpu()
+    n, moves = 200, 6
+    a = well_conditioned(98, n)
+    rows, v = inputs.rows(99, moves, n) / np.sqrt(n), inputs.rows(97, n, 130) / np.sqrt(n)
+    seen = []
+    for sizes in ((130, 17), (17,), (1, 17)):
+        with dsu.Walker(a, 4) as w:
+            for m in sizes:
+                w.set_multidet(np.ascontiguousarray(v[:, :m]), expansion(n, m) if m > 1 else [(1.0, []), (0.1, [(3, 0)])])
+                got = []
+                for e, row in enumerate(rows):
+                    got.append(w.propose_md(e, 0.9 * a[e] + 0.1 * row, v[e, :m]))
+                    w.reject()
+            seen.append((got, w.md_value()))
+    assert seen[0] == seen[1] == seen[2]
