@@ -238,11 +238,17 @@ template <typename T, int KP> struct FlushLds {
 
 // ---------------------------------------------------------------------------
 // The three products of eq. (4) in one launch, 64 rows per workgroup: for
-// matrices of at most kFusedRows padded rows, where two launches fewer count
-// more than idle compute units (np = 64: 9 us against 13 in three launches; np = 128: 14
-// and 15; np = 192: 18 and 17).
+// matrices of at most FusedRows padded rows, where two launches fewer count
+// more than idle compute units.  FP64, 16 slots: np = 64 9 us against 13 in three
+// launches, 128 14 and 15, 192 18 and 17.  FP32, whose products take half as long
+// (a flush and the next move's look-ahead, 16 / 32 / 64 / 128 slots): np = 192 19 /
+// 22 / 31 / 51 us against 24 / 30 / 36 / 48, 256 22 / 26 / 37 / 61 against 25 / 31 / 38
+// / 52, 320 24 / 29 / 42 / 72 against 26 / 33 / 40 / 51, 448 29 / 36 / 54 / 92 against 28
+// / 37 / 43 / 57.
 // ---------------------------------------------------------------------------
-constexpr int kFusedRows = 128;
+template <typename T, int KP> struct FusedRows {
+    static constexpr int value = sizeof(T) == 8 || KP > 64 ? 128 : (KP == 64 ? 256 : 320);
+};
 
 template <typename T, int KP>
 __global__ __launch_bounds__(kThreads) void k_flush_fused(FlushArgs<T> fd, int ld, int kslots) {
@@ -282,7 +288,7 @@ __global__ __launch_bounds__(kThreads) void k_flush_fused(FlushArgs<T> fd, int l
 template <typename T, int KP, int Z>
 static hipError_t flush_mfma(const FlushArgs<T> &fa, int np, int kslots, hipStream_t s) {
     if constexpr (Z == 1)
-        if (np <= kFusedRows) {
+        if (np <= FusedRows<T, KP>::value) {
             hipLaunchKernelGGL((k_flush_fused<T, KP>), dim3(np / kRowBlock), dim3(kThreads), 0, s, fa, np, kslots);
             return hipGetLastError();
         }

@@ -1,0 +1,30 @@
+"""The FP32 flush on both sides of the size from which its products are launched
+one by one (padded rows 320 up to 32 slots, 256 at 64, 128 above)."""
+import numpy as np
+import pytest
+
+from gpu_util import require_gpu
+from paper_1708_00744_amd import dsu, inputs
+from test_gpu_edges import well_conditioned
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,k", [(192, 1), (320, 16), (321, 16), (310, 32), (385, 32), (256, 33), (257, 64), (128, 65),
+                                 (129, 128)])
+def test_fp32_flush_both_sides(n, k):
+    require_gpu()
+    a = well_conditioned(61 + n, n)
+    noise = inputs.rows(62, k, n)
+    order = np.random.default_rng(n).permutation(n)[:k]
+    b = a.copy()
+    with dsu.Walker(a, min(256, k + 1), precision=dsu.FP32_MIXED) as w:
+        w.set_flush_kernel(dsu.FLUSH_MFMA)
+        for e, row in zip(order, noise):
+            b[e] = 0.9 * a[e] + 0.1 * row / np.sqrt(n)
+            w.propose(int(e), b[e])
+            w.accept()
+        assert w.pending() == k
+        got = w.inverse()
+    # entries below 1, N-term FP32 sums (unit roundoff 2^-24), x 64 for the chain of moves
+    assert np.abs(got - np.linalg.inv(b)).max() <= 64.0 * np.sqrt(n) * 2.0**-24
