@@ -114,7 +114,13 @@ static hipError_t zgemm(const zc *A, int lda, const zc *B, int ldb, zc *C, int l
 // Flush, first half, one wave per row of BT (4 rows per workgroup): the
 // row's look-ahead products y_j = BT[i] . U[j] (16 slots at a time, lanes
 // striding the columns, then a wave reduction), y_j -= 1 where e_j = i, and
-// the row of W = (Y - E) C^{-T}: w_j = sum_l y_l Cinv[j][l].
+// the row of W = (Y - E) C^{-T}: w_j = sum_l y_l Cinv[j][l].  Bound by U's loads from
+// L2: four slots' are in flight together, and each workgroup starts at a column of
+// its own (all of them at the same columns of rows np elements apart meet in a
+// quarter of L2's channels).  Slot by slot from column 0 a launch took 304 to 523
+// us at n = 512, k = 200, by how far the waves drift apart; a flush with the next
+// move's look-ahead, before and so: n = 512, k = 200 394 to 612 -> 310 us, n = 1000
+// 863 to 1050 -> 392, n = 256, k = 130 200 to 260 -> 167, n = 1000, k = 8 61 to 69 -> 42.
 __global__ __launch_bounds__(kThreads) void k_zflush_w(ZWalkerDev w, int np, int k) {
     __shared__ zc s_y[4][DSU_KMAX_LDS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -125,11 +131,17 @@ __global__ __launch_bounds__(kThreads) void k_zflush_w(ZWalkerDev w, int np, int
         zc acc[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc[j] = make_double2(0.0, 0.0);
-        for (int c = lane; c < np; c += 64) {
-            const zc b = bt[c];
+        for (int t = 0, c = lane + 64 * (blockIdx.x % (np / 64)); t < np; t += 64, c = c + 64 < np ? c + 64 : lane) {
+            const zc b = la_load(bt + c);
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (j < nj) acc[j] = zfma(b, w.u[(size_t)(j0 + j) * np + c], acc[j]);
+            for (int q = 0; q < 16; q += 4) {
+                if (q >= nj) break;
+                zc u[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) u[j] = la_load(w.u + (size_t)(q + j < nj ? j0 + q + j : j0) * np + c);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[q + j] = zfma(b, u[j], acc[q + j]);
+            }
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
