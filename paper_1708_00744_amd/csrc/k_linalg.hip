@@ -239,15 +239,16 @@ template <typename T, int KP> struct FlushLds {
 // ---------------------------------------------------------------------------
 // The three products of eq. (4) in one launch, 64 rows per workgroup: for
 // matrices of at most FusedRows padded rows, where two launches fewer count
-// more than idle compute units.  FP64, 16 slots: np = 64 9 us against 13 in three
-// launches, 128 14 and 15, 192 18 and 17.  FP32, whose products take half as long
-// (a flush and the next move's look-ahead, 16 / 32 / 64 / 128 slots): np = 192 19 /
-// 22 / 31 / 51 us against 24 / 30 / 36 / 48, 256 22 / 26 / 37 / 61 against 25 / 31 / 38
-// / 52, 320 24 / 29 / 42 / 72 against 26 / 33 / 40 / 51, 448 29 / 36 / 54 / 92 against 28
-// / 37 / 43 / 57.
+// more than idle compute units.  A flush and the next move's look-ahead, us, one
+// launch against three, at 16 / 32 / 64 / 128 slots.  FP64: np = 64 15.6 / 17.5 / 22.9 /
+// - and 20.1 / 23.6 / 26.9 / -, 128 21.7 / 24.8 / 34.7 / 70 and 23.9 / 28.2 / 31.6 / 38,
+// 192 26.5 / 31.6 / 45.9 / 92 and 26.5 / 31.8 / 35.4 / 42.  FP32: np = 128 16.7 / 18.7 / 24.6
+// / 39 and 22.0 / 28.0 / 34.0 / 43, 192 19 / 22 / 31 / 51 and 24 / 30 / 36 / 48, 256 22 / 26 /
+// 37 / 61 and 25 / 31 / 38 / 52, 320 24 / 29 / 42 / 72 and 26 / 33 / 40 / 51, 448 29 / 36 / 54 / 92
+// and 28 / 37 / 43 / 57.
 // ---------------------------------------------------------------------------
 template <typename T, int KP> struct FusedRows {
-    static constexpr int value = sizeof(T) == 8 || KP > 64 ? 128 : (KP == 64 ? 256 : 320);
+    static constexpr int value = sizeof(T) == 8 ? (KP <= 32 ? 128 : 64) : (KP <= 32 ? 320 : (KP == 64 ? 256 : 128));
 };
 
 template <typename T, int KP>

@@ -1,5 +1,6 @@
-"""The FP32 flush on both sides of the size from which its products are launched
-one by one (padded rows 320 up to 32 slots, 256 at 64, 128 above)."""
+"""The flush on both sides of the size from which its products are launched one by
+one (padded rows: FP32 320 up to 32 slots, 256 at 64, 128 above; FP64 128 up to
+32 slots, 64 above)."""
 import numpy as np
 import pytest
 
@@ -28,3 +29,22 @@ def test_fp32_flush_both_sides(n, k):
         got = w.inverse()
     # entries below 1, N-term FP32 sums (unit roundoff 2^-24), x 64 for the chain of moves
     assert np.abs(got - np.linalg.inv(b)).max() <= 64.0 * np.sqrt(n) * 2.0**-24
+
+
+@pytest.mark.parametrize("n,k", [(64, 33), (65, 33), (128, 32), (128, 64), (100, 65), (128, 128), (129, 32)])
+def test_fp64_flush_both_sides(n, k):
+    require_gpu()
+    a = well_conditioned(63 + n, n)
+    noise = inputs.rows(64, k, n)
+    order = np.random.default_rng(n).permutation(n)[:k]
+    b = a.copy()
+    with dsu.Walker(a, min(256, k + 1)) as w:
+        w.set_flush_kernel(dsu.FLUSH_MFMA)
+        for e, row in zip(order, noise):
+            b[e] = 0.9 * a[e] + 0.1 * row / np.sqrt(n)
+            w.propose(int(e), b[e])
+            w.accept()
+        assert w.pending() == k
+        got = w.inverse()
+    # as above with 2^-53, and 2^10 more for the moves' borderings
+    assert np.abs(got - np.linalg.inv(b)).max() <= 2.0**10 * 64.0 * np.sqrt(n) * 2.0**-53
