@@ -63,7 +63,7 @@ enum {
 
 /* Flush kernel selection for the single-walker form. */
 enum {
-    DSU_FLUSH_AUTO = 0,  /* VALU for k = 1 and small k n, matrix cores above     */
+    DSU_FLUSH_AUTO = 0,  /* VALU where k <= 4 and n make it faster, else MFMA   */
     DSU_FLUSH_VALU = 1,  /* vector-ALU rank-k kernel                             */
     DSU_FLUSH_MFMA = 2   /* matrix-core (MFMA) rank-k kernels                    */
 };

@@ -212,12 +212,19 @@ template <typename T> static hipError_t walker_flush_t(dsu_walker *w, bool valu)
 
 static int walker_do_flush(dsu_walker *w) {
     if (w->k > 0) {
-        // the vector ALUs read BT, U and Vg once per slot group and cost about
-        // k np; the matrix cores three launches.  FP64 us, vector / matrix:
-        // k = 1 16 / 22 at n = 1024, 64 / 80 at 4096; k = 2 15 / 17 at 512, 23 /
-        // 22 at 1024; k = 4 16 / 17 at 256, 23 / 17 at 512
-        const bool valu = w->flush_mode == DSU_FLUSH_VALU ||
-                          (w->flush_mode == DSU_FLUSH_AUTO && (w->k == 1 || (w->k <= 4 && w->k * w->np <= 1024)));
+        // The vector ALUs read BT, U and Vg once per slot group and cost about
+        // k np; the matrix cores one launch (small n) or three, the same up to 16
+        // slots.  A flush and the next look-ahead, us, vector / matrix.  FP64: k =
+        // 1 24.5 / 31 at n = 1024, 75 / 89 at 4096; k = 2 32.5 / 33.9 at 960, 31.4 / 31.0 at
+        // 1024, 99 / 89 at 4096; k = 3 27.8 / 29.8 at 448, 26.9 / 26.7 at 512; k = 4 28.5 /
+        // 28.6 at 384, 31.4 / 29.9 at 448.  FP32: k = 2 16.3 / 16.8 at 100, 32 / 34.5 at
+        // 1024, 90 / 97 at 4096; k = 3 18.1 / 16.9 at 128, 22.8 / 22.1 at 256, 22.4 / 23.6 at
+        // 320, 26.7 / 27.3 at 448, 28.4 / 27.3 at 512; k = 4 19.4 / 16.9 at 128, 29.7 / 27.3 at
+        // 448
+        const int k = w->k, np = w->np;
+        const bool line = w->prec == DSU_FP64 ? k == 1 || (k == 2 && np < 1024) || (k <= 4 && k * np <= 1536)
+                                              : k <= 2 || (k == 3 && np > 256 && np < 512);
+        const bool valu = w->flush_mode == DSU_FLUSH_VALU || (w->flush_mode == DSU_FLUSH_AUTO && line);
         if (w->prec == DSU_FP64) HIPCHK(walker_flush_t<double>(w, valu));
         else HIPCHK(walker_flush_t<float>(w, valu));
     }

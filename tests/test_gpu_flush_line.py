@@ -48,3 +48,29 @@ def test_fp64_flush_both_sides(n, k):
         got = w.inverse()
     # as above with 2^-53, and 2^10 more for the moves' borderings
     assert np.abs(got - np.linalg.inv(b)).max() <= 2.0**10 * 64.0 * np.sqrt(n) * 2.0**-53
+
+
+# the automatic choice at and beside its lines agrees with both kernels
+@pytest.mark.parametrize("n,k,prec", [(1, 1, dsu.FP64), (960, 2, dsu.FP64), (961, 2, dsu.FP64), (512, 3, dsu.FP64),
+                                      (513, 3, dsu.FP64), (384, 4, dsu.FP64), (385, 4, dsu.FP64), (40, 5, dsu.FP64),
+                                      (70, 2, dsu.FP32_MIXED), (256, 3, dsu.FP32_MIXED), (257, 3, dsu.FP32_MIXED),
+                                      (448, 3, dsu.FP32_MIXED), (449, 3, dsu.FP32_MIXED), (300, 4, dsu.FP32_MIXED)])
+def test_automatic_flush_kernel(n, k, prec):
+    require_gpu()
+    a = well_conditioned(65 + n, n)
+    noise = inputs.rows(66, k, n)
+    b, got = a.copy(), []
+    for e in range(k):
+        b[e] = 0.9 * a[e] + 0.1 * noise[e] / np.sqrt(n)
+    for mode in (dsu.FLUSH_AUTO, dsu.FLUSH_VALU, dsu.FLUSH_MFMA):
+        with dsu.Walker(a, min(256, k + 1), precision=prec) as w:
+            w.set_flush_kernel(mode)
+            for e in range(k):
+                w.propose(e, b[e])
+                w.accept()
+            w.flush()
+            got.append(w.inverse())
+    assert np.array_equal(got[0], got[1]) or np.array_equal(got[0], got[2])
+    tol = 64.0 * np.sqrt(n) * (2.0**-24 if prec == dsu.FP32_MIXED else 2.0**-43)
+    for x in got:
+        assert np.abs(x - np.linalg.inv(b)).max() <= tol
