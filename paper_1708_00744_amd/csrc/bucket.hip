@@ -646,15 +646,18 @@ static int batch_recompute_some(dsu_batch *b, const std::vector<int> &which) {
     return DSU_OK;
 }
 
+// One blocking copy.  (An asynchronous one into pageable memory and its wait take
+// 28 us against 18 to 25 for 1 to 400 determinants, 17 to 90 against 24 to 34 for more.)
 static int batch_read_states(dsu_batch *b, std::vector<DetState> *st) {
     st->resize(b->ndet);
-    HIPCHK(hipMemcpyAsync(st->data(), b->states, sizeof(DetState) * b->ndet, hipMemcpyDeviceToHost, b->bk.stream));
     HIPCHK(hipStreamSynchronize(b->bk.stream));
+    HIPCHK(hipMemcpy(st->data(), b->states, sizeof(DetState) * b->ndet, hipMemcpyDeviceToHost));
     return DSU_OK;
 }
 
-static int batch_write_states(dsu_batch *b, const std::vector<DetState> &st) {
-    HIPCHK(hipMemcpyAsync(b->states, st.data(), sizeof(DetState) * b->ndet, hipMemcpyHostToDevice, b->bk.stream));
+// Completed sweeps (unless sweep < 0) and, with clear_trace, trace positions of every determinant.
+static int batch_set_states(dsu_batch *b, long long sweep, int clear_trace) {
+    HIPCHK(launch_set_states(b->states, b->ndet, sweep, clear_trace, b->bk.stream));
     HIPCHK(hipStreamSynchronize(b->bk.stream));
     return DSU_OK;
 }
@@ -722,7 +725,10 @@ extern "C" int dsu_batch_create(int32_t walkers, int32_t n, int32_t spins, int32
     if (rc == DSU_OK && hipMemcpy(b->pos, positions_host, sizeof(double) * n * 3 * b->ndet, hipMemcpyHostToDevice) !=
                             hipSuccess)
         rc = fail(DSU_EDEVICE, "upload of walker state failed");
-    if (rc == DSU_OK) rc = batch_write_states(b, std::vector<DetState>(b->ndet, DetState{0.0, 1, 0, 0, 0, 0}));
+    const std::vector<DetState> fresh(b->ndet, DetState{0.0, 1, 0, 0, 0, 0});
+    if (rc == DSU_OK &&
+        hipMemcpy(b->states, fresh.data(), sizeof(DetState) * b->ndet, hipMemcpyHostToDevice) != hipSuccess)
+        rc = fail(DSU_EDEVICE, "upload of walker state failed");
     if (rc != DSU_OK) {
         batch_free(b);
         delete b;
@@ -943,10 +949,7 @@ extern "C" int dsu_batch_stats(dsu_batch *b, double *logdet, int32_t *sign, int6
 extern "C" int dsu_batch_set_sweep(dsu_batch *b, int64_t sweeps_done) {
     if (!b) return fail(DSU_EINVAL, "batch is NULL");
     if (sweeps_done < 0) return fail(DSU_EINVAL, "sweeps_done %lld < 0", (long long)sweeps_done);
-    std::vector<DetState> st;
-    CHK(batch_read_states(b, &st));
-    for (DetState &x : st) x.sweep = sweeps_done;
-    return batch_write_states(b, st);
+    return batch_set_states(b, sweeps_done, 0);
 }
 
 extern "C" int dsu_batch_get_positions(dsu_batch *b, int32_t det, double *out_host) {
@@ -991,10 +994,7 @@ extern "C" int dsu_batch_set_trace(dsu_batch *b, int32_t sweeps) {
         slots[i].trace_a = b->trace_a ? b->trace_a + (size_t)b->trace_cap * i : nullptr;
         slots[i].trace_cap = b->trace_r ? b->trace_cap : 0;
     }
-    std::vector<DetState> st;
-    CHK(batch_read_states(b, &st));
-    for (DetState &x : st) x.trace_pos = 0;
-    CHK(batch_write_states(b, st));
+    CHK(batch_set_states(b, -1, 1));
     return b->bk.set_dets(slots);
 }
 

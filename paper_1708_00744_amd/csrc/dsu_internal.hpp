@@ -211,6 +211,8 @@ hipError_t launch_flush_stream(const DetDesc<T> *d, int ndesc, int np, int ktile
                                int has_next, int e0n, int kwn, hipStream_t s);
 template <typename T>
 hipError_t launch_reset_state(const DetDesc<T> *d, const GjDesc *gj, double *drift, int ndesc, hipStream_t s);
+// Of n states in a row: completed sweeps (unless sweep < 0), and trace positions to 0.
+hipError_t launch_set_states(DetState *st, int n, long long sweep, int clear_trace, hipStream_t s);
 
 // Sampled residual of the inverse: out_bits[d] = bit pattern of
 // max_{s, j} |phi(r_{e_s}) . BT[j, :] - delta(j, e_s)| over `samples` (1..64,

@@ -686,6 +686,19 @@ hipError_t launch_reset_state(const DetDesc<T> *d, const GjDesc *gj, double *dri
 template hipError_t launch_reset_state<float>(const DetDesc<float> *, const GjDesc *, double *, int, hipStream_t);
 template hipError_t launch_reset_state<double>(const DetDesc<double> *, const GjDesc *, double *, int, hipStream_t);
 
+// Completed sweeps (unless sweep < 0) and trace positions of `n` states in a row.
+__global__ void k_set_states(DetState *st, int n, long long sweep, int clear_trace) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    if (sweep >= 0) st[i].sweep = sweep;
+    if (clear_trace) st[i].trace_pos = 0;
+}
+
+hipError_t launch_set_states(DetState *st, int n, long long sweep, int clear_trace, hipStream_t s) {
+    hipLaunchKernelGGL(k_set_states, dim3((n + 63) / 64), dim3(64), 0, s, st, n, sweep, clear_trace);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------- sampled inverse residual
 // Sec. III checks the determinants against a direct calculation; between FP64
 // recomputes the batched form checks its inverse X against the Slater matrix

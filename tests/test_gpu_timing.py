@@ -28,3 +28,26 @@ def test_every_window_has_a_time_in_every_phase(prec, n, K):
             st = b.stats()
             outs.append((st["logdet"].tolist(), st["accepted"].tolist(), b.positions(1).tolist()))
     assert outs[0] == outs[1] == outs[2]
+
+
+# one workgroup of states, a full one, one more; the counts of all determinants are
+# set, and a trace starts over
+@pytest.mark.parametrize("walkers", [1, 64, 65])
+def test_set_sweep_and_trace_reach_every_determinant(walkers):
+    require_gpu()
+    n = 12
+    pos = np.stack([inputs.positions(5, w, n, 10.0) for w in range(walkers)])
+    with dsu.Batch(n, pos, [5] * walkers, list(range(walkers)), 0.2, 8, precision=dsu.FP64, box_l=10.0) as b:
+        before = b.stats()
+        b.set_sweep(41)
+        after = b.stats()
+        assert (after["sweeps"] == 41).all() and (before["sweeps"] == 0).all()
+        assert all(np.array_equal(after[q], before[q]) for q in ("logdet", "sign", "accepted"))
+        for _ in range(2):
+            b.set_trace(1)
+            b.sweep(1)
+            taken = sum(int(b.trace(w)[1].sum()) for w in range(walkers))
+            total = int(b.stats()["accepted"].sum())
+            assert taken == total - int(after["accepted"].sum())
+            after = b.stats()
+        assert (after["sweeps"] == 43).all()
