@@ -79,6 +79,7 @@ class Bucket {
     // until they are checked.
     int recompute_async(const std::vector<int> &which);
     void check_recompute(std::vector<int> *singular);
+    bool recompute_pending() const { return !pending_.empty(); }
     // Sampled residuals of every member, A rebuilt from the positions: right =
     // max over `samples` rows of |A A^{-1} - I| (launch_resid), left = the same
     // for A^{-1} A - I (launch_resid_left); either may be NULL.  Waits.

@@ -462,7 +462,7 @@ extern "C" int dsu_server_result(dsu_server *s, int32_t slot, dsu_result *out, i
     if (it != s->buckets.end() && it->second->busy) return fail(DSU_ESTATE, "bucket busy");
     // a step leaves its recomputes on the stream: they set the state read here
     // and write the memory a removal gives back
-    if (it != s->buckets.end()) {
+    if (it != s->buckets.end() && it->second->bk.recompute_pending()) {
         HIPCHK(hipStreamSynchronize(it->second->bk.stream));
         (void)flag_singular(s, it->second.get());
     }
