@@ -213,8 +213,7 @@ typedef struct dsu_zwalker dsu_zwalker;
 
 /* Create from the complex Slater matrix (2*n*n doubles).  Computes A^{-1},
  * log|det A| and arg det A in FP64 complex on the device (Gauss-Jordan with
- * partial pivoting by |re| + |im|, so a pivot's modulus is within sqrt(2) of
- * the largest).  n in [1, 16384], k_delay in [1, DSU_MAX_K], policy as for
+ * partial pivoting by modulus).  n in [1, 16384], k_delay in [1, DSU_MAX_K], policy as for
  * dsu_walker_create.  DSU_ESINGULAR if A is singular to working
  * precision (a pivot at or below n * 2^-52 times the largest pivot). */
 int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, const double *slater_host, void *hip_stream,

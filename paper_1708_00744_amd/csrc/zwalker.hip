@@ -42,7 +42,9 @@ struct ZWalkerDev {
     zc *w;             // np x (kp + 1): flush scratch W
     zc *work;          // np x np: the inversion's other buffer; also dsu_zget_inverse's output
     zc *panel;         // np x 16: a group's factored columns
+    zc *mult;          // 16 x np: a group's multipliers, a column of M each as its pivot found it
     zc *pval;          // np: pivots
+    zc *pinv;          // np: their reciprocals
     int *slot;         // np: the pivot a row was taken for
     int *piv;          // np: the row taken for a pivot
     double *stat;      // log|det|, arg det without the row order's sign, 1 if singular to working precision
@@ -166,18 +168,24 @@ __global__ __launch_bounds__(kThreads) void k_zflush_w(ZWalkerDev w, int np, int
 // Fresh inverse: in-place Gauss-Jordan on M = A^T with partial pivoting, WS
 // columns (a group) at a time.  A launch pair per column with the rows moved
 // in memory cost 12 us a column, the matrix's pitched upload 5 ms; now a launch
-// pair per group (33 + 6 us at n = 600) and one flat upload.  New matrix in,
-// inverse out at n = 600: 12.0 -> 2.1 ms.
+// pair per group (38 + 12 us at n = 600) and one flat upload.  New matrix in,
+// inverse out: 11.7 -> 2.2 ms at n = 600, 45.9 -> 10.4 ms at n = 1500.
 //  * k_zgj_group, one workgroup, thread t holds rows t + NT r of the group's
 //    columns in registers, so a pivot step is one exchange through LDS and one
 //    barrier;
-//  * k_zgj_update applies the group's rank-WS update to all other columns, from
-//    one buffer to another (the pivot rows it needs are those of the old one).
+//  * k_zgj_update applies the group's steps to all other columns, from one
+//    buffer to another (the pivot rows it needs are those of the old one).  Every
+//    element gets what one elimination step after the other gives it, with the
+//    steps' own multipliers.  A product by the group's inverse (its factored
+//    columns on the untouched pivot rows, the real part and the imaginary part
+//    each accumulated from the old element) takes 6 us instead of 12 and 1.77 ms
+//    instead of 2.18 in all, but its inverses' rms errors were 1.42 times those
+//    of the elimination (1000 twisted-wave matrices of n = 100 and 130); these
+//    are 1.00 times (+- 0.014).
 // Rows are not interchanged: slot[i] names the pivot row i was taken for (-1:
 // none yet).  With row p_j taken for pivot j the result holds, in row p_i and
 // column j, element (i, p_j) of the inverse; k_zgj_gather puts it in place.
-// The pivot is the largest |re| + |im| (within sqrt(2) of the largest modulus,
-// without its square root or the overflow of squares).
+// The pivot is the largest in modulus, by its square, which its reciprocal needs anyway.
 // ---------------------------------------------------------------------------
 
 // M[i][j] = A[j][i] for i, j < n (zero elsewhere up to np), through LDS; slots
@@ -201,9 +209,10 @@ __global__ __launch_bounds__(kThreads) void k_zgj_load(const zc *in, int ldi, zc
 }
 
 // Pivots k0 .. k0 + w - 1 on the group's columns; factored columns to panel
-// (np x WS), pivot values to pval, the rows taken to piv and slot.  A pivot step
-// is bound by its serial chain (search, exchange, reciprocal) and by 4 WS RPT
-// FP64 multiply-adds a thread, on one compute unit, so:
+// (np x WS), the steps' multipliers to mult, pivots and their reciprocals to pval
+// and pinv, the rows taken to piv and slot.  A pivot step
+// is bound by its serial chain (search, exchange, reciprocal) and by 6 WS RPT
+// FP64 operations a thread, on one compute unit, so:
 //  * WS RPT = 32 complex values a thread on as few waves as hold the rows: what
 //    a wave does once a step serves RPT rows of each lane;
 //  * the pivot row sits one column a lane (in each 16 lanes) and enters the
@@ -212,8 +221,9 @@ __global__ __launch_bounds__(kThreads) void k_zgj_load(const zc *in, int ldi, zc
 //    the left), so the pivot column is always the first, every index is fixed
 //    and the body of one step stays in the instruction cache.
 template <int WS, int RPT>
-__global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc *__restrict__ panel, int *slot,
-                                                   int *piv, zc *pval, int np, int n, int k0, int w) {
+__global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc *__restrict__ panel,
+                                                   zc *__restrict__ mult, int *slot, int *piv, zc *pval, zc *pinv,
+                                                   int np, int n, int k0, int w) {
     __shared__ zc s_row[WS];
     __shared__ double s_key[8];
     __shared__ int s_at[8];
@@ -259,7 +269,7 @@ __global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc 
         int bi = tid;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) {
-            const double v = fabs(fx[r]) + fabs(fy[r]), key = mine[r] != -1 ? -1.0 : (v == v ? v : -0.5);
+            const double v = __builtin_fma(fx[r], fx[r], fy[r] * fy[r]), key = mine[r] != -1 ? -1.0 : (v == v ? v : -0.5);
             if (key > best) {
                 best = key;
                 bi = tid + nt * r;
@@ -287,12 +297,16 @@ __global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc 
         __syncthreads();
         const zc rv = s_row[lane & (WS - 1)];
         const double px = row_bcast_f64<0>(rv.x), py = row_bcast_f64<0>(rv.y);
-        const double d = 1.0 / (px * px + py * py), ix = px * d, iy = -py * d;
+        const double d = __builtin_fma(px, px, py * py), ix = px / d, iy = -py / d;
         const double sx = __builtin_fma(rv.x, ix, -(rv.y * iy)), sy = __builtin_fma(rv.x, iy, rv.y * ix);
         if (tid == 0) {
             pval[k0 + s] = make_double2(px, py);
+            pinv[k0 + s] = make_double2(ix, iy);
             piv[k0 + s] = p;
         }
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+            if (mine[r] != -2) (mult + (size_t)s * np + nt * r)[tid] = make_double2(fx[r], fy[r]);
 #pragma unroll
         for (int r = 0; r < RPT; ++r)
             if (own[r]) {  // the pivot row itself: scaled
@@ -310,8 +324,8 @@ __global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc 
             const double qx = row_bcast_f64<c>(sx), qy = row_bcast_f64<c>(sy);
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
-                ax[r][c - 1] = __builtin_fma(-fx[r], qx, __builtin_fma(fy[r], qy, ax[r][c]));
-                ay[r][c - 1] = __builtin_fma(-fx[r], qy, __builtin_fma(-fy[r], qx, ay[r][c]));
+                ax[r][c - 1] = ax[r][c] - __builtin_fma(fx[r], qx, -(fy[r] * qy));
+                ay[r][c - 1] = ay[r][c] - __builtin_fma(fx[r], qy, fy[r] * qx);
             }
         });
 #pragma unroll
@@ -331,49 +345,72 @@ __global__ __launch_bounds__(512) void k_zgj_group(const zc *__restrict__ m, zc 
     }
 }
 
-// dst[i][c] = (row i taken in this group ? 0 : src[i][c]) + sum_j panel[i][j] src[p_j][c]
-// outside the group's columns, panel[i][c - k0] there.  A workgroup: 16 rows x 64
-// columns, four rows a thread; all loads are issued before the products, whose
-// operands are read from LDS (held in registers they spilled: 27 us a launch at
-// n = 600 against 6).
+// a - f q, as in k_zgj_group's steps: the product first, so that one rounding at a's size is taken, not two.
+__device__ __forceinline__ zc zgj_step(zc a, zc f, zc q) {
+    return make_double2(a.x - __builtin_fma(f.x, q.x, -(f.y * q.y)), a.y - __builtin_fma(f.x, q.y, f.y * q.x));
+}
+
+// The group's steps on the columns outside it, panel[i][c - k0] in its own.  A
+// workgroup: 16 rows x 64 columns, four rows a thread; all loads are issued before
+// the products.  Its first wave takes the pivot rows through the group's steps (q_s,
+// pivot row s as step s leaves it), then every row takes a - f_s q_s, s in order; a
+// row taken at step t starts from q_t.
 template <int WS>
 __global__ __launch_bounds__(kThreads) void k_zgj_update(const zc *__restrict__ src, zc *__restrict__ dst,
-                                                         const zc *__restrict__ panel, const int *__restrict__ slot,
-                                                         const int *__restrict__ piv, int np, int n, int k0, int w) {
-    __shared__ zc s_t[16][WS], s_q[WS][64];
+                                                         const zc *__restrict__ panel, const zc *__restrict__ mult,
+                                                         const int *__restrict__ slot, const int *__restrict__ piv,
+                                                         const zc *__restrict__ pinv, int np, int n, int k0, int w) {
+    __shared__ zc s_f[16][WS], s_fp[WS][WS], s_q[WS][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = blockIdx.x * 64 + lane, i0 = blockIdx.y * 16;
-    constexpr int NQ = (WS + 3) / 4;
-    zc q[NQ], o[4];
+    zc v[WS], o[4];
+    int at[4];
+    if (wave == 0)
 #pragma unroll
-    for (int h = 0; h < NQ; ++h) {
-        const int j = wave + 4 * h;
-        q[h] = la_load(src + (size_t)piv[k0 + (j < w ? j : 0)] * np + c);
-    }
+        for (int t = 0; t < WS; ++t) v[t] = la_load(src + (size_t)piv[k0 + (t < w ? t : 0)] * np + c);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + wave + 4 * r;
-        o[r] = i < n && slot[i] < k0 ? la_load(src + (size_t)i * np + c) : make_double2(0.0, 0.0);
+        at[r] = i < n ? __builtin_amdgcn_readfirstlane(slot[i]) - k0 : -1;  // the step that takes the row (< 0: none)
+        o[r] = i < n && at[r] < 0 ? la_load(src + (size_t)i * np + c) : make_double2(0.0, 0.0);
     }
-    for (int v = tid; v < 16 * WS; v += kThreads)
-        s_t[v / WS][v % WS] =
-            i0 + v / WS < n && v % WS < w ? la_load(panel + (size_t)i0 * WS + v) : make_double2(0.0, 0.0);
-#pragma unroll
-    for (int h = 0; h < NQ; ++h)
-        if (wave + 4 * h < WS) s_q[wave + 4 * h][lane] = q[h];
+    for (int q = tid; q < 16 * WS; q += kThreads) {
+        const int i = q % 16, j = q / 16;
+        s_f[i][j] = i0 + i < n && j < w ? la_load(mult + (size_t)j * np + i0 + i) : make_double2(0.0, 0.0);
+    }
+    for (int q = tid; q < WS * WS; q += kThreads) {
+        const int t = q % WS, j = q / WS;
+        s_fp[t][j] = t < w && j < w ? la_load(mult + (size_t)j * np + piv[k0 + t]) : make_double2(0.0, 0.0);
+    }
     __syncthreads();
-#pragma unroll 4
-    for (int j = 0; j < w; ++j) {
-        const zc x = s_q[j][lane];
+    if (wave == 0)
+        static_for(std::make_integer_sequence<int, WS>{}, [&](auto s_c) __attribute__((always_inline)) {
+            constexpr int s = decltype(s_c)::value;
+            if (s >= w) return;  // uniform
+            const zc f = la_load(pinv + k0 + s), x = v[s];
+            const zc q = make_double2(__builtin_fma(x.x, f.x, -(x.y * f.y)), __builtin_fma(x.x, f.y, x.y * f.x));
+            s_q[s][lane] = q;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = zfma(s_t[wave + 4 * r][j], x, o[r]);
+            for (int t = s + 1; t < WS; ++t) v[t] = zgj_step(v[t], s_fp[t][s], q);
+        });
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (at[r] >= 0) o[r] = s_q[at[r]][lane];
+#pragma unroll 4
+    for (int s = 0; s < w; ++s) {
+        const zc q = s_q[s][lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (s > at[r]) o[r] = zgj_step(o[r], s_f[wave + 4 * r][s], q);
     }
     const bool own = c >= k0 && c < k0 + w;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + wave + 4 * r;
-        if (own) o[r] = s_t[wave + 4 * r][c - k0];
-        if (i < n) dst[(size_t)i * np + c] = o[r];
+        if (i >= n) continue;
+        if (own) o[r] = la_load(panel + (size_t)i * WS + c - k0);
+        dst[(size_t)i * np + c] = o[r];
     }
 }
 
@@ -438,8 +475,10 @@ __global__ __launch_bounds__(1024) void k_zgj_stat(const zc *__restrict__ pval, 
 // One inversion, of the n x n matrix `host` (which becomes A) or of A: M starts in the buffer from which an even or odd
 // number of updates ends in `work`, and is gathered from there into BT.
 template <int WS, int RPT>
-static hipError_t zgj_invert(const zc *host, zc *a, zc *bt, zc *work, zc *panel, int *slot, int *piv, zc *pval,
-                             double *stat, int n, int np, hipStream_t s) {
+static hipError_t zgj_invert(const zc *host, const ZWalkerDev &d, int n, int np, hipStream_t s) {
+    zc *a = d.a, *bt = d.bt, *work = d.work, *panel = d.panel, *mult = d.mult, *pval = d.pval, *pinv = d.pinv;
+    int *slot = d.slot, *piv = d.piv;
+    double *stat = d.stat;
     const int groups = (n + WS - 1) / WS;
     zc *src = groups % 2 ? bt : work, *dst = groups % 2 ? work : bt;
     if (host) {  // up in one piece (a pitched copy of pageable rows goes row by row: 3 ms at n = 600)
@@ -451,10 +490,11 @@ static hipError_t zgj_invert(const zc *host, zc *a, zc *bt, zc *work, zc *panel,
     const int nt = round_up((n + RPT - 1) / RPT, 64);
     for (int k0 = 0; k0 < n; k0 += WS) {
         const int w = n - k0 < WS ? n - k0 : WS;
-        hipLaunchKernelGGL((k_zgj_group<WS, RPT>), dim3(1), dim3(nt), 0, s, (const zc *)src, panel, slot, piv, pval, np,
-                           n, k0, w);
+        hipLaunchKernelGGL((k_zgj_group<WS, RPT>), dim3(1), dim3(nt), 0, s, (const zc *)src, panel, mult, slot, piv, pval,
+                           pinv, np, n, k0, w);
         hipLaunchKernelGGL((k_zgj_update<WS>), dim3(np / 64, (n + 15) / 16), dim3(kThreads), 0, s, (const zc *)src, dst,
-                           (const zc *)panel, (const int *)slot, (const int *)piv, np, n, k0, w);
+                           (const zc *)panel, (const zc *)mult, (const int *)slot, (const int *)piv, (const zc *)pinv, np,
+                           n, k0, w);
         zc *t = src;
         src = dst;
         dst = t;
@@ -507,7 +547,7 @@ static void zwalker_free(dsu_zwalker *w) {
     for (void *p : {(void *)w->wd.bt, (void *)w->wd.u, (void *)w->wd.vg, (void *)w->wd.a, w->la.phi,
                     (void *)w->wd.cinv, w->la.cinvt, w->la.part, w->la.t, w->la.b, w->la.ratio, (void *)w->wd.idx,
                     (void *)w->la.counter, (void *)w->wd.w, (void *)w->wd.work, (void *)w->wd.panel,
-                    (void *)w->wd.pval, (void *)w->wd.slot, (void *)w->wd.piv, (void *)w->wd.stat, (void *)w->flush_y, (void *)w->flush_w})
+                    (void *)w->wd.mult, (void *)w->wd.pval, (void *)w->wd.pinv, (void *)w->wd.slot, (void *)w->wd.piv, (void *)w->wd.stat, (void *)w->flush_y, (void *)w->flush_w})
         dfree(p);
     if (w->words_h) (void)hipHostFree(w->words_h);
     if (w->row_stage) (void)hipHostFree(w->row_stage);
@@ -524,7 +564,7 @@ static int zwalker_recompute(dsu_zwalker *w, const double *slater_host, double *
                   : n <= 4096 ? zgj_invert<4, 8>
                   : n <= 8192 ? zgj_invert<2, 16>
                               : zgj_invert<1, 32>;
-    HIPCHK(invert(reinterpret_cast<const zc *>(slater_host), d.a, d.bt, d.work, d.panel, d.slot, d.piv, d.pval, d.stat, n, np, w->stream));
+    HIPCHK(invert(reinterpret_cast<const zc *>(slater_host), d, n, np, w->stream));
     double st[3];
     w->piv_h.resize(n);
     HIPCHK(hipMemcpyAsync(st, d.stat, sizeof(st), hipMemcpyDeviceToHost, w->stream));
@@ -629,7 +669,9 @@ extern "C" int dsu_zwalker_create(int32_t n, int32_t k_delay, int32_t policy, co
     TRY(dalloc(&w->wd.w, np * (kp + 1)));
     TRY(dalloc(&w->wd.work, np * np));
     TRY(dalloc(&w->wd.panel, np * 16));
+    TRY(dalloc(&w->wd.mult, np * 16));
     TRY(dalloc(&w->wd.pval, np));
+    TRY(dalloc(&w->wd.pinv, np));
     TRY(dalloc(&w->wd.slot, np));
     TRY(dalloc(&w->wd.piv, np));
     TRY(dalloc(&w->wd.stat, 3));

@@ -202,3 +202,63 @@ def test_zwalker_n512_sampled():
     assert len(errs) == 400 and errs.max() < FP64_TOL
     np.testing.assert_allclose(w.inverse(), ainv, rtol=1e-8, atol=1e-9)
     w.close()
+
+
+def _fma(a, b, c):
+    """fl(a b + c): Dekker's exact product and Knuth's exact sum, then one sum of what they leave."""
+    def halves(x):
+        t = 134217729.0 * x
+        h = t - (t - x)
+        return h, x - h
+    (ah, al), (bh, bl) = halves(a), halves(b)
+    p = a * b
+    e = ((ah * bh - p) + ah * bl + al * bh) + al * bl
+    s = p + c
+    z = s - p
+    return s + (((p - (s - z)) + (c - z)) + e)
+
+
+def _gauss_jordan(a):
+    """A^{-1} by Gauss-Jordan on A^T, a pivot at a time (the largest modulus of the rows left), with fused
+    multiply-adds in the products: the operations that every element of the library's inverse takes, in their order."""
+    n = len(a)
+    x, y = a.T.real.copy(), a.T.imag.copy()
+    free, piv = np.ones(n, bool), np.empty(n, int)
+    for s in range(n):
+        fx, fy = x[:, s].copy(), y[:, s].copy()
+        p = int(np.where(free, _fma(fx, fx, fy * fy), -1.0).argmax())
+        free[p], piv[s] = False, p
+        px, py = fx[p], fy[p]
+        d = _fma(px, px, py * py)
+        ix, iy = px / d, -py / d
+        rx, ry = _fma(x[p], ix, -(y[p] * iy)), _fma(x[p], iy, y[p] * ix)
+        rx[s], ry[s] = ix, iy
+        own = _fma(fy, iy, -(fx * ix)), -_fma(fx, iy, fy * ix)
+        gx, gy = fx[:, None], fy[:, None]
+        x, y = x - _fma(gx, rx, -(gy * ry)), y - _fma(gx, ry, gy * rx)
+        x[:, s], y[:, s] = own
+        x[p], y[p] = rx, ry
+    inv = np.empty((n, n), np.complex128)
+    for i in range(n):
+        inv[piv, i] = x[piv[i]] + 1j * y[piv[i]]
+    return inv
+
+
+@pytest.mark.parametrize("n,seed", [(1, 3), (16, 5), (40, 7), (100, 9), (130, 11)])
+def test_zinverse_takes_the_elimination_s_own_steps(n, seed):
+    """The inversion works on 16 columns at a time, but rounds as the elimination of one column after the other
+    does: it differs from that by less than a tenth of that elimination's own rounding errors (against an inverse
+    refined in extended precision).  A different order of products would differ by about as much as the errors."""
+    require_gpu()
+    a = inputs.dense_matrix(seed, n) + 1j * inputs.dense_matrix(seed + 1, n)
+    ref = _gauss_jordan(a)
+    x, wide = np.linalg.inv(a).astype(np.clongdouble), a.astype(np.clongdouble)
+    x = x + x @ (np.eye(n) - wide @ x)
+    err = float(np.sqrt((np.abs(ref - x) ** 2).mean()))
+    w = dsu.ZWalker(a, 8)
+    new = w.inverse()
+    w.recompute(a)
+    again = w.inverse()
+    w.close()
+    assert np.array_equal(again, new)
+    assert float(np.sqrt((np.abs(new - ref) ** 2).mean())) <= 0.1 * err
