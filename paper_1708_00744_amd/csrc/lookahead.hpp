@@ -262,20 +262,22 @@ __global__ __launch_bounds__(kLaThreads) void k_lookahead(LaDev w, LaSource src,
     __syncthreads();
     double *part = static_cast<double *>(w.part) + (size_t)blockIdx.x * Z * w.ldp;
     const R *xb = s_x + (size_t)(lr < NB ? lr : NB - 1) * ldx + 4 * lk;
-    // FP64 sums; FP32 products in chains of 16 columns, added up in FP64
+    // FP64: the sums of four columns that a matrix instruction makes are added in
+    // pairs, the rounding errors of a chain as long as the row being 1.2 to 1.9
+    // times as large in R; FP32 products in chains of 16 columns, added up in FP64
     f64x4 acc{0, 0, 0, 0};
     for (int g = 0; g < groups; ++g) {
         vec_t cur[16 / VEC];
 #pragma unroll
         for (int h = 0; h < 16 / VEC; ++h) cur[h] = y[h];
         if (g + 1 < groups) load(g + 1);
+        f64x4 sum[16 / VEC];
 #pragma unroll
         for (int h = 0; h < 16 / VEC; ++h) {
             const vec_t bv = *reinterpret_cast<const vec_t *>(xb + 64 * (g % gpt) + 16 * (h / (4 / VEC)) +
                                                               VEC * (h % (4 / VEC)));
             if constexpr (sizeof(R) == 8) {
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) acc = Mma<R>::mma(cur[h][q], bv[q], acc);
+                sum[h] = Mma<R>::mma(cur[h][0], bv[0], f64x4{0, 0, 0, 0}) + Mma<R>::mma(cur[h][1], bv[1], f64x4{0, 0, 0, 0});
             } else {
                 f32x4 part32{0, 0, 0, 0};
 #pragma unroll
@@ -283,6 +285,13 @@ __global__ __launch_bounds__(kLaThreads) void k_lookahead(LaDev w, LaSource src,
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[i] += (double)part32[i];
             }
+        }
+        if constexpr (sizeof(R) == 8) {
+#pragma unroll
+            for (int o = 8 / VEC; o > 0; o /= 2)
+#pragma unroll
+                for (int h = 0; h < o; ++h) sum[h] += sum[h + o];
+            acc += sum[0];
         }
         if (g % gpt != gpt - 1) continue;
         const int r0 = 16 * (wave + kLaWaves * (g / gpt));
@@ -301,9 +310,18 @@ __global__ __launch_bounds__(kLaThreads) void k_lookahead(LaDev w, LaSource src,
             const int v = v0 + lr < md.m ? v0 + lr : md.m - 1;
             const double *t = md.t + (size_t)(c0 + lk) * md.m + v;
             f64x4 acc{0, 0, 0, 0};
-#pragma unroll 8
-            for (int j = 0; j < cols; j += 4)
-                acc = Mma<double>::mma(la_load(t + (size_t)j * md.m), (double)s_x[j + lk], acc);
+            for (int j = 0; j < cols; j += 32) {  // (added in pairs, as above)
+                f64x4 sum[8];
+#pragma unroll
+                for (int h = 0; h < 8; ++h)
+                    sum[h] = Mma<double>::mma(la_load(t + (size_t)(j + 4 * h) * md.m), (double)s_x[j + 4 * h + lk],
+                                              f64x4{0, 0, 0, 0});
+#pragma unroll
+                for (int o = 4; o > 0; o /= 2)
+#pragma unroll
+                    for (int h = 0; h < o; ++h) sum[h] += sum[h + o];
+                acc += sum[0];
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int vo = v0 + lk + 4 * i;
@@ -325,8 +343,19 @@ __global__ __launch_bounds__(kLaThreads) void k_lookahead(LaDev w, LaSource src,
     const S *pt = static_cast<const S *>(w.part);
     for (int v = tid; v < (MD ? nd + md.m : nd); v += kLaThreads) {
         S s = la_zero<S>();
-#pragma unroll 8
-        for (int q = 0; q < nblk; ++q) s = la_add(s, la_load(pt + (size_t)q * w.ldp + v));
+        for (int q = 0; q < nblk; q += 8) {  // (in pairs, as above)
+            S a[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = la_load(pt + (size_t)(q + i < nblk ? q + i : q) * w.ldp + v);
+#pragma unroll
+            for (int i = 1; i < 8; ++i)
+                if (q + i >= nblk) a[i] = la_zero<S>();
+#pragma unroll
+            for (int o = 4; o > 0; o /= 2)
+#pragma unroll
+                for (int i = 0; i < o; ++i) a[i] = la_add(a[i], a[i + o]);
+            s = la_add(s, a[0]);
+        }
         if (GR == 2 && m >= 0 && v == NX * ld + m) s = la_sub(s, la_one<S>());
         if constexpr (MD) {
             if (v >= nd) md.x[v - nd] = md.vphi[v - nd] - s;  // (to be divided by R)
