@@ -31,14 +31,14 @@
 //    every copied row element is independent: one grid of small blocks.
 // Per launch on MI355X, propose then accept, before (row staging + one dot
 // product per block + a serial tail; one accept block) and now: N = 64, K = 16
-// FP64 9.7 + 4.0 -> 6.4 + 2.7 us; N = 1024, K = 64 FP64 19.2 + 9.3 -> 10.5 +
-// 3.0 us; N = 4096, K = 128 FP32 36.4 + 21.6 -> 13.5 + 3.3 us; complex N = 500,
-// K = 16 11.1 + 4.9 -> 9.0 + 2.8 us; multideterminant N = 1024, K = 64, 16
-// virtuals 38.1 + 12.4 -> 17.5 + 4.9 us.  Of the 10.5 us about 2 are the link,
+// FP64 9.7 + 4.0 -> 6.8 + 2.7 us; N = 1024, K = 64 FP64 19.2 + 9.3 -> 10.8 +
+// 3.0 us; N = 4096, K = 128 FP32 36.4 + 21.6 -> 14.0 + 3.3 us; complex N = 500,
+// K = 16 11.1 + 4.9 -> 9.5 + 2.9 us; multideterminant N = 1024, K = 64, 16
+// virtuals 38.1 + 12.4 -> 15.8 + 4.9 us.  Of the 10.8 us about 2 are the link,
 // 1 the products, 1 the count-off, 1.5 the partial sums, 2 the t and b
 // products; instruction fetch is part of each (every line runs once a launch:
 // a 20 KB form of this kernel with the loads of all phases in flight together
-// measured 15 us, this one is under 5 KB).
+// measured 15 us, this one has 5 to 6.4 KB, 13 for the expansion).
 #pragma once
 #include "dsu_internal.hpp"
 #include "tiles.hpp"
@@ -345,11 +345,14 @@ __global__ __launch_bounds__(kLaThreads) void k_lookahead(LaDev w, LaSource src,
         S s = la_zero<S>();
         for (int q = 0; q < nblk; q += 8) {  // (in pairs, as above)
             S a[8];
+            if (q + 8 <= nblk) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = la_load(pt + (size_t)(q + i < nblk ? q + i : q) * w.ldp + v);
+                for (int i = 0; i < 8; ++i) a[i] = la_load(pt + (size_t)(q + i) * w.ldp + v);
+            } else {
 #pragma unroll
-            for (int i = 1; i < 8; ++i)
-                if (q + i >= nblk) a[i] = la_zero<S>();
+                for (int i = 0; i < 8; ++i)
+                    a[i] = q + i < nblk ? la_load(pt + (size_t)(q + i) * w.ldp + v) : la_zero<S>();
+            }
 #pragma unroll
             for (int o = 4; o > 0; o /= 2)
 #pragma unroll
