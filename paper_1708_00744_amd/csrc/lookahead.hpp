@@ -31,10 +31,10 @@
 //    every copied row element is independent: one grid of small blocks.
 // Per launch on MI355X, propose then accept, before (row staging + one dot
 // product per block + a serial tail; one accept block) and now: N = 64, K = 16
-// FP64 9.7 + 4.0 -> 6.8 + 2.7 us; N = 1024, K = 64 FP64 19.2 + 9.3 -> 10.8 +
-// 3.0 us; N = 4096, K = 128 FP32 36.4 + 21.6 -> 14.0 + 3.3 us; complex N = 500,
-// K = 16 11.1 + 4.9 -> 9.5 + 2.9 us; multideterminant N = 1024, K = 64, 16
-// virtuals 38.1 + 12.4 -> 15.8 + 4.9 us.  Of the 10.8 us about 2 are the link,
+// FP64 9.7 + 4.0 -> 6.8 + 2.8 us; N = 1024, K = 64 FP64 19.2 + 9.3 -> 10.7 +
+// 3.0 us; N = 4096, K = 128 FP32 36.4 + 21.6 -> 13.7 + 3.2 us; complex N = 500,
+// K = 16 11.1 + 4.9 -> 9.4 + 2.9 us; multideterminant N = 1024, K = 64, 16
+// virtuals 38.1 + 12.4 -> 15.3 + 4.8 us.  Of the 10.7 us about 2 are the link,
 // 1 the products, 1 the count-off, 1.5 the partial sums, 2 the t and b
 // products; instruction fetch is part of each (every line runs once a launch:
 // a 20 KB form of this kernel with the loads of all phases in flight together
